@@ -197,6 +197,8 @@ sc_status tsdf_integrate_backward(sc_volume* vol, const sc_keyframe* kfs, int32_
         if (!ops) return SC_EDEVICE;
         // op.kf is the keyframe's index in the call: it addresses the pixel gradients
         for (int j = 0; j < cnt; ++j) make_op(vol, &kfs[k0 + j], intr, &T[k0 + j], +1, k0 + j, &ops[j]);
+        const bool dirty = vol->cand_dirty;
+        vol->cand_dirty = true;
         st = run_candidates(vol, ops, cnt, intr, s);
         if (st != SC_OK) return st;
         const int grid = vol->n_cu * 4;
@@ -208,6 +210,8 @@ sc_status tsdf_integrate_backward(sc_volume* vol, const sc_keyframe* kfs, int32_
             adjoint_kernel<SC_COLOR_RGBA8><<<grid, 256, 0, s>>>(vol->d_ops, vol->dev, vol->cand, grad_D, nullptr,
                                                                 grad_depth, nullptr, grad_D0, nullptr, vol->adj_acc,
                                                                 cnt);
+        if (hipPeekAtLastError() != hipSuccess) return SC_EDEVICE;
+        vol->cand_dirty = dirty;
         xi_final_kernel<<<(3 * cnt + 255) / 256, 256, 0, s>>>(vol->adj_acc, 3 * cnt, grad_xi + 6 * (size_t)k0);
     }
     if (grad_D0 && nb > 0)

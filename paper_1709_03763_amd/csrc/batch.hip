@@ -1594,6 +1594,8 @@ sc_status run_candidates(sc_volume* vol, const OpDesc* ops, int n_ops, const sc_
 // stream.
 static sc_status run_chunk(sc_volume* vol, const OpDesc* ops, int n_ops, const sc_intrinsics* in, hipStream_t s)
 {
+    const bool dirty = vol->cand_dirty;
+    vol->cand_dirty = true;
     sc_status st = run_candidates(vol, ops, n_ops, in, s);
     if (st != SC_OK) return st;
     st = stream_in_batch(vol, s);
@@ -1605,6 +1607,7 @@ static sc_status run_chunk(sc_volume* vol, const OpDesc* ops, int n_ops, const s
     const bool timed = vol->timing_n < vol->timing_cap;
     if (timed && hipEventRecord(vol->timing_ev[2 * vol->timing_n], s) != hipSuccess) return SC_EDEVICE;
     if (hipGraphLaunch(main, s) != hipSuccess) return SC_EDEVICE;
+    vol->cand_dirty = dirty;  // the pass empties the candidate table
     if (timed) {
         if (hipEventRecord(vol->timing_ev[2 * vol->timing_n + 1], s) != hipSuccess) return SC_EDEVICE;
         vol->timing_n++;

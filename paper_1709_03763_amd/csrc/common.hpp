@@ -153,6 +153,7 @@ struct sc_volume {
     sc::BatchHdr* h_hdr;     // pinned host staging, two buffers
     uint32_t cand_buckets;
     int parity;              // plain-path candidate counter parity
+    bool cand_dirty;         // a candidate stage was enqueued whose voxel pass was not: entries may be left
     hipStream_t cap_stream;  // private stream used for graph capture
     hipEvent_t staged[2];    // recorded after each staging buffer's descriptors were copied to the device
     int stage;               // staging buffer the next chunk fills
