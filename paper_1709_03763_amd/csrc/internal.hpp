@@ -5,6 +5,30 @@
 
 namespace sc {
 
+// Device scratch (see scratch.cpp): `p` null when there is no memory.  `idle`:
+// the device has finished with the buffer; else it is freed, which waits.
+struct Scratch {
+    unsigned char* p = nullptr;
+    size_t bytes = 0;
+    int device = 0;
+};
+Scratch scratch_take(size_t bytes);
+void scratch_give(Scratch& s, bool idle);
+void scratch_trim();
+
+// Parts of one buffer, 256-byte aligned.
+struct Carve {
+    unsigned char* base;
+    size_t off = 0;
+    template <class T>
+    T* take(size_t n)
+    {
+        T* t = base ? reinterpret_cast<T*>(base + off) : nullptr;
+        off = (off + sizeof(T) * n + 255) & ~size_t(255);
+        return t;
+    }
+};
+
 void fill_u64(uint64_t* p, uint64_t v, size_t n, hipStream_t s);
 void fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s);
 void make_op(const sc_volume* vol, const sc_keyframe* kf, const sc_intrinsics* in, const sc_pose* T, int sign,

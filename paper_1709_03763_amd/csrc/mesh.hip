@@ -611,33 +611,33 @@ sc_status sc_volume_mesh(sc_volume* vol, void* stream, float* tri_xyz, int32_t* 
     hipStream_t s = (hipStream_t)stream;
     const uint32_t n = (uint32_t)nb;
     const uint32_t wgs = (n + 1023u) / 1024u;
+    Scratch buf;
     uint32_t* counts = nullptr;
     uint64_t *offsets = nullptr, *sums = nullptr, *d_total = nullptr;
-    bool ok = hipMalloc(&counts, sizeof(uint32_t) * n) == hipSuccess;
-    ok = ok && hipMalloc(&offsets, sizeof(uint64_t) * n) == hipSuccess;
-    ok = ok && hipMalloc(&sums, sizeof(uint64_t) * wgs) == hipSuccess;
-    ok = ok && hipMalloc(&d_total, sizeof(uint64_t)) == hipSuccess;
-    const bool allocated = ok;
-    uint64_t total = 0;
-    if (ok) {
-        MeshOut cnt{nullptr, nullptr, counts, nullptr, 0};
-        mesh_kernel<<<n, 64, 0, s>>>(vol->dev, cnt);
-        scan_local_kernel<<<wgs, 256, 0, s>>>(counts, offsets, sums, n);
-        scan_sums_kernel<<<1, 256, 0, s>>>(sums, wgs, d_total);
-        scan_add_kernel<<<wgs, 256, 0, s>>>(offsets, sums, n);
-        if (cap > 0 && (tri_xyz || tri_keys)) {
-            MeshOut fill{tri_xyz, tri_keys, nullptr, offsets, cap};
-            mesh_kernel<<<n, 64, 0, s>>>(vol->dev, fill);
-        }
-        ok = hipGetLastError() == hipSuccess;
-        ok = ok && hipMemcpyAsync(&total, d_total, sizeof(total), hipMemcpyDeviceToHost, s) == hipSuccess;
-        ok = ok && hipStreamSynchronize(s) == hipSuccess;
+    for (int pass = 0; pass < 2; ++pass) {
+        Carve c{buf.p};
+        counts = c.take<uint32_t>(n);
+        offsets = c.take<uint64_t>(n);
+        sums = c.take<uint64_t>(wgs);
+        d_total = c.take<uint64_t>(1);
+        if (pass == 0) buf = scratch_take(c.off);
+        if (!buf.p) return SC_ENOMEM;
     }
-    (void)hipFree(counts);
-    (void)hipFree(offsets);
-    (void)hipFree(sums);
-    (void)hipFree(d_total);
-    if (!ok) return allocated ? SC_EDEVICE : SC_ENOMEM;
+    uint64_t total = 0;
+    MeshOut cnt{nullptr, nullptr, counts, nullptr, 0};
+    mesh_kernel<<<n, 64, 0, s>>>(vol->dev, cnt);
+    scan_local_kernel<<<wgs, 256, 0, s>>>(counts, offsets, sums, n);
+    scan_sums_kernel<<<1, 256, 0, s>>>(sums, wgs, d_total);
+    scan_add_kernel<<<wgs, 256, 0, s>>>(offsets, sums, n);
+    if (cap > 0 && (tri_xyz || tri_keys)) {
+        MeshOut fill{tri_xyz, tri_keys, nullptr, offsets, cap};
+        mesh_kernel<<<n, 64, 0, s>>>(vol->dev, fill);
+    }
+    bool ok = hipGetLastError() == hipSuccess;
+    ok = ok && hipMemcpyAsync(&total, d_total, sizeof(total), hipMemcpyDeviceToHost, s) == hipSuccess;
+    ok = ok && hipStreamSynchronize(s) == hipSuccess;
+    scratch_give(buf, ok);
+    if (!ok) return SC_EDEVICE;
     *n_tri = (int64_t)total;
     return SC_OK;
 }
@@ -653,34 +653,29 @@ sc_status sc_mesh_vertices(const float* tri_xyz, const int32_t* tri_keys, int64_
     hipStream_t s = (hipStream_t)stream;
     const int64_t nv = 3 * n_tri;
     const uint32_t slots = pow2_at_least((uint64_t)(2 * nv));
+    Scratch buf;
     uint64_t* table = nullptr;
-    unsigned long long* d_count = nullptr;
-    int* d_err = nullptr;
-    bool ok = hipMalloc(&table, sizeof(uint64_t) * slots) == hipSuccess;
-    ok = ok && hipMalloc(&d_count, sizeof(unsigned long long)) == hipSuccess;
-    ok = ok && hipMalloc(&d_err, sizeof(int)) == hipSuccess;
-    const bool allocated = ok;
-    unsigned long long count = 0;
-    int err = 0;
-    if (ok) {
-        fill_u64(table, kKeyEmpty, slots, s);
-        ok = hipMemsetAsync(d_count, 0, sizeof(unsigned long long), s) == hipSuccess &&
-             hipMemsetAsync(d_err, 0, sizeof(int), s) == hipSuccess;
-        const int64_t per_wg = 256 * kVertPerThread;
-        if (ok)
-            unique_vertex_kernel<<<(unsigned)((nv + per_wg - 1) / per_wg), 256, 0, s>>>(
-                tri_xyz, tri_keys, nv, table, slots - 1, vert_xyz, cap, d_count, d_err);
-        ok = ok && hipGetLastError() == hipSuccess;
-        ok = ok && hipMemcpyAsync(&count, d_count, sizeof(count), hipMemcpyDeviceToHost, s) == hipSuccess;
-        ok = ok && hipMemcpyAsync(&err, d_err, sizeof(int), hipMemcpyDeviceToHost, s) == hipSuccess;
-        ok = ok && hipStreamSynchronize(s) == hipSuccess;
+    unsigned long long* d_count = nullptr;  // the count, then the error word
+    for (int pass = 0; pass < 2; ++pass) {
+        Carve c{buf.p};
+        table = c.take<uint64_t>(slots);
+        d_count = c.take<unsigned long long>(2);
+        if (pass == 0) buf = scratch_take(c.off);
+        if (!buf.p) return SC_ENOMEM;
     }
-    (void)hipFree(table);
-    (void)hipFree(d_count);
-    (void)hipFree(d_err);
-    if (!ok) return allocated ? SC_EDEVICE : SC_ENOMEM;
-    if (err) return SC_ERANGE;
-    *n_vert = (int64_t)count;
+    unsigned long long got[2] = {0, 0};
+    fill_u64(table, kKeyEmpty, slots, s);
+    fill_u64(reinterpret_cast<uint64_t*>(d_count), 0ull, 2, s);
+    const int64_t per_wg = 256 * kVertPerThread;
+    unique_vertex_kernel<<<(unsigned)((nv + per_wg - 1) / per_wg), 256, 0, s>>>(
+        tri_xyz, tri_keys, nv, table, slots - 1, vert_xyz, cap, d_count, reinterpret_cast<int*>(d_count + 1));
+    bool ok = hipGetLastError() == hipSuccess;
+    ok = ok && hipMemcpyAsync(got, d_count, sizeof(got), hipMemcpyDeviceToHost, s) == hipSuccess;
+    ok = ok && hipStreamSynchronize(s) == hipSuccess;
+    scratch_give(buf, ok);
+    if (!ok) return SC_EDEVICE;
+    if (got[1]) return SC_ERANGE;
+    *n_vert = (int64_t)got[0];
     return SC_OK;
 }
 
@@ -697,43 +692,36 @@ sc_status sc_nn_distance(const float* ref, int64_t n_ref, const float* query, in
     g.inv = 1.0f / (radius * (1.0f + 1.0f / 64.0f));
     const uint32_t slots = pow2_at_least((uint64_t)(2 * std::max<int64_t>(n_ref, 1)));
     g.mask = slots - 1;
+    Scratch buf;
     uint32_t* slot_of = nullptr;
     uint32_t* total = nullptr;
-    bool ok = true, allocated = true;
-    if (n_ref > 0) {
-        ok = ok && hipMalloc(&g.keys, sizeof(uint64_t) * slots) == hipSuccess;
-        ok = ok && hipMalloc(&g.cnt, sizeof(uint32_t) * slots) == hipSuccess;
-        ok = ok && hipMalloc(&g.off, sizeof(uint32_t) * slots) == hipSuccess;
-        ok = ok && hipMalloc(&g.cur, sizeof(uint32_t) * slots) == hipSuccess;
-        ok = ok && hipMalloc(&g.pts, sizeof(float) * 3 * (size_t)n_ref) == hipSuccess;
-        ok = ok && hipMalloc(&slot_of, sizeof(uint32_t) * (size_t)n_ref) == hipSuccess;
-        ok = ok && hipMalloc(&total, sizeof(uint32_t)) == hipSuccess;
-        allocated = ok;
-        if (ok) {
-            fill_u64(g.keys, kKeyEmpty, slots, s);
-            fill_u32(g.cnt, 0u, slots, s);
-            fill_u32(g.cur, 0u, slots, s);
-            fill_u32(total, 0u, 1, s);
-            const unsigned grid_r = (unsigned)((n_ref + 255) / 256);
-            nn_count_kernel<<<grid_r, 256, 0, s>>>(ref, n_ref, g, slot_of);
-            nn_offset_kernel<<<(slots + 256 * kSlotsPerThread - 1) / (256 * kSlotsPerThread), 256, 0, s>>>(g, slots,
-                                                                                                          total);
-            nn_scatter_kernel<<<grid_r, 256, 0, s>>>(ref, n_ref, g, slot_of);
-        }
+    for (int pass = 0; pass < 2 && n_ref > 0; ++pass) {
+        Carve c{buf.p};
+        g.keys = c.take<uint64_t>(slots);
+        g.cnt = c.take<uint32_t>(slots);
+        g.off = c.take<uint32_t>(slots);
+        g.cur = c.take<uint32_t>(slots);
+        g.pts = c.take<float>(3 * (size_t)n_ref);
+        slot_of = c.take<uint32_t>((size_t)n_ref);
+        total = c.take<uint32_t>(1);
+        if (pass == 0) buf = scratch_take(c.off);
+        if (!buf.p) return SC_ENOMEM;
     }
-    if (ok)
-        nn_query_kernel<<<(unsigned)((n_query + 255) / 256), 256, 0, s>>>(query, n_query, g, n_ref == 0, radius, dist,
-                                                                          sum);
-    ok = ok && hipGetLastError() == hipSuccess;
+    if (n_ref > 0) {
+        fill_u64(g.keys, kKeyEmpty, slots, s);
+        fill_u32(g.cnt, 0u, slots, s);
+        fill_u32(g.cur, 0u, slots, s);
+        fill_u32(total, 0u, 1, s);
+        const unsigned grid_r = (unsigned)((n_ref + 255) / 256);
+        nn_count_kernel<<<grid_r, 256, 0, s>>>(ref, n_ref, g, slot_of);
+        nn_offset_kernel<<<(slots + 256 * kSlotsPerThread - 1) / (256 * kSlotsPerThread), 256, 0, s>>>(g, slots, total);
+        nn_scatter_kernel<<<grid_r, 256, 0, s>>>(ref, n_ref, g, slot_of);
+    }
+    nn_query_kernel<<<(unsigned)((n_query + 255) / 256), 256, 0, s>>>(query, n_query, g, n_ref == 0, radius, dist, sum);
+    bool ok = hipGetLastError() == hipSuccess;
     ok = ok && hipStreamSynchronize(s) == hipSuccess;
-    (void)hipFree(g.keys);
-    (void)hipFree(g.cnt);
-    (void)hipFree(g.off);
-    (void)hipFree(g.cur);
-    (void)hipFree(g.pts);
-    (void)hipFree(slot_of);
-    (void)hipFree(total);
-    return ok ? SC_OK : (allocated ? SC_EDEVICE : SC_ENOMEM);
+    scratch_give(buf, ok);
+    return ok ? SC_OK : SC_EDEVICE;
 }
 
 }  // extern "C"

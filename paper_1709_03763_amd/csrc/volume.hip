@@ -787,6 +787,7 @@ void sc_volume_destroy(sc_volume* vol)
         if (e) hipEventDestroy(e);
     rec_destroy(vol);
     stream_destroy(vol);
+    scratch_trim();
     delete vol;
 }
 
@@ -833,8 +834,9 @@ sc_status sc_volume_import(sc_volume* vol, void* stream, const int32_t* block_xy
         return SC_EINVAL;
     if (n == 0) return SC_OK;
     hipStream_t s = (hipStream_t)stream;
-    int32_t* slots = nullptr;
-    HIP_TRY(hipMalloc(&slots, sizeof(int32_t) * (size_t)n));
+    Scratch buf = scratch_take(sizeof(int32_t) * (size_t)n);
+    if (!buf.p) return SC_EDEVICE;
+    int32_t* slots = reinterpret_cast<int32_t*>(buf.p);
     sc_status st = hash_alloc(vol, block_xyz, n, slots, stream);
     if (st == SC_OK) {
         import_kernel<<<(unsigned)n, 256, 0, s>>>(vol->dev, slots, n, D, W, C);
@@ -843,7 +845,7 @@ sc_status sc_volume_import(sc_volume* vol, void* stream, const int32_t* block_xy
     int64_t nb = 0;
     int32_t sticky = 0;
     if (st == SC_OK) st = sc_volume_query(vol, stream, &nb, &sticky);
-    (void)hipFree(slots);
+    scratch_give(buf, st == SC_OK);
     if (st != SC_OK) return st;
     return sticky;
 }
