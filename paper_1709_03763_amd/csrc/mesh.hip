@@ -449,16 +449,28 @@ __global__ __launch_bounds__(256) void unique_vertex_kernel(const float* __restr
 // radius (1 + 2^-6): a point within the radius of a query lies in one of the
 // 27 cells around the query's cell (the margin absorbs the rounding of the
 // FP32 cell coordinate while |x| / radius stays below about 10^5)
+//
+// The cells are found by hashing, a cell's key, first point and count in one
+// 16-byte entry (one load a probe), the points sorted by cell as 16 bytes
+// each.  Build: every point finds or inserts its cell and takes its rank in
+// it (lanes of a wavefront in one cell share one atomic; coherent clouds put
+// tens of points in a row into a cell), the inserted cells, listed, get their
+// ranges, and the points are stored at range + rank.
 // ---------------------------------------------------------------------------
 
+struct NnCell {
+    unsigned long long key;  // kKeyEmpty = free
+    uint32_t off, cnt;       // points [off, off + cnt) of `pts`
+};
+
 struct NnGrid {
-    uint64_t* keys;   // cell key per slot (kKeyEmpty = free)
-    uint32_t* cnt;    // points per slot
-    uint32_t* off;    // first point of each slot in `pts`
-    uint32_t* cur;    // scatter cursor per slot
-    float* pts;       // reference points sorted by slot (x, y, z)
+    NnCell* cells;
+    float4* pts;       // reference points sorted by cell (x, y, z, -)
+    uint32_t* list;    // slots of the occupied cells
+    uint32_t* counts;  // [0] listed cells, [32] points given a range (its own line)
     uint32_t mask;
-    float inv;        // 1 / cell edge
+    float inv;         // 1 / cell edge
+    float edge;
 };
 
 __device__ inline int nn_cell(float x, float inv)
@@ -467,111 +479,227 @@ __device__ inline int nn_cell(float x, float inv)
     return (int)fminf(fmaxf(c, -1.0e6f), 1.0e6f);
 }
 
-__device__ inline int nn_find(const NnGrid& g, int cx, int cy, int cz)
+__global__ __launch_bounds__(256) void nn_clear_kernel(NnGrid g)
 {
-    const uint64_t key = pack_key(cx, cy, cz);
-    uint32_t h = hash_block(cx, cy, cz) & g.mask;
-    for (uint32_t probe = 0; probe <= g.mask; ++probe) {
-        const uint64_t k = g.keys[h];
-        if (k == key) return (int)h;
-        if (k == kKeyEmpty) return -1;
-        h = (h + 1) & g.mask;
-    }
-    return -1;
+    const uint64_t n = (uint64_t)g.mask + 1;
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+        reinterpret_cast<uint4*>(g.cells)[i] = make_uint4(~0u, ~0u, 0u, 0u);
+    if (blockIdx.x == 0 && threadIdx.x < 2) g.counts[32 * threadIdx.x] = 0u;
 }
 
+constexpr int kNnPer = 8;  // points per thread: one reservation in the cell list per 2048
+
+// Slot and rank of every point.  Bound: the latency of the probes and of one
+// atomic a round.
 __global__ __launch_bounds__(256) void nn_count_kernel(const float* __restrict__ ref, int64_t n, NnGrid g,
-                                                       uint32_t* slot_of)
+                                                       uint2* slot_rank)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int cx = nn_cell(ref[3 * i], g.inv), cy = nn_cell(ref[3 * i + 1], g.inv), cz = nn_cell(ref[3 * i + 2], g.inv);
-    const uint64_t key = pack_key(cx, cy, cz);
-    uint32_t h = hash_block(cx, cy, cz) & g.mask;
-    for (uint32_t probe = 0; probe <= g.mask; ++probe) {
-        const uint64_t old =
-            atomicCAS((unsigned long long*)(g.keys + h), (unsigned long long)kKeyEmpty, (unsigned long long)key);
-        if (old == kKeyEmpty || old == key) break;
-        h = (h + 1) & g.mask;
+    __shared__ uint32_t fresh[256 * kNnPer];
+    __shared__ uint32_t n_fresh, base;
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x == 0) n_fresh = 0u;
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * (256 * kNnPer) + threadIdx.x;
+    for (int k = 0; k < kNnPer; ++k) {
+        const int64_t i = i0 + 256 * k;
+        const bool have = i < n;
+        uint32_t h = ~0u;
+        if (have) {
+            const int cx = nn_cell(ref[3 * i], g.inv), cy = nn_cell(ref[3 * i + 1], g.inv),
+                      cz = nn_cell(ref[3 * i + 2], g.inv);
+            const uint64_t key = pack_key(cx, cy, cz);
+            h = hash_block(cx, cy, cz) & g.mask;
+            // at least as many slots as points: the probe ends
+            for (uint32_t probe = 0; probe <= g.mask; ++probe) {
+                // entries only go from free to a key, so a plain read that finds the key is reliable
+                const uint64_t seen = g.cells[h].key;
+                if (seen == key) break;
+                if (seen == kKeyEmpty) {
+                    const uint64_t old = atomicCAS(&g.cells[h].key, (unsigned long long)kKeyEmpty,
+                                                   (unsigned long long)key);
+                    if (old == kKeyEmpty) {
+                        fresh[atomicAdd(&n_fresh, 1u)] = h;
+                        break;
+                    }
+                    if (old == key) break;
+                }
+                h = (h + 1) & g.mask;
+            }
+        }
+        // lanes of one cell: the lowest one adds them all, each takes its place among them
+        uint32_t rank = 0u, total = 0u;
+        int leader = lane;
+        uint64_t todo = __ballot(have);
+        while (todo) {
+            const int l = __ffsll((unsigned long long)todo) - 1;
+            const uint64_t same = __ballot(h == (uint32_t)__builtin_amdgcn_readlane(h, l));
+            if (h == (uint32_t)__builtin_amdgcn_readlane(h, l)) {
+                rank = lanes_below(same);
+                total = (uint32_t)__popcll(same);
+                leader = l;
+            }
+            todo &= ~same;
+        }
+        uint32_t first = 0u;
+        if (have && lane == leader) first = atomicAdd(&g.cells[h].cnt, total);
+        first = (uint32_t)__shfl((int)first, leader);
+        if (have) slot_rank[i] = make_uint2(h, first + rank);
     }
-    slot_of[i] = h;
-    atomicAdd(g.cnt + h, 1u);
+    __syncthreads();
+    if (threadIdx.x == 0) base = n_fresh ? atomicAdd(g.counts, n_fresh) : 0u;
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < n_fresh; j += blockDim.x) g.list[base + j] = fresh[j];
 }
 
-constexpr int kSlotsPerThread = 16;  // grid slots per thread: one reservation per 4096
-
-// Offsets: a workgroup scans its 4096 slots and reserves their range with one
-// atomic (ranges of different workgroups need not be in slot order).
-__global__ __launch_bounds__(256) void nn_offset_kernel(NnGrid g, uint32_t n_slots, uint32_t* total)
+// Ranges of the listed cells: a workgroup scans 256 counts and reserves their
+// range with one atomic (the ranges need not be in cell order).
+__global__ __launch_bounds__(256) void nn_offset_kernel(NnGrid g)
 {
-    __shared__ uint32_t part[256];
+    __shared__ uint32_t part[4];
     __shared__ uint32_t base;
-    const uint32_t i0 = (blockIdx.x * 256u + threadIdx.x) * kSlotsPerThread;
-    uint32_t mine = 0u;
-    for (int k = 0; k < kSlotsPerThread; ++k)
-        if (i0 + k < n_slots) mine += g.cnt[i0 + k];
-    part[threadIdx.x] = mine;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        const uint32_t y = (threadIdx.x >= (unsigned)o) ? part[threadIdx.x - o] : 0u;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t n = g.counts[0];
+    for (uint32_t j0 = blockIdx.x * 256u; j0 < n; j0 += gridDim.x * 256u) {
+        const uint32_t j = j0 + threadIdx.x;
+        const uint32_t h = j < n ? g.list[j] : 0u;
+        const uint32_t c = j < n ? g.cells[h].cnt : 0u;
+        uint32_t incl = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(incl, o);
+            incl += (lane >= o) ? y : 0u;
+        }
+        if (lane == 63) part[wave] = incl;
         __syncthreads();
-        part[threadIdx.x] += y;
+        if (threadIdx.x == 0) base = atomicAdd(g.counts + 32, part[0] + part[1] + part[2] + part[3]);
+        __syncthreads();
+        uint32_t off = base + incl - c;
+        for (int w = 0; w < wave; ++w) off += part[w];
+        if (j < n) g.cells[h].off = off;
         __syncthreads();
     }
-    if (threadIdx.x == 255) base = atomicAdd(total, part[255]);
-    __syncthreads();
-    uint32_t off = base + part[threadIdx.x] - mine;
-    for (int k = 0; k < kSlotsPerThread; ++k)
-        if (i0 + k < n_slots) {
-            g.off[i0 + k] = off;
-            off += g.cnt[i0 + k];
-        }
 }
 
 __global__ __launch_bounds__(256) void nn_scatter_kernel(const float* __restrict__ ref, int64_t n, NnGrid g,
-                                                         const uint32_t* __restrict__ slot_of)
+                                                         const uint2* __restrict__ slot_rank)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const uint32_t h = slot_of[i];
-    const uint32_t pos = g.off[h] + atomicAdd(g.cur + h, 1u);
-    g.pts[3 * (size_t)pos] = ref[3 * i];
-    g.pts[3 * (size_t)pos + 1] = ref[3 * i + 1];
-    g.pts[3 * (size_t)pos + 2] = ref[3 * i + 2];
+    const uint2 s = slot_rank[i];
+    g.pts[g.cells[s.x].off + s.y] = make_float4(ref[3 * i], ref[3 * i + 1], ref[3 * i + 2], 0.0f);
 }
 
-__global__ __launch_bounds__(256) void nn_query_kernel(const float* __restrict__ q, int64_t n, NnGrid g, bool empty,
-                                                       float radius, float* dist, double* sum)
+// The 27 cells, the query's own first, then those sharing a face, an edge, a
+// corner: (dx + 1) | (dy + 1) << 2 | (dz + 1) << 4.
+struct NnOrder {
+    uint8_t v[27];
+};
+constexpr NnOrder nn_order()
 {
+    NnOrder o{};
+    int n = 0;
+    for (int away = 0; away <= 3; ++away)
+        for (int z = 0; z < 3; ++z)
+            for (int y = 0; y < 3; ++y)
+                for (int x = 0; x < 3; ++x)
+                    if ((x != 1) + (y != 1) + (z != 1) == away) o.v[n++] = (uint8_t)(x | (y << 2) | (z << 4));
+    return o;
+}
+static __device__ constexpr NnOrder kNnOrder = nn_order();
+
+// One thread per query.  The query's own cell comes first; another cell is
+// looked up only when its box is nearer than the best distance so far (and
+// the radius), which leaves one or two of the 27 for a query near the
+// surface.  The box distance is taken low by 2^-21 of the coordinate and the
+// edge, more than the roundings of the cell coordinate and of the products
+// here, so that a cell holding a nearer point is never left out and the
+// minimum is that over all 27 cells.  Bound: the latency of the probes and of
+// the points' loads, 64 addresses each (1.0 M random queries against 2.0 M
+// vertices, radius five voxels: 2036 us with every cell read, in three 4-byte
+// loads a point, 381 us so; a call with its grid 2.6 -> 0.5 ms).
+// The distances' sum: per-workgroup partials in FP64, added by nn_sum_kernel
+// (one atomic a wavefront on the sum had serialised).
+__global__ __launch_bounds__(256) void nn_query_kernel(const float* __restrict__ q, int64_t n, NnGrid g, bool empty,
+                                                       float radius, float* dist, double* partial)
+{
+    __shared__ double part[4];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     double mine = 0.0;
     if (i < n) {
-        const float x = q[3 * i], y = q[3 * i + 1], z = q[3 * i + 2];
+        const float x[3] = {q[3 * i], q[3 * i + 1], q[3 * i + 2]};
         float best = __builtin_inff();
         if (!empty) {
-            const int cx = nn_cell(x, g.inv), cy = nn_cell(y, g.inv), cz = nn_cell(z, g.inv);
-            for (int dz = -1; dz <= 1; ++dz)
-                for (int dy = -1; dy <= 1; ++dy)
-                    for (int dx = -1; dx <= 1; ++dx) {
-                        const int h = nn_find(g, cx + dx, cy + dy, cz + dz);
-                        if (h < 0) continue;
-                        const uint32_t a = g.off[h], e = a + g.cnt[h];
-                        for (uint32_t k = a; k < e; ++k) {
-                            const float ex = x - g.pts[3 * (size_t)k];
-                            const float ey = y - g.pts[3 * (size_t)k + 1];
-                            const float ez = z - g.pts[3 * (size_t)k + 2];
-                            best = fminf(best, (ex * ex + ey * ey) + ez * ez);
-                        }
+            int c[3];
+            float lo[3], hi[3];  // squared distance to the cells below and above along each axis
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                c[r] = nn_cell(x[r], g.inv);
+                const float m = 0x1p-21f * (fabsf(x[r]) + g.edge);
+                const float a = fmaxf(x[r] - (float)c[r] * g.edge - m, 0.0f);
+                const float b = fmaxf((float)(c[r] + 1) * g.edge - x[r] - m, 0.0f);
+                lo[r] = a * a;
+                hi[r] = b * b;
+            }
+            // nothing beyond the radius counts
+            const float cap = radius * radius * (1.0f + 0x1p-16f);
+            for (int j = 0; j < 27; ++j) {
+                const int o = kNnOrder.v[j];
+                const int d[3] = {(o & 3) - 1, ((o >> 2) & 3) - 1, (o >> 4) - 1};
+                float away = 0.0f;
+#pragma unroll
+                for (int r = 0; r < 3; ++r) away += d[r] < 0 ? lo[r] : d[r] > 0 ? hi[r] : 0.0f;
+                if (away * (1.0f - 0x1p-20f) > fminf(best, cap)) continue;
+                const int cx = c[0] + d[0], cy = c[1] + d[1], cz = c[2] + d[2];
+                const uint64_t key = pack_key(cx, cy, cz);
+                uint32_t h = hash_block(cx, cy, cz) & g.mask;
+                uint32_t a = 0u, e = 0u;
+                for (uint32_t probe = 0; probe <= g.mask; ++probe) {
+                    const uint4 w = reinterpret_cast<const uint4*>(g.cells)[h];
+                    const uint64_t k = ((uint64_t)w.y << 32) | w.x;
+                    if (k == key) {
+                        a = w.z;
+                        e = w.z + w.w;
                     }
+                    if (k == key || k == kKeyEmpty) break;
+                    h = (h + 1) & g.mask;
+                }
+#pragma unroll 4
+                for (uint32_t k = a; k < e; ++k) {
+                    const float4 p = g.pts[k];
+                    const float ex = x[0] - p.x;
+                    const float ey = x[1] - p.y;
+                    const float ez = x[2] - p.z;
+                    best = fminf(best, (ex * ex + ey * ey) + ez * ez);
+                }
+            }
         }
         const float d = fminf(sqrtf(best), radius);
         if (dist) dist[i] = d;
         mine = (double)d;
     }
-    if (sum) {
+    if (partial) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
-        if ((threadIdx.x & 63) == 0 && i - (threadIdx.x & 63) < n) atomicAdd(sum, mine);  // not a loop
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mine;
+        __syncthreads();
+        if (threadIdx.x == 0) partial[blockIdx.x] = (part[0] + part[1]) + (part[2] + part[3]);
+    }
+}
+
+// The partials' sum, by one workgroup.
+__global__ __launch_bounds__(1024) void nn_sum_kernel(const double* __restrict__ partial, int64_t n, double* sum)
+{
+    __shared__ double part[16];
+    double mine = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) mine += partial[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < 16; ++w) s += part[w];
+        *sum = s;
     }
 }
 
@@ -686,38 +814,41 @@ sc_status sc_nn_distance(const float* ref, int64_t n_ref, const float* query, in
         !(radius < 1.0e30f) || n_ref > ((int64_t)1 << 29) || n_query > ((int64_t)1 << 31))
         return SC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    if (sum && hipMemsetAsync(sum, 0, sizeof(double), s) != hipSuccess) return SC_EDEVICE;
-    if (n_query == 0) return hipStreamSynchronize(s) == hipSuccess ? SC_OK : SC_EDEVICE;
+    if (n_query == 0) {
+        if (sum) fill_u64(reinterpret_cast<uint64_t*>(sum), 0ull, 1, s);
+        return hipStreamSynchronize(s) == hipSuccess ? SC_OK : SC_EDEVICE;
+    }
     NnGrid g{};
-    g.inv = 1.0f / (radius * (1.0f + 1.0f / 64.0f));
+    g.edge = radius * (1.0f + 1.0f / 64.0f);
+    g.inv = 1.0f / g.edge;
     const uint32_t slots = pow2_at_least((uint64_t)(2 * std::max<int64_t>(n_ref, 1)));
     g.mask = slots - 1;
+    const int64_t wgs = (n_query + 255) / 256;
     Scratch buf;
-    uint32_t* slot_of = nullptr;
-    uint32_t* total = nullptr;
-    for (int pass = 0; pass < 2 && n_ref > 0; ++pass) {
+    uint2* slot_rank = nullptr;
+    double* partial = nullptr;
+    for (int pass = 0; pass < 2; ++pass) {
         Carve c{buf.p};
-        g.keys = c.take<uint64_t>(slots);
-        g.cnt = c.take<uint32_t>(slots);
-        g.off = c.take<uint32_t>(slots);
-        g.cur = c.take<uint32_t>(slots);
-        g.pts = c.take<float>(3 * (size_t)n_ref);
-        slot_of = c.take<uint32_t>((size_t)n_ref);
-        total = c.take<uint32_t>(1);
+        partial = c.take<double>(sum ? (size_t)wgs : 1);
+        if (n_ref > 0) {
+            g.cells = c.take<NnCell>(slots);
+            g.pts = c.take<float4>((size_t)n_ref);
+            slot_rank = c.take<uint2>((size_t)n_ref);
+            g.list = c.take<uint32_t>((size_t)n_ref);
+            g.counts = c.take<uint32_t>(64);
+        }
         if (pass == 0) buf = scratch_take(c.off);
         if (!buf.p) return SC_ENOMEM;
     }
     if (n_ref > 0) {
-        fill_u64(g.keys, kKeyEmpty, slots, s);
-        fill_u32(g.cnt, 0u, slots, s);
-        fill_u32(g.cur, 0u, slots, s);
-        fill_u32(total, 0u, 1, s);
-        const unsigned grid_r = (unsigned)((n_ref + 255) / 256);
-        nn_count_kernel<<<grid_r, 256, 0, s>>>(ref, n_ref, g, slot_of);
-        nn_offset_kernel<<<(slots + 256 * kSlotsPerThread - 1) / (256 * kSlotsPerThread), 256, 0, s>>>(g, slots, total);
-        nn_scatter_kernel<<<grid_r, 256, 0, s>>>(ref, n_ref, g, slot_of);
+        nn_clear_kernel<<<(unsigned)std::min<uint32_t>(slots / 256, 4096), 256, 0, s>>>(g);
+        nn_count_kernel<<<(unsigned)((n_ref + 256 * kNnPer - 1) / (256 * kNnPer)), 256, 0, s>>>(ref, n_ref, g,
+                                                                                               slot_rank);
+        nn_offset_kernel<<<(unsigned)std::min<int64_t>((n_ref + 255) / 256, 1024), 256, 0, s>>>(g);
+        nn_scatter_kernel<<<(unsigned)((n_ref + 255) / 256), 256, 0, s>>>(ref, n_ref, g, slot_rank);
     }
-    nn_query_kernel<<<(unsigned)((n_query + 255) / 256), 256, 0, s>>>(query, n_query, g, n_ref == 0, radius, dist, sum);
+    nn_query_kernel<<<(unsigned)wgs, 256, 0, s>>>(query, n_query, g, n_ref == 0, radius, dist, sum ? partial : nullptr);
+    if (sum) nn_sum_kernel<<<1, 1024, 0, s>>>(partial, wgs, sum);
     bool ok = hipGetLastError() == hipSuccess;
     ok = ok && hipStreamSynchronize(s) == hipSuccess;
     scratch_give(buf, ok);
