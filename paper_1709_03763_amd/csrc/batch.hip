@@ -959,99 +959,6 @@ __global__ __launch_bounds__(256) void batch_pipe_kernel(const OpDesc* __restric
 // wait for the current step's samples leaves them in flight.
 // ---------------------------------------------------------------------------
 
-// A block's geometry under one operation: the lane's FP32 camera point of
-// voxel (x, y, 0) of its column, and the camera z of the block origin in FP64.
-struct RingGeom {
-    float base[3];
-    double qz;
-};
-
-__device__ inline void ring_geom(const OpDesc& o, const VolDev& v, const PipeBlock& pb, int lane, RingGeom& g)
-{
-    float q[3];
-    block_origin(o, v.s, pb.bx, pb.by, pb.bz, q, g.qz);
-    const float kx = (float)(lane & 7), ky = (float)(lane >> 3);
-#pragma unroll
-    for (int r = 0; r < 3; ++r) g.base[r] = (q[r] + kx * o.a[0][r]) + ky * o.a[1][r];
-}
-
-typedef __attribute__((address_space(1))) const unsigned char GlobalBytes;
-typedef __attribute__((address_space(1))) const float GlobalF32;
-typedef __attribute__((address_space(1))) const uint32_t GlobalU32;
-
-// Element `i` of a keyframe array through a 32-bit byte offset from a
-// uniform base (a global load with a scalar base and a vector offset).
-template <class T, class G>
-__device__ inline T kf_load(const void* base, uint32_t i)
-{
-    return *(G*)((GlobalBytes*)base + i * (uint32_t)sizeof(T));
-}
-
-// The lane's voxels in z-slices kz0 .. kz0 + 3 of one (block, operation)
-// after their gathers: the camera z (NaN for a voxel outside the image, so
-// that its band test fails), the pixel, and the keyframe sample there (pixel
-// 0 for a voxel outside the image).
-template <int CM>
-struct RingFetch {
-    float pz[4], wr[4], z[4];
-    uint32_t pix[4];
-    uint32_t c[4];  // RGBA8 colour at the pixel (RGBA8 mode)
-};
-
-// Projections of the lane's voxels in z-slices kz0 .. kz0 + 3 and their
-// keyframe gathers: one record per voxel from a packed keyframe, else depth,
-// weight and (RGBA8) colour.  The z steps k a_z are the descriptor's
-// host-rounded products, equal to the FP32 products of the convention.
-template <int CM, bool kPacked>
-__device__ inline void ring_fetch(const OpDesc& o, const RingGeom& g, int kz0, RingFetch<CM>& f)
-{
-    // the operation's constants, read together at the top
-    const ProjConst k = proj_const(o);
-    float za[4][3];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 3; ++r) za[j][r] = o.za[kz0 + j][r];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float px = g.base[0] + za[j][0];
-        const float py = g.base[1] + za[j][1];
-        const float pz = g.base[2] + za[j][2];
-        bool in;
-        f.pix[j] = pixel_index_fast(k, px, py, pz, in);
-        f.pz[j] = in ? pz : __builtin_nanf("");
-    }
-    if (kPacked) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            // the record's first three words, adjacent: one 12-byte load
-            const uint32_t i = 4u * f.pix[j];
-            f.z[j] = __uint_as_float(kf_load<uint32_t, GlobalU32>(o.packed, i));
-            f.wr[j] = __uint_as_float(kf_load<uint32_t, GlobalU32>(o.packed, i + 1u));
-            f.c[j] = kf_load<uint32_t, GlobalU32>(o.packed, i + 2u);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            f.wr[j] = kf_load<float, GlobalF32>(o.weight, f.pix[j]);
-            f.z[j] = kf_load<float, GlobalF32>(o.depth, f.pix[j]);
-            f.c[j] = (CM == SC_COLOR_RGBA8) ? kf_load<uint32_t, GlobalU32>(o.color, f.pix[j]) : 0u;
-        }
-    }
-}
-
-// Touched decisions of fetched voxels; with kPacked the weight is already
-// quantised and the depth of a pixel without weight is -inf.
-template <int CM, bool kPacked>
-__device__ inline void ring_decide(const RingFetch<CM>& f, float mu, float w[4], bool t[4])
-{
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        w[j] = kPacked ? f.wr[j] : qweight(f.wr[j]);
-        t[j] = (kPacked || w[j] > 0.0f) && fabsf(f.z[j] - f.pz[j]) <= mu;
-    }
-}
-
 // The operations of a block in bit order, its mask words held one per lane
 // (loaded once per block, so the walk issues no load that a wait could
 // confuse with the keyframe gathers in flight).  words <= 64.
@@ -1145,7 +1052,7 @@ __device__ inline bool ring_step(const OpDesc* __restrict__ ops, const VolDev& v
         part_n = 0;
     }
     RingGeom gn = gc;
-    if (part_n == 0 && op_n >= 0) ring_geom(ops[op_n], v, pb, lane, gn);
+    if (part_n == 0 && op_n >= 0) ring_geom(ops[op_n], v, pb.bx, pb.by, pb.bz, lane, gn);
     // issued on every step (a block's last step fetches its own part again),
     // so the number of loads in flight is the same on every path
     ring_fetch<CM, kPacked>(ops[op_n >= 0 ? op_n : op_c], gn, 4 * (op_n >= 0 ? part_n : part_c), nxt);
@@ -1265,7 +1172,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void b
         RingFetch<CM> f0, f1;
         RingGeom gc;
         if (op_c >= 0) {
-            ring_geom(ops[op_c], v, pb, lane, gc);
+            ring_geom(ops[op_c], v, pb.bx, pb.by, pb.bz, lane, gc);
             ring_fetch<CM, kPacked>(ops[op_c], gc, 0, f0);
         }
         if (CM == SC_COLOR_RGBA8) {

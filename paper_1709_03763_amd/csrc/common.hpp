@@ -108,7 +108,7 @@ struct CandDev {
     uint32_t* sorted;     // occupied buckets ordered by operation count (batched path), one per bucket
     uint64_t* skey;       // block key of each sorted entry
     int32_t* sslot;       // pool slot of each sorted entry's block before the pass (-1: not allocated)
-    uint32_t* counters;   // [0..1] list length (parity), [2..3] work cursor (parity),
+    uint32_t* counters;   // [0..1] list length of the plain path (parity),
                           // [4] batch candidates, [5] batch work cursor, [6] batch tile cursor
     uint32_t* bins;       // per-operation-count histogram / offsets (batched path)
     uint32_t* cursors;    // two sets (candidate stage, voxel pass) of kCursors work cursors, kCursorStride words apart

@@ -400,6 +400,99 @@ __device__ inline void test_voxels(const OpDesc& op, float mu, const float base[
     decide_voxels<CM, VPL>(f, mu, h);
 }
 
+// A block's geometry under one operation: the lane's FP32 camera point of
+// voxel (x, y, 0) of its column, and the camera z of the block origin in FP64.
+struct RingGeom {
+    float base[3];
+    double qz;
+};
+
+__device__ inline void ring_geom(const OpDesc& o, const VolDev& v, int bx, int by, int bz, int lane, RingGeom& g)
+{
+    float q[3];
+    block_origin(o, v.s, bx, by, bz, q, g.qz);
+    const float kx = (float)(lane & 7), ky = (float)(lane >> 3);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) g.base[r] = (q[r] + kx * o.a[0][r]) + ky * o.a[1][r];
+}
+
+typedef __attribute__((address_space(1))) const unsigned char GlobalBytes;
+typedef __attribute__((address_space(1))) const float GlobalF32;
+typedef __attribute__((address_space(1))) const uint32_t GlobalU32;
+
+// Element `i` of a keyframe array through a 32-bit byte offset from a
+// uniform base (a global load with a scalar base and a vector offset).
+template <class T, class G>
+__device__ inline T kf_load(const void* base, uint32_t i)
+{
+    return *(G*)((GlobalBytes*)base + i * (uint32_t)sizeof(T));
+}
+
+// The lane's voxels in z-slices kz0 .. kz0 + 3 of one (block, operation)
+// after their gathers: the camera z (NaN for a voxel outside the image, so
+// that its band test fails), the pixel, and the keyframe sample there (pixel
+// 0 for a voxel outside the image).
+template <int CM>
+struct RingFetch {
+    float pz[4], wr[4], z[4];
+    uint32_t pix[4];
+    uint32_t c[4];  // RGBA8 colour at the pixel (RGBA8 mode)
+};
+
+// Projections of the lane's voxels in z-slices kz0 .. kz0 + 3 and their
+// keyframe gathers: one record per voxel from a packed keyframe, else depth,
+// weight and (RGBA8) colour.  The z steps k a_z are the descriptor's
+// host-rounded products, equal to the FP32 products of the convention.
+template <int CM, bool kPacked>
+__device__ inline void ring_fetch(const OpDesc& o, const RingGeom& g, int kz0, RingFetch<CM>& f)
+{
+    // the operation's constants, read together at the top
+    const ProjConst k = proj_const(o);
+    float za[4][3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 3; ++r) za[j][r] = o.za[kz0 + j][r];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float px = g.base[0] + za[j][0];
+        const float py = g.base[1] + za[j][1];
+        const float pz = g.base[2] + za[j][2];
+        bool in;
+        f.pix[j] = pixel_index_fast(k, px, py, pz, in);
+        f.pz[j] = in ? pz : __builtin_nanf("");
+    }
+    if (kPacked) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            // the record's first three words, adjacent: one 12-byte load
+            const uint32_t i = 4u * f.pix[j];
+            f.z[j] = __uint_as_float(kf_load<uint32_t, GlobalU32>(o.packed, i));
+            f.wr[j] = __uint_as_float(kf_load<uint32_t, GlobalU32>(o.packed, i + 1u));
+            f.c[j] = kf_load<uint32_t, GlobalU32>(o.packed, i + 2u);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            f.wr[j] = kf_load<float, GlobalF32>(o.weight, f.pix[j]);
+            f.z[j] = kf_load<float, GlobalF32>(o.depth, f.pix[j]);
+            f.c[j] = (CM == SC_COLOR_RGBA8) ? kf_load<uint32_t, GlobalU32>(o.color, f.pix[j]) : 0u;
+        }
+    }
+}
+
+// Touched decisions of fetched voxels; with kPacked the weight is already
+// quantised and the depth of a pixel without weight is -inf.
+template <int CM, bool kPacked>
+__device__ inline void ring_decide(const RingFetch<CM>& f, float mu, float w[4], bool t[4])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        w[j] = kPacked ? f.wr[j] : qweight(f.wr[j]);
+        t[j] = (kPacked || w[j] > 0.0f) && fabsf(f.z[j] - f.pz[j]) <= mu;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // voxel updates
 // ---------------------------------------------------------------------------
@@ -1157,9 +1250,11 @@ __device__ inline void cand_tile(const OpDesc& op, const VolDev& v, const CandDe
     // insert the tile's blocks: each wavefront first compacts the occupied
     // entries of its part of the set into its index list (about one in twenty
     // is occupied), then claims them 64 at a time, so it waits for about one
-    // claim latency rather than one per round holding an occupied entry; new
-    // candidates are appended with one atomic per wavefront (the claim loop's
-    // trip count is the same for every lane)
+    // claim latency rather than one per round holding an occupied entry.  With
+    // a list, each claimed entry is replaced by its bucket if it is a new
+    // candidate, and the tile appends them with one atomic (with one per
+    // wavefront and round, queued on the counter, a 640x480 keyframe's
+    // candidates took 15 us, so 11)
     const int lane = tid & 63;
     constexpr int kRounds = kSet / kThreads;
     uint16_t* wl = idx + (tid >> 6) * (kRounds * 64);
@@ -1173,6 +1268,7 @@ __device__ inline void cand_tile(const OpDesc& op, const VolDev& v, const CandDe
         n += __popcll(bal);
     }
     wave_lds_sync();
+    int n_fresh = 0;
     for (int r0 = 0; r0 < n; r0 += 64) {
         const int r = r0 + lane;
         bool fresh = false;
@@ -1183,13 +1279,28 @@ __device__ inline void cand_tile(const OpDesc& op, const VolDev& v, const CandDe
             unpack_key(key, bx, by, bz);
             gb = cand_claim(cd, v, key, bx, by, bz, fresh);
             if (gb >= 0 && op_bit >= 0) cand_mark(cd, gb, op_bit);
+            if (count) lds[wl[r]] = fresh ? (uint64_t)gb : kKeyEmpty;
         }
-        if (count) {
-            const uint64_t bal = __ballot(fresh);
-            if (bal) {
-                const uint32_t base = wave_fetch_add(count, (uint32_t)__popcll(bal), lane);
-                if (fresh) cand_append(cd, v, base + lanes_below(bal), gb);
-            }
+        n_fresh += __popcll(__ballot(fresh));
+    }
+    if (count) {
+        __shared__ uint32_t part[kThreads / 64], base;
+        if (lane == 0) part[tid >> 6] = (uint32_t)n_fresh;
+        __syncthreads();
+        if (tid == 0) {
+            uint32_t sum = 0u;
+            for (int w = 0; w < kThreads / 64; ++w) sum += part[w];
+            base = sum ? atomicAdd(count, sum) : 0u;
+        }
+        __syncthreads();
+        uint32_t to = base;
+        for (int w = 0; w < (tid >> 6); ++w) to += part[w];
+        for (int r0 = 0; r0 < n; r0 += 64) {
+            const int r = r0 + lane;
+            const uint64_t e = r < n ? lds[wl[r]] : kKeyEmpty;
+            const uint64_t bal = __ballot(e != kKeyEmpty);
+            if (e != kKeyEmpty) cand_append(cd, v, to + lanes_below(bal), (int)e);
+            to += (uint32_t)__popcll(bal);
         }
     }
 }

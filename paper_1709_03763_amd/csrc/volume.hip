@@ -185,89 +185,136 @@ __global__ __launch_bounds__(256) void cand_plain_kernel(OpDesc op, VolDev v, Ca
     __shared__ uint16_t idx[CandCfg<kTilePlain, kCellPlain>::lds_set];
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         cd.counters[1 - parity] = 0u;
-        cd.counters[2 + (1 - parity)] = 0u;
+        if (op.rec_mode == 1) *op.rec_count = 0u;  // the integration's record starts empty
     }
     cand_tile<kTilePlain, kCellPlain>(op, v, cd, cd.counters + parity, blockIdx.x, blockIdx.y, -1, lds, idx);
 }
 
-// Applies one operation to one candidate block with one wavefront, eight
-// voxels per lane (lane = x + 8 y, loop over z), coalesced in brick order.
-template <int CM>
-__device__ void block_one_op(const OpDesc& op, const VolDev& v, uint64_t key, int lane)
-{
-    int bx, by, bz;
-    unpack_key(key, bx, by, bz);
-    float q[3];
-    double qz;
-    block_origin(op, v.s, bx, by, bz, q, qz);
-    const float kx = (float)(lane & 7), ky = (float)(lane >> 3);
-    float base[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) base[r] = (q[r] + kx * op.a[0][r]) + ky * op.a[1][r];
-    const double bz64 = (qz + (double)(lane & 7) * op.az[0]) + (double)(lane >> 3) * op.az[1];
-    VoxHits<CM, 8> hv;
-    test_voxels<CM, 8>(op, v.mu, base, 0, hv);
-    const uint32_t tmask = hv.hit;
-    if (__ballot(tmask != 0) == 0) return;
-    if (op.rec_mode == 1 && lane == 0) {
-        // the integration's touched-block record: one append by one lane
-        const uint32_t pos = atomicAdd(op.rec_count, 1u);
-        if (pos < (uint32_t)op.rec_cap) op.rec_keys[pos] = key;
-    }
-    const int slot = (op.sign > 0) ? vol_insert_wave(v, key, bx, by, bz, lane) : (int)bcast((uint32_t)vol_find(v, key, bx, by, bz));
-    if (slot < 0) {
-        if (op.sign < 0) set_error(v.err, SC_ENOTALLOC);
-        return;
-    }
-    float* blk = v.pool + (size_t)slot * v.stride;
-    bool bad = false;
-#pragma unroll
-    for (int kz = 0; kz < 8; ++kz) {
-        if (!((tmask >> kz) & 1u)) continue;
-        const int i = lane + 64 * kz;
-        double* Dp = reinterpret_cast<double*>(blk);
-        double D = Dp[i];
-        float W = blk[kPoolW + i];
-        const double dd = distance(hv.z[kz], bz64 + (double)kz * op.az[2]);
-        if (CM == SC_COLOR_RGBA8) {
-            uint32_t* Cp = reinterpret_cast<uint32_t*>(blk + kPoolC);
-            uint32_t C = Cp[i];
-            bad |= !update_rgba8(D, W, C, dd, hv.w[kz], hv.c[kz], op.sign);
-            Cp[i] = C;
-        } else {
-            double* Cd = reinterpret_cast<double*>(blk + kPoolC);
-            double C[3] = {Cd[i], Cd[512 + i], Cd[1024 + i]};
-            const float* cp = reinterpret_cast<const float*>(op.color) + 3 * hv.pix[kz];
-            const float c[3] = {cp[0], cp[1], cp[2]};
-            bad |= !update_f32(D, W, C, dd, hv.w[kz], c, op.sign);
-            Cd[i] = C[0];
-            Cd[512 + i] = C[1];
-            Cd[1024 + i] = C[2];
-        }
-        Dp[i] = D;
-        blk[kPoolW + i] = W;
-    }
-    if (__ballot(bad) != 0) set_error(v.err, SC_EWEIGHT);
-}
+// Applies one operation to its candidate blocks, one wavefront a block, eight
+// voxels a lane (lane = x + 8 y, z in registers), and clears the blocks'
+// candidate entries.  Workgroup wavefronts take the list's entries in a fixed
+// stride: a keyframe proposes a few thousand blocks, about one a wavefront,
+// and a queue counter that every wavefront reads once more to find the list
+// empty is served one wavefront at a time.  For the same reason the blocks of
+// a touched-block record are kept per wavefront and appended with one atomic
+// per workgroup.
+// Bound: the latency of a block's chain of loads (list, key, then slot and
+// keyframe samples together, then the voxels four slices at a time: all eight
+// at once take 169 registers, or spill).  640x480 keyframe: 1 cm voxels, in an
+// online session, 79 -> 27 us; 5 mm voxels 86 -> 24 us.
+constexpr int kPlainRec = 16;  // recorded blocks a wavefront holds: 65,536 candidates with 1024 workgroups
 
-// Persistent: each wavefront pops candidate blocks until the list is
-// exhausted (no lane-dependent branches in the loop).
-template <int CM>
-__global__ __launch_bounds__(256) void update_plain_kernel(OpDesc op, VolDev v, CandDev cd, int parity)
+template <int CM, bool kPacked>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void update_plain_kernel(OpDesc op, VolDev v, CandDev cd, int parity)
 {
+    __shared__ uint64_t rec[4][kPlainRec];
+    __shared__ uint32_t rec_n[4];
+    __shared__ uint32_t rec_base;
     const int lane = threadIdx.x & 63;
+    const int wave = (int)bcast(threadIdx.x >> 6);
     const uint32_t n = min(cd.counters[parity], cd.cap);
-    WorkCursor cur;
-    cursor_init(cur, blockIdx.x * (blockDim.x >> 6) + bcast(threadIdx.x >> 6));
-    const uint32_t n_workers = gridDim.x * (blockDim.x >> 6);
-    for (;;) {
-        const uint32_t i = cursor_pop(cur, cd.counters + 2 + parity, n_workers, lane);
-        if (i >= n) break;
+    const uint32_t n_workers = gridDim.x * 4u;
+    uint32_t held = 0u;  // recorded blocks not yet appended
+    bool bad = false;
+    for (uint32_t i = blockIdx.x * 4u + (uint32_t)wave; i < n; i += n_workers) {
         const uint32_t h = bcast(cd.list[i]);
         const uint64_t key = bcast64(cd.keys[h]);
-        block_one_op<CM>(op, v, key, lane);
+        int bx, by, bz;
+        unpack_key(key, bx, by, bz);
+        RingGeom g;
+        ring_geom(op, v, bx, by, bz, lane, g);
+        RingFetch<CM> f[2];
+        ring_fetch<CM, kPacked>(op, g, 0, f[0]);
+        ring_fetch<CM, kPacked>(op, g, 4, f[1]);
+        int slot = (int)bcast((uint32_t)vol_find(v, key, bx, by, bz));
+        float w[8];
+        bool t[8];
+        ring_decide<CM, kPacked>(f[0], v.mu, w, t);
+        ring_decide<CM, kPacked>(f[1], v.mu, w + 4, t + 4);
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) any = any || t[j];
         cd.keys[h] = kKeyEmpty;
+        if (__ballot(any) == 0ull) continue;
+        if (op.rec_mode == 1) {
+            if (held < (uint32_t)kPlainRec) rec[wave][held] = key;  // every lane, the same value
+            ++held;
+        }
+        if (slot < 0 && op.sign > 0) slot = vol_insert_wave(v, key, bx, by, bz, lane);
+        if (slot < 0) {
+            if (op.sign < 0) set_error(v.err, SC_ENOTALLOC);
+            continue;
+        }
+        float* blk = v.pool + (size_t)slot * v.stride;
+        double* Dp = reinterpret_cast<double*>(blk);
+        float* Wp = blk + kPoolW;
+        const double bz64 = (g.qz + (double)(lane & 7) * op.az[0]) + (double)(lane >> 3) * op.az[1];
+        if (CM == SC_COLOR_RGBA8) {
+            uint32_t* Cp = reinterpret_cast<uint32_t*>(blk + kPoolC);
+#pragma unroll
+            for (int p = 0; p < 8; p += 4) {
+                double D[4];
+                float W[4];
+                uint32_t C[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    // a lane without a touched voxel reads the block's first: no branch between the loads
+                    const int x = t[p + q] ? lane + 64 * (p + q) : 0;
+                    D[q] = Dp[x];
+                    W[q] = Wp[x];
+                    C[q] = Cp[x];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (!t[p + q]) continue;
+                    const int x = lane + 64 * (p + q);
+                    bad |= !update_rgba8_fast(D[q], W[q], C[q],
+                                              distance(f[p / 4].z[q], bz64 + (double)(p + q) * op.az[2]), w[p + q],
+                                              f[p / 4].c[q], op.sign);
+                    Dp[x] = D[q];
+                    Wp[x] = W[q];
+                    Cp[x] = C[q];
+                }
+            }
+        } else {
+            double* Cd = reinterpret_cast<double*>(blk + kPoolC);
+            const float* col = reinterpret_cast<const float*>(op.color);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (!t[j]) continue;
+                const int x = lane + 64 * j;
+                const RingFetch<CM>& fj = f[j >> 2];
+                const float* cp = col + 3 * (size_t)fj.pix[j & 3];
+                double C[3] = {Cd[x], Cd[512 + x], Cd[1024 + x]};
+                const float c[3] = {cp[0], cp[1], cp[2]};
+                double D = Dp[x];
+                float W = Wp[x];
+                bad |= !update_f32(D, W, C, distance(fj.z[j & 3], bz64 + (double)j * op.az[2]), w[j], c, op.sign);
+                Dp[x] = D;
+                Wp[x] = W;
+                Cd[x] = C[0];
+                Cd[512 + x] = C[1];
+                Cd[1024 + x] = C[2];
+            }
+        }
     }
+    if (__ballot(bad) != 0) set_error(v.err, SC_EWEIGHT);
+    if (op.rec_mode != 1) return;
+    if (lane == 0) rec_n[wave] = held;
+    __syncthreads();
+    uint32_t sum = 0u, most = 0u, before = 0u;
+    for (int q = 0; q < 4; ++q) {
+        before += q < wave ? rec_n[q] : 0u;
+        sum += rec_n[q];
+        most = max(most, rec_n[q]);
+    }
+    if (sum == 0u) return;
+    // more than a wavefront holds: the record counts as overflowed and is not used
+    const bool over = most > (uint32_t)kPlainRec;
+    if (threadIdx.x == 0) rec_base = atomicAdd(op.rec_count, over ? (uint32_t)op.rec_cap + 1u : sum);
+    __syncthreads();
+    const uint32_t pos = rec_base + before + (uint32_t)lane;
+    if (!over && (uint32_t)lane < held && pos < (uint32_t)op.rec_cap) op.rec_keys[pos] = rec[wave][lane];
 }
 
 // Writes imported block records into their pool slots (D widened to FP64;
@@ -590,7 +637,6 @@ sc_status plain_op(sc_volume* vol, const sc_keyframe* kf, const sc_intrinsics* i
     make_op(vol, kf, in, T, sign, 0, &op);
     if (sign > 0) {
         rec_for_integration(vol, kf, in, T, true, &op);
-        if (op.rec_mode == 1) fill_u32(op.rec_count, 0u, 1, s);
     } else {
         // the plain de-integration generates its own candidates: only the
         // reference is released
@@ -608,11 +654,13 @@ sc_status plain_op(sc_volume* vol, const sc_keyframe* kf, const sc_intrinsics* i
         rec_commit(vol);
         return sst;
     }
-    const int grid = vol->n_cu * vol->plain_wgs;  // resident at once: the first items are assigned statically
-    if (vol->p.color_mode == SC_COLOR_RGBA8)
-        update_plain_kernel<SC_COLOR_RGBA8><<<grid, 256, 0, s>>>(op, vol->dev, vol->cand, p);
+    const int grid = vol->n_cu * vol->plain_wgs;  // resident at once
+    if (vol->p.color_mode == SC_COLOR_F32)
+        update_plain_kernel<SC_COLOR_F32, false><<<grid, 256, 0, s>>>(op, vol->dev, vol->cand, p);
+    else if (op.packed)
+        update_plain_kernel<SC_COLOR_RGBA8, true><<<grid, 256, 0, s>>>(op, vol->dev, vol->cand, p);
     else
-        update_plain_kernel<SC_COLOR_F32><<<grid, 256, 0, s>>>(op, vol->dev, vol->cand, p);
+        update_plain_kernel<SC_COLOR_RGBA8, false><<<grid, 256, 0, s>>>(op, vol->dev, vol->cand, p);
     rec_commit(vol);
     if (hipGetLastError() != hipSuccess) return SC_EDEVICE;
     vol->cand_dirty = dirty;  // the pass leaves the candidate table as it found it
@@ -672,11 +720,9 @@ sc_status sc_volume_create(const sc_volume_params* p, sc_volume** out)
     vol->cand_wgs[1] = cand_batch_resident_wgs(true);
     {
         int n = 0;
-        const hipError_t e = (p->color_mode == SC_COLOR_RGBA8)
-                                 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, update_plain_kernel<SC_COLOR_RGBA8>,
-                                                                               256, 0)
-                                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, update_plain_kernel<SC_COLOR_F32>,
-                                                                               256, 0);
+        const void* k = p->color_mode == SC_COLOR_F32 ? (const void*)update_plain_kernel<SC_COLOR_F32, false>
+                                                      : (const void*)update_plain_kernel<SC_COLOR_RGBA8, false>;
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, 256, 0);
         vol->plain_wgs = (e == hipSuccess) ? std::max(1, std::min(n, 4)) : 1;
     }
     // default voxel-pass schedule: RGBA8 volumes take the ring pass (two
