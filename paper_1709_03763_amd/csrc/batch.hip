@@ -45,23 +45,28 @@ __device__ inline void batch_init(const OpDesc* __restrict__ ops, const BatchHdr
     if (threadIdx.x < 2) cd.cursors[threadIdx.x * kCursorSet + kCursorDone] = 0u;
     if (threadIdx.x == 0) cd.big[0] = 0u;
     for (int i = threadIdx.x; i < n_bins; i += blockDim.x) cd.bins[i] = 0u;
-    for (int o = threadIdx.x; o < hdr->n_ops; o += blockDim.x)
-        if (ops[o].rec_mode == 1) *ops[o].rec_count = 0u;
+    for (int i = threadIdx.x; i < hdr->n_ops * kRecShards; i += blockDim.x) {
+        const OpDesc& op = ops[i / kRecShards];
+        if (op.rec_mode == 1) op.rec_count[(i % kRecShards) * kRecCountStride] = 0u;
+    }
 }
 
 // A de-integration whose touched-block record is complete takes its
 // candidates from the record instead of from frustum cells.
 __device__ inline bool uses_record(const OpDesc& op)
 {
-    return op.rec_mode == 2 && *op.rec_count <= (uint32_t)op.rec_cap;
+    if (op.rec_mode != 2) return false;
+    // one part a lane, read together (every lane of the wavefront is active)
+    const uint32_t c = op.rec_count[((int)threadIdx.x % kRecShards) * kRecCountStride];
+    return __ballot(c > (uint32_t)op.rec_cap) == 0ull;
 }
 
 // Candidate blocks of de-integrations from their records: every recorded
 // block is claimed in the candidate table and marked with the operation's
 // bit.  Workgroup (x, y) takes operations y, y + gridDim.y, ... and, of each,
-// the keys x * 256 + threadIdx.x + k * gridDim.x * 256.  A record that
-// overflowed its capacity is not used: the operation's frustum-cell tiles
-// are generated here instead, tile x, x + gridDim.x, ...
+// part x of the record.  A record with a part that overflowed its capacity is
+// not used: the operation's frustum-cell tiles are generated here instead,
+// tile x, x + gridDim.x, ...
 __global__ __launch_bounds__(256) void cand_record_kernel(const OpDesc* __restrict__ ops, const BatchHdr* hdr,
                                                           VolDev v, CandDev cd, int n_bins)
 {
@@ -82,9 +87,9 @@ __global__ __launch_bounds__(256) void cand_record_kernel(const OpDesc* __restri
             }
             continue;
         }
-        const uint32_t n = *op.rec_count;
-        for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-            const uint64_t key = op.rec_keys[i];
+        const uint32_t n = op.rec_count[blockIdx.x * kRecCountStride];
+        for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+            const uint64_t key = op.rec_keys[(size_t)blockIdx.x * op.rec_cap + i];
             int bx, by, bz;
             unpack_key(key, bx, by, bz);
             bool fresh;
@@ -137,11 +142,7 @@ __global__ __launch_bounds__(256) void cand_batch_kernel(const OpDesc* __restric
         if (it >= items) {
             __syncthreads();
             if (threadIdx.x == 0) {
-                const uint32_t m = atomicOr(cd.cursors + kCursorDone, 1u << r) | (1u << r);
-                int nr = -1;
-                for (int j = 1; j < kCursors && nr < 0; ++j)
-                    if (!((m >> ((r + j) % kCursors)) & 1u)) nr = (r + j) % kCursors;
-                next = nr;
+                next = next_range(cd.cursors, r);
             }
             __syncthreads();
             if (next < 0) break;
@@ -722,18 +723,21 @@ struct PipeBlock {
     uint32_t touched, n_upd, pairs;
     bool re_touch, e_na, e_w;
     bool pair_any;   // the current operation touched a voxel of the block (ring pass)
+    uint32_t shard;  // part of the records that this wavefront appends to
     uint32_t n_rec;  // recording integrations that touched the block, not yet appended
     int rec_op;      // lane i < n_rec: the i-th of them
 };
 
 // Appends the block to the records of the integrations listed in lanes
-// 0 .. n_rec - 1, one atomic per lane on that operation's counter.
+// 0 .. n_rec - 1, in the part `shard`, one atomic per lane on that
+// operation's counter.
 __device__ inline void record_flush(const OpDesc* __restrict__ ops, PipeBlock& pb, int lane)
 {
     if ((uint32_t)lane < pb.n_rec) {
         const OpDesc& o = ops[pb.rec_op];
-        const uint32_t pos = atomicAdd(o.rec_count, 1u);
-        if (pos < (uint32_t)o.rec_cap) o.rec_keys[pos] = pack_key(pb.bx, pb.by, pb.bz);
+        const uint32_t pos = atomicAdd(o.rec_count + pb.shard * kRecCountStride, 1u);
+        if (pos < (uint32_t)o.rec_cap)
+            o.rec_keys[(size_t)pb.shard * o.rec_cap + pos] = pack_key(pb.bx, pb.by, pb.bz);
     }
     pb.n_rec = 0u;
 }
@@ -1122,7 +1126,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void b
     const uint32_t worker = blockIdx.x * (blockDim.x >> 6) + (uint32_t)wave;
     const uint32_t n_workers = gridDim.x * (blockDim.x >> 6);
     RangeCursor cur;
-    range_init(cur, worker);
+    range_init(cur, worker, n, n_workers);
     uint32_t* const cursors = cd.cursors + kCursorSet;  // the voxel pass's set
     uint32_t n_upd = 0, n_pairs = 0, n_written = 0;
     for (;;) {
@@ -1136,6 +1140,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void b
         pb.touched = pb.n_upd = pb.pairs = 0u;
         pb.re_touch = pb.e_na = pb.e_w = false;
         pb.n_rec = 0u;
+        pb.shard = worker % kRecShards;
         pb.rec_op = 0;
         // the operation mask first, then the block state into registers;
         // the first operation's gathers are issued before the state goes to
@@ -1323,8 +1328,8 @@ static void launch_candidates(sc_volume* vol, bool from_cells, hipStream_t s)
     const int n_bins = vol->p.max_batch_ops + 1;
     // first the recorded candidates (their kernel also clears the batch's
     // counters), then the frustum tiles
-    // 16 workgroups per operation: about one recorded key per thread
-    cand_record_kernel<<<dim3(16, (unsigned)std::min(vol->p.max_batch_ops, 256)), 256, 0, s>>>(
+    // a workgroup per part of a record
+    cand_record_kernel<<<dim3(kRecShards, (unsigned)std::min(vol->p.max_batch_ops, 256)), 256, 0, s>>>(
         vol->d_ops, vol->d_hdr, vol->dev, vol->cand, n_bins);
     const int threads = CandCfg<kTileBatch, kCellBatch>::threads;
     if (from_cells) {
@@ -1624,13 +1629,14 @@ sc_status sc_volume_stats(sc_volume* vol, void* stream, int64_t* stats)
 {
     if (!vol || !stats) return SC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    int64_t slots[4 * kStatSlots];
+    static_assert(4 * kStatSlots * kStatStride * sizeof(int64_t) <= 16384, "the slots fit the stack");
+    int64_t slots[4 * kStatSlots * kStatStride];
     if (hipMemcpyAsync(slots, vol->cand.stats, sizeof(slots), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return SC_EDEVICE;
     for (int k = 0; k < 4; ++k) {
         stats[k] = 0;
-        for (int j = 0; j < kStatSlots; ++j) stats[k] += slots[k * kStatSlots + j];
+        for (int j = 0; j < kStatSlots; ++j) stats[k] += slots[(k * kStatSlots + j) * kStatStride];
     }
     return SC_OK;
 }

@@ -77,10 +77,14 @@ struct OpDesc {
     // rec_mode 2 takes those blocks as its candidates (the same keyframe at
     // the same pose touches the same blocks) when the record did not
     // overflow; rec_mode 0: no record.
-    uint64_t* rec_keys;   // rec_cap keys
-    uint32_t* rec_count;  // appended so far (may exceed rec_cap: overflowed)
+    // In kRecShards parts, so that the appends of a pass spread over as many
+    // counters: part p holds up to rec_cap keys from rec_keys + p rec_cap.
+    uint64_t* rec_keys;
+    uint32_t* rec_count;  // appended to part p so far, at p kRecCountStride (may exceed rec_cap: overflowed)
     int32_t rec_cap;
 };
+constexpr int kRecShards = 16;
+constexpr int kRecCountStride = 32;  // one counter per 128 bytes
 static_assert(offsetof(OpDesc, za) == 64, "projection constants of OpDesc: za at byte 64");
 
 // Device view of a volume.

@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256) void reset_kernel(VolDev v, CandDev c, double*
     fill_words(c.bins, sizeof(uint32_t) * (kMaxBatchOps + 2), 0u);
     fill_words(c.cursors, sizeof(uint32_t) * 2 * kCursorSet, 0u);
     fill_words(c.big, sizeof(uint32_t), 0u);
-    fill_words(c.stats, sizeof(unsigned long long) * 4 * kStatSlots, 0u);
+    fill_words(c.stats, sizeof(unsigned long long) * 4 * kStatSlots * kStatStride, 0u);
     fill_words(adj_acc, sizeof(double) * 3 * kAdjChunk, 0u);
 }
 static_assert(kKeyEmpty == ~0ull, "reset_kernel stores the empty key as two words of ones");
@@ -185,8 +185,10 @@ __global__ __launch_bounds__(256) void cand_plain_kernel(OpDesc op, VolDev v, Ca
     __shared__ uint16_t idx[CandCfg<kTilePlain, kCellPlain>::lds_set];
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         cd.counters[1 - parity] = 0u;
-        if (op.rec_mode == 1) *op.rec_count = 0u;  // the integration's record starts empty
     }
+    // the integration's record starts empty
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kRecShards && op.rec_mode == 1)
+        op.rec_count[threadIdx.x * kRecCountStride] = 0u;
     cand_tile<kTilePlain, kCellPlain>(op, v, cd, cd.counters + parity, blockIdx.x, blockIdx.y, -1, lds, idx);
 }
 
@@ -311,10 +313,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void u
     if (sum == 0u) return;
     // more than a wavefront holds: the record counts as overflowed and is not used
     const bool over = most > (uint32_t)kPlainRec;
-    if (threadIdx.x == 0) rec_base = atomicAdd(op.rec_count, over ? (uint32_t)op.rec_cap + 1u : sum);
+    const uint32_t shard = blockIdx.x % kRecShards;
+    if (threadIdx.x == 0)
+        rec_base = atomicAdd(op.rec_count + shard * kRecCountStride, over ? (uint32_t)op.rec_cap + 1u : sum);
     __syncthreads();
     const uint32_t pos = rec_base + before + (uint32_t)lane;
-    if (!over && (uint32_t)lane < held && pos < (uint32_t)op.rec_cap) op.rec_keys[pos] = rec[wave][lane];
+    if (!over && (uint32_t)lane < held && pos < (uint32_t)op.rec_cap)
+        op.rec_keys[(size_t)shard * op.rec_cap + pos] = rec[wave][lane];
 }
 
 // Writes imported block records into their pool slots (D widened to FP64;
@@ -509,8 +514,7 @@ struct RecordRegistry {
 namespace sc {
 
 constexpr int kRecSlots = 1024;   // records held at once
-constexpr int kRecCap = 16384;    // blocks per record
-constexpr int kRecCountStride = 32;  // one record counter per 128 bytes, so appends to different records do not meet
+constexpr int kRecCap = 1024;     // blocks per part of a record, of kRecShards
 
 static std::string rec_fingerprint(const sc_keyframe* kf, const sc_intrinsics* in, const sc_pose* T)
 {
@@ -530,8 +534,8 @@ static bool rec_ready(sc_volume* vol)
     if (!r || r->failed) return false;
     if (r->d_keys) return true;
     const int cap = (int)std::min<int64_t>(kRecCap, vol->p.max_blocks);
-    if (hipMalloc(&r->d_keys, sizeof(uint64_t) * (size_t)kRecSlots * cap) != hipSuccess ||
-        hipMalloc(&r->d_count, kRecCountStride * sizeof(uint32_t) * kRecSlots) != hipSuccess) {
+    if (hipMalloc(&r->d_keys, sizeof(uint64_t) * (size_t)kRecSlots * kRecShards * cap) != hipSuccess ||
+        hipMalloc(&r->d_count, sizeof(uint32_t) * (size_t)kRecSlots * kRecShards * kRecCountStride) != hipSuccess) {
         (void)hipGetLastError();
         hipFree(r->d_keys);
         r->d_keys = nullptr;
@@ -592,8 +596,8 @@ void rec_for_integration(sc_volume* vol, const sc_keyframe* kf, const sc_intrins
     const int slot = r->free_slots.back();
     r->free_slots.pop_back();
     r->map.emplace(f, RecordRegistry::Entry{slot, 1});
-    op->rec_keys = r->d_keys + (size_t)slot * r->cap;
-    op->rec_count = r->d_count + (size_t)kRecCountStride * slot;
+    op->rec_keys = r->d_keys + (size_t)slot * kRecShards * r->cap;
+    op->rec_count = r->d_count + (size_t)slot * kRecShards * kRecCountStride;
     op->rec_cap = r->cap;
     op->rec_mode = 1;
 }
@@ -609,8 +613,8 @@ void rec_for_deintegration(sc_volume* vol, const sc_keyframe* kf, const sc_intri
     auto it = r->map.find(rec_fingerprint(kf, in, T));
     if (it == r->map.end()) return;
     const int slot = it->second.slot;
-    op->rec_keys = r->d_keys + (size_t)slot * r->cap;
-    op->rec_count = r->d_count + (size_t)kRecCountStride * slot;
+    op->rec_keys = r->d_keys + (size_t)slot * kRecShards * r->cap;
+    op->rec_count = r->d_count + (size_t)slot * kRecShards * kRecCountStride;
     op->rec_cap = r->cap;
     op->rec_mode = 2;
     if (--it->second.refs == 0) {
@@ -770,7 +774,7 @@ sc_status sc_volume_create(const sc_volume_params* p, sc_volume** out)
     ok &= hipMalloc(&c.bins, sizeof(uint32_t) * (kMaxBatchOps + 2)) == hipSuccess;
     ok &= hipMalloc(&c.cursors, sizeof(uint32_t) * 2 * kCursorSet) == hipSuccess;
     ok &= hipMalloc(&c.big, sizeof(uint32_t) * (kBigCap + 1)) == hipSuccess;
-    ok &= hipMalloc(&c.stats, sizeof(unsigned long long) * 4 * kStatSlots) == hipSuccess;
+    ok &= hipMalloc(&c.stats, sizeof(unsigned long long) * 4 * kStatSlots * kStatStride) == hipSuccess;
     ok &= hipMalloc(&vol->d_ops, sizeof(OpDesc) * p->max_batch_ops) == hipSuccess;
     ok &= hipMalloc(&vol->adj_acc, sizeof(double) * 3 * kAdjChunk) == hipSuccess;
     ok &= hipHostMalloc((void**)&vol->h_ops, 2 * sizeof(OpDesc) * p->max_batch_ops, hipHostMallocDefault) ==
