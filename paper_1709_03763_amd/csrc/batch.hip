@@ -7,9 +7,10 @@
 //   1. reset counters and the histogram
 //   2. candidate blocks of every operation (per-pixel frustum cells,
 //      deduplicated per tile in LDS, then in a global table whose per-block
-//      bit mask records which operations proposed the block)
-//   3. histogram of operations per candidate block, descending scan, scatter:
-//      the work queue holds the busiest blocks first
+//      bit mask records which operations proposed the block; blocks new to the
+//      table are listed)
+//   3. histogram of operations per candidate block, scatter in descending
+//      order: the work queue holds the busiest blocks first
 //   4. persistent voxel pass: each worker pops a block, loads its voxels once,
 //      applies the proposing operations in processing order in registers
 //      (the touched test decides per voxel), allocates the block if a
@@ -44,7 +45,7 @@ __device__ inline void batch_init(const OpDesc* __restrict__ ops, const BatchHdr
     for (int i = threadIdx.x; i < 2 * kCursors; i += blockDim.x) cd.cursors[i * kCursorStride] = 0u;
     if (threadIdx.x < 2) cd.cursors[threadIdx.x * kCursorSet + kCursorDone] = 0u;
     if (threadIdx.x == 0) cd.big[0] = 0u;
-    for (int i = threadIdx.x; i < n_bins; i += blockDim.x) cd.bins[i] = 0u;
+    for (int i = threadIdx.x; i < 2 * n_bins; i += blockDim.x) cd.bins[i] = 0u;
     for (int i = threadIdx.x; i < hdr->n_ops * kRecShards; i += blockDim.x) {
         const OpDesc& op = ops[i / kRecShards];
         if (op.rec_mode == 1) op.rec_count[(i % kRecShards) * kRecCountStride] = 0u;
@@ -70,19 +71,24 @@ __device__ inline bool uses_record(const OpDesc& op)
 __global__ __launch_bounds__(256) void cand_record_kernel(const OpDesc* __restrict__ ops, const BatchHdr* hdr,
                                                           VolDev v, CandDev cd, int n_bins)
 {
-    if (blockIdx.x == 0 && blockIdx.y == 0) batch_init(ops, hdr, cd, n_bins);
     __shared__ uint64_t lds[CandCfg<kTileBatch, kCellBatch>::lds_set];
     __shared__ uint16_t idx[CandCfg<kTileBatch, kCellBatch>::lds_set];
+    __shared__ uint32_t fresh[kFresh], n_fresh, base;
+    if (blockIdx.x == 0 && blockIdx.y == 0) batch_init(ops, hdr, cd, n_bins);
     const int n_ops = hdr->n_ops;
-    const int tiles = hdr->tiles_x * hdr->tiles_y;
+    const FreshList fl{fresh, &n_fresh, (int)((blockIdx.y * gridDim.x + blockIdx.x) % kSegs)};
+    if (threadIdx.x == 0) n_fresh = 0u;
+    __syncthreads();
     for (int o = blockIdx.y; o < n_ops; o += gridDim.y) {
         const OpDesc& op = ops[o];
         if (op.rec_mode != 2) continue;
         if (!uses_record(op)) {
+            const int tiles_x = (op.width + kTileBatch - 1) / kTileBatch;
+            const int tiles = tiles_x * ((op.height + kTileBatch - 1) / kTileBatch);
             for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-                const int ty = tile / hdr->tiles_x;
-                const int tx = tile - ty * hdr->tiles_x;
-                cand_tile<kTileBatch, kCellBatch>(op, v, cd, nullptr, tx, ty, o, lds, idx);
+                const int ty = tile / tiles_x;
+                const int tx = tile - ty * tiles_x;
+                cand_tile<kTileBatch, kCellBatch>(op, v, cd, nullptr, tx, ty, o, lds, idx, fl.seg);
                 __syncthreads();
             }
             continue;
@@ -92,15 +98,23 @@ __global__ __launch_bounds__(256) void cand_record_kernel(const OpDesc* __restri
             const uint64_t key = op.rec_keys[(size_t)blockIdx.x * op.rec_cap + i];
             int bx, by, bz;
             unpack_key(key, bx, by, bz);
-            bool fresh;
-            const int gb = cand_claim(cd, v, key, bx, by, bz, fresh);
+            bool fr;
+            const int gb = cand_claim(cd, v, key, bx, by, bz, fr);
             if (gb >= 0) cand_mark(cd, gb, o);
+            if (fr) fresh_put(cd, fl, (uint32_t)gb);
         }
+        fresh_flush(cd, fl, &base);
     }
 }
 
+// The candidate lists, cleared before the kernels that append to them.
+__global__ void seg_clear_kernel(CandDev cd)
+{
+    if (threadIdx.x <= kSegs) cd.seg_n[threadIdx.x * kRecCountStride] = 0u;
+}
+
 // Frustum-cell candidates of the operations without a record, one (operation,
-// 64 x 64 tile) item at a time.  Tiles differ widely in cost (grazing
+// TILE x TILE tile) item at a time.  Tiles differ widely in cost (grazing
 // surfaces give large cell boxes), so items are handed out dynamically: item
 // i belongs to range i mod kCursors, workgroup b takes item b first (no
 // atomic), then kCandPop items at a time from its range's cursor; a
@@ -111,14 +125,23 @@ __global__ __launch_bounds__(256) void cand_record_kernel(const OpDesc* __restri
 // kFromCells: every operation's keyframe is packed (its cell depth ranges
 // stand in for the pixels).
 constexpr int kCandPop = 2;
-template <bool kFromCells>
-__global__ __launch_bounds__(256) void cand_batch_kernel(const OpDesc* __restrict__ ops, const BatchHdr* hdr,
-                                                         VolDev v, CandDev cd)
+// Tiles of 64 pixels, or of 32 pixels and one wavefront each for unpacked
+// keyframes whose 64-pixel tiles span many blocks (run_candidates): the same
+// cells, so the same candidates.
+template <int TILE, int CELL, bool kFromCells>
+__global__ __launch_bounds__((CandCfg<TILE, CELL>::threads)) void cand_batch_kernel(const OpDesc* __restrict__ ops,
+                                                                                    const BatchHdr* hdr, VolDev v,
+                                                                                    CandDev cd)
 {
-    __shared__ uint64_t lds[CandCfg<kTileBatch, kCellBatch>::lds_set];
-    __shared__ uint16_t idx[CandCfg<kTileBatch, kCellBatch>::lds_set];
+    constexpr int kSet = kFromCells ? kTileBits / 64 : CandCfg<TILE, CELL>::lds_set;
+    __shared__ uint64_t lds[kSet];
+    __shared__ uint16_t idx[kFromCells ? CandCfg<TILE, CELL>::threads * 8 : CandCfg<TILE, CELL>::lds_set];
     __shared__ float red[8];
     __shared__ int next;
+    __shared__ uint32_t fresh[kFromCells ? kFresh : 1], n_fresh, base;
+    const FreshList fl{fresh, &n_fresh, (int)blockIdx.x % kSegs};
+    if (threadIdx.x == 0) n_fresh = 0u;
+    __syncthreads();
     const int tiles = hdr->tiles_x * hdr->tiles_y;
     const int items = hdr->n_tile_ops * tiles;
     int r = (int)blockIdx.x % kCursors;
@@ -158,15 +181,16 @@ __global__ __launch_bounds__(256) void cand_batch_kernel(const OpDesc* __restric
         if (kFromCells) {
             // packed keyframes: the tile's bit map; a tile whose box is too
             // large is listed for cand_big_kernel (the hash set)
-            if (!cand_tile_bits<kTileBatch>(ops[o], v, cd, tx, ty, o, reinterpret_cast<uint32_t*>(lds), idx, red) &&
+            if (!cand_tile_bits<TILE>(ops[o], v, cd, tx, ty, o, reinterpret_cast<uint32_t*>(lds), idx, red, fl) &&
                 threadIdx.x == 0) {
                 const uint32_t pos = atomicAdd(cd.big, 1u);
                 if (pos < (uint32_t)kBigCap) cd.big[1 + pos] = (uint32_t)it;
             }
+            fresh_flush(cd, fl, &base);
         } else {
-            cand_tile<kTileBatch, kCellBatch, false>(ops[o], v, cd, nullptr, tx, ty, o, lds, idx);
+            cand_tile<TILE, CELL, false>(ops[o], v, cd, nullptr, tx, ty, o, lds, idx, fl.seg);
+            __syncthreads();
         }
-        __syncthreads();
         ++k;
     }
 }
@@ -191,7 +215,7 @@ __global__ __launch_bounds__(256) void cand_big_kernel(const OpDesc* __restrict_
         const int tile = it - kk * tiles;
         const int ty = tile / hdr->tiles_x;
         const int tx = tile - ty * hdr->tiles_x;
-        cand_tile<kTileBatch, kCellBatch, true>(ops[o], v, cd, nullptr, tx, ty, o, lds, idx);
+        cand_tile<kTileBatch, kCellBatch, true>(ops[o], v, cd, nullptr, tx, ty, o, lds, idx, (int)blockIdx.x % kSegs);
         __syncthreads();
     }
 }
@@ -199,16 +223,16 @@ __global__ __launch_bounds__(256) void cand_big_kernel(const OpDesc* __restrict_
 // Workgroups of cand_batch_kernel that fit on one CU at once (registers and
 // LDS); the kernel strides over its items statically, so a grid larger than
 // this runs its surplus as a second, mostly idle wave of workgroups.
-int cand_batch_resident_wgs(bool from_cells)
+int cand_batch_resident_wgs(int variant)
 {
+    const void* const k[3] = {(const void*)cand_batch_kernel<kTileBatch, kCellBatch, false>,
+                              (const void*)cand_batch_kernel<kTileBatch, kCellBatch, true>,
+                              (const void*)cand_batch_kernel<kTilePlain, kCellBatch, false>};
+    const int threads[3] = {CandCfg<kTileBatch, kCellBatch>::threads, CandCfg<kTileBatch, kCellBatch>::threads,
+                            CandCfg<kTilePlain, kCellBatch>::threads};
     int n = 0;
-    const hipError_t e =
-        from_cells ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, cand_batch_kernel<true>,
-                                                                  CandCfg<kTileBatch, kCellBatch>::threads, 0)
-                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, cand_batch_kernel<false>,
-                                                                  CandCfg<kTileBatch, kCellBatch>::threads, 0);
-    if (e != hipSuccess) n = 0;
-    return std::max(1, std::min(n, 8));
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k[variant], threads[variant], 0) != hipSuccess) n = 0;
+    return std::max(1, std::min(n, variant == 2 ? 16 : 8));
 }
 
 __device__ inline int mask_count(const CandDev& cd, uint32_t h)
@@ -218,137 +242,123 @@ __device__ inline int mask_count(const CandDev& cd, uint32_t h)
     return c;
 }
 
-// Occupied buckets of one wavefront's stretch [base, base + kCollect) of the
-// candidate table (clipped at b1), compacted into the wavefront's LDS list in
-// bucket order; returns their number.  All key loads issue together, so the
-// scans below wait for one load latency per stretch instead of one per
-// bucket a lane visits.  Every lane of the wavefront takes part.
-constexpr int kCollectPerLane = 8;
-constexpr int kCollect = 64 * kCollectPerLane;
+// Chunk of the candidate lists that workgroup w of the histogram and the
+// scatter takes: kChunk entries of list w % (kSegs + 1), then every
+// kChunkRow-th chunk of it.
+constexpr int kChunkPer = 4;                 // entries per thread
+constexpr uint32_t kChunk = 256 * kChunkPer;
+constexpr uint32_t kChunkRow = 16;
 
-__device__ inline int wave_collect(const CandDev& cd, uint32_t base, uint32_t b1, uint32_t* list, int lane)
-{
-    uint64_t key[kCollectPerLane];
-#pragma unroll
-    for (int k = 0; k < kCollectPerLane; ++k) {
-        const uint32_t i = base + 64u * k + (uint32_t)lane;
-        key[k] = i < b1 ? cd.keys[i] : kKeyEmpty;
-    }
-    int n = 0;
-#pragma unroll
-    for (int k = 0; k < kCollectPerLane; ++k) {
-        const bool occ = key[k] != kKeyEmpty;
-        const uint64_t bal = __ballot(occ);
-        if (occ) list[n + (int)lanes_below(bal)] = base + 64u * k + (uint32_t)lane;
-        n += __popcll(bal);
-    }
-    wave_lds_sync();
-    return n;
-}
-
-// Each workgroup takes a contiguous share of the candidate table's buckets,
-// so the histogram and the scatter below see the same buckets per workgroup.
-__device__ inline void wg_share(uint32_t n, uint32_t& b0, uint32_t& b1)
-{
-    const uint32_t per = (n + gridDim.x - 1) / gridDim.x;
-    b0 = min(n, blockIdx.x * per);
-    b1 = min(n, b0 + per);
-}
-
-// Histogram of operation counts over the occupied buckets, privatised in LDS
-// per workgroup.
+// Histogram of operation counts over the candidates, privatised in LDS per
+// workgroup.
 __global__ __launch_bounds__(256) void hist_kernel(CandDev cd, int n_bins)
 {
     __shared__ uint32_t h[kMaxBatchOps + 1];
-    __shared__ uint32_t lst[4][kCollect];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t b0, b1;
-    wg_share(cd.mask_bits + 1u, b0, b1);
+    const uint32_t s = blockIdx.x % (kSegs + 1);
+    const uint32_t n = min(cd.seg_n[s * kRecCountStride], s == kSegs ? ~0u : cd.seg_cap);
+    uint32_t c0 = blockIdx.x / (kSegs + 1) * kChunk;
+    if (c0 >= n) return;
     for (int c = threadIdx.x; c < n_bins; c += blockDim.x) h[c] = 0u;
     __syncthreads();
-    for (uint32_t base = b0 + wave * kCollect; base < b1; base += 4 * kCollect) {
-        const int n = wave_collect(cd, base, b1, lst[wave], lane);
-        for (int r = lane; r < n; r += 64) atomicAdd(h + min(mask_count(cd, lst[wave][r]), n_bins - 1), 1u);
-        wave_lds_sync();
+    const uint32_t* list = cd.seg + (size_t)s * cd.seg_cap;
+    for (; c0 < n; c0 += kChunkRow * kChunk) {
+        uint32_t e[kChunkPer];
+#pragma unroll
+        for (int k = 0; k < kChunkPer; ++k) {
+            const uint32_t i = c0 + threadIdx.x + 256u * k;
+            e[k] = i < n ? list[i] : ~0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kChunkPer; ++k)
+            if (e[k] != ~0u) atomicAdd(h + min(mask_count(cd, e[k]), n_bins - 1), 1u);
     }
     __syncthreads();
     for (int c = threadIdx.x; c < n_bins; c += blockDim.x)
         if (h[c]) atomicAdd(cd.bins + c, h[c]);
 }
 
-// Exclusive scan in descending operation count: offset[c] = #blocks with more
-// than c operations; the total is the number of candidate blocks.  One
-// workgroup; n_bins <= 4097.
-__global__ __launch_bounds__(1024) void scan_kernel(CandDev cd, int n_bins)
-{
-    __shared__ uint32_t part[1024];
-    const int tid = threadIdx.x;
-    const int per = (n_bins + 1023) / 1024;
-    // thread tid owns bins (descending) [n_bins-1 - tid*per, ...]
-    uint32_t sum = 0;
-    for (int k = 0; k < per; ++k) {
-        const int c = n_bins - 1 - (tid * per + k);
-        if (c >= 0) sum += cd.bins[c];
-    }
-    part[tid] = sum;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        uint32_t x = (tid >= off) ? part[tid - off] : 0u;
-        __syncthreads();
-        part[tid] += x;
-        __syncthreads();
-    }
-    uint32_t run = (tid > 0) ? part[tid - 1] : 0u;
-    for (int k = 0; k < per; ++k) {
-        const int c = n_bins - 1 - (tid * per + k);
-        if (c >= 0) {
-            const uint32_t b = cd.bins[c];
-            cd.bins[c] = run;
-            run += b;
-        }
-    }
-    if (tid == 1023) {
-        cd.counters[4] = part[1023];
-        cd.stats[0] += part[1023];  // slot 0 of counter 0
-    }
-}
-
-// Scatter into operation-count order: each workgroup reserves one range per
-// count it holds, then places its buckets inside those ranges, with each
-// block's key and current pool slot (looked up here, in parallel, so the
-// voxel pass starts a block with one round of independent loads).  Both
-// passes over the workgroup's buckets compact the occupied ones first.
+// Scatter into descending operation count: every workgroup scans the
+// histogram itself (offset[c] = candidates with more than c operations),
+// reserves one range per count it holds, then places its candidates inside
+// those ranges, with each block's key and current pool slot (looked up here,
+// in parallel, so the voxel pass starts a block with one round of independent
+// loads).
+// Bound: the latency of the random reads (masks, keys, the block hash).  The
+// histogram, a scan and a scatter that read the whole table of 2^21 keys took
+// 18 + 5 + 23 us of an update of 40 operations, so 10 + 24.
 __global__ __launch_bounds__(256) void scatter_kernel(CandDev cd, VolDev v, int n_bins)
 {
-    __shared__ uint32_t h[kMaxBatchOps + 1];
-    __shared__ uint32_t lst[4][kCollect];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t b0, b1;
-    wg_share(cd.mask_bits + 1u, b0, b1);
-    for (int c = threadIdx.x; c < n_bins; c += blockDim.x) h[c] = 0u;
-    __syncthreads();
-    for (uint32_t base = b0 + wave * kCollect; base < b1; base += 4 * kCollect) {
-        const int n = wave_collect(cd, base, b1, lst[wave], lane);
-        for (int r = lane; r < n; r += 64) atomicAdd(h + min(mask_count(cd, lst[wave][r]), n_bins - 1), 1u);
-        wave_lds_sync();
+    __shared__ uint32_t h[kMaxBatchOps + 1];    // histogram of the chunk, then its ranges
+    __shared__ uint32_t off[kMaxBatchOps + 1];  // first entry of each count
+    __shared__ uint32_t part[256];
+    const uint32_t s = blockIdx.x % (kSegs + 1);
+    const uint32_t n = min(cd.seg_n[s * kRecCountStride], s == kSegs ? ~0u : cd.seg_cap);
+    uint32_t c0 = blockIdx.x / (kSegs + 1) * kChunk;
+    if (c0 >= n && blockIdx.x != 0) return;
+    // descending scan: thread t owns the bins n_bins - 1 - (t per .. t per + per - 1)
+    const int per = (n_bins + 255) / 256;
+    uint32_t sum = 0u;
+    for (int k = 0; k < per; ++k) {
+        const int c = n_bins - 1 - ((int)threadIdx.x * per + k);
+        if (c >= 0) sum += cd.bins[c];
     }
+    part[threadIdx.x] = sum;
     __syncthreads();
-    for (int c = threadIdx.x; c < n_bins; c += blockDim.x)
-        if (h[c]) h[c] = atomicAdd(cd.bins + c, h[c]);
-    __syncthreads();
-    for (uint32_t base = b0 + wave * kCollect; base < b1; base += 4 * kCollect) {
-        const int n = wave_collect(cd, base, b1, lst[wave], lane);
-        for (int r = lane; r < n; r += 64) {
-            const uint32_t i = lst[wave][r];
-            const uint64_t key = cd.keys[i];
-            const uint32_t pos = atomicAdd(h + min(mask_count(cd, i), n_bins - 1), 1u);
-            int bx, by, bz;
-            unpack_key(key, bx, by, bz);
-            cd.sorted[pos] = i;
-            cd.skey[pos] = key;
-            cd.sslot[pos] = vol_find(v, key, bx, by, bz);
+    for (int o = 1; o < 256; o <<= 1) {
+        const uint32_t y = ((int)threadIdx.x >= o) ? part[threadIdx.x - o] : 0u;
+        __syncthreads();
+        part[threadIdx.x] += y;
+        __syncthreads();
+    }
+    uint32_t run = part[threadIdx.x] - sum;
+    for (int k = 0; k < per; ++k) {
+        const int c = n_bins - 1 - ((int)threadIdx.x * per + k);
+        if (c >= 0) {
+            off[c] = run;
+            run += cd.bins[c];
         }
-        wave_lds_sync();
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 255) {
+        cd.counters[4] = part[255];
+        cd.stats[0] += part[255];  // slot 0 of counter 0
+    }
+    const uint32_t* list = cd.seg + (size_t)s * cd.seg_cap;
+    for (; c0 < n; c0 += kChunkRow * kChunk) {
+        __syncthreads();
+        for (int c = threadIdx.x; c < n_bins; c += blockDim.x) h[c] = 0u;
+        __syncthreads();
+        uint32_t e[kChunkPer], cnt[kChunkPer], at[kChunkPer];
+        uint64_t key[kChunkPer];
+        int slot[kChunkPer];
+#pragma unroll
+        for (int k = 0; k < kChunkPer; ++k) {
+            const uint32_t i = c0 + threadIdx.x + 256u * k;
+            e[k] = i < n ? list[i] : ~0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kChunkPer; ++k) key[k] = e[k] != ~0u ? cd.keys[e[k]] : 0ull;
+#pragma unroll
+        for (int k = 0; k < kChunkPer; ++k) {
+            if (e[k] != ~0u) {
+                cnt[k] = (uint32_t)min(mask_count(cd, e[k]), n_bins - 1);
+                at[k] = atomicAdd(h + cnt[k], 1u);
+                int bx, by, bz;
+                unpack_key(key[k], bx, by, bz);
+                slot[k] = vol_find(v, key[k], bx, by, bz);
+            }
+        }
+        __syncthreads();
+        for (int c = threadIdx.x; c < n_bins; c += blockDim.x)
+            if (h[c]) h[c] = off[c] + atomicAdd(cd.bins + n_bins + c, h[c]);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kChunkPer; ++k) {
+            if (e[k] == ~0u) continue;
+            const uint32_t pos = h[cnt[k]] + at[k];
+            cd.sorted[pos] = e[k];
+            cd.skey[pos] = key[k];
+            cd.sslot[pos] = slot[k];
+        }
     }
 }
 
@@ -1323,27 +1333,32 @@ static bool schedule_ok(const sc_schedule& s)
 
 // Candidate stage: clears the per-batch counters, generates the candidate
 // blocks with their operation masks, and orders them by operation count.
-static void launch_candidates(sc_volume* vol, bool from_cells, hipStream_t s)
+// Variants: 0 pixels, 1 cell ranges of packed keyframes, 2 pixels on small
+// tiles.
+static void launch_candidates(sc_volume* vol, int variant, hipStream_t s)
 {
     const int n_bins = vol->p.max_batch_ops + 1;
+    seg_clear_kernel<<<1, 64, 0, s>>>(vol->cand);
     // first the recorded candidates (their kernel also clears the batch's
     // counters), then the frustum tiles
     // a workgroup per part of a record
     cand_record_kernel<<<dim3(kRecShards, (unsigned)std::min(vol->p.max_batch_ops, 256)), 256, 0, s>>>(
         vol->d_ops, vol->d_hdr, vol->dev, vol->cand, n_bins);
-    const int threads = CandCfg<kTileBatch, kCellBatch>::threads;
-    if (from_cells) {
-        cand_batch_kernel<true><<<vol->n_cu * vol->cand_wgs[1], threads, 0, s>>>(vol->d_ops, vol->d_hdr, vol->dev,
+    const int grid = vol->n_cu * vol->cand_wgs[variant];
+    constexpr int threads = CandCfg<kTileBatch, kCellBatch>::threads;
+    if (variant == 0)
+        cand_batch_kernel<kTileBatch, kCellBatch, false><<<grid, threads, 0, s>>>(vol->d_ops, vol->d_hdr, vol->dev,
+                                                                                  vol->cand);
+    else if (variant == 2)
+        cand_batch_kernel<kTilePlain, kCellBatch, false>
+            <<<grid, CandCfg<kTilePlain, kCellBatch>::threads, 0, s>>>(vol->d_ops, vol->d_hdr, vol->dev, vol->cand);
+    else {
+        cand_batch_kernel<kTileBatch, kCellBatch, true><<<grid, threads, 0, s>>>(vol->d_ops, vol->d_hdr, vol->dev,
                                                                                  vol->cand);
         cand_big_kernel<<<vol->n_cu, threads, 0, s>>>(vol->d_ops, vol->d_hdr, vol->dev, vol->cand);
-    } else
-        cand_batch_kernel<false><<<vol->n_cu * vol->cand_wgs[0], threads, 0, s>>>(vol->d_ops, vol->d_hdr, vol->dev,
-                                                                                  vol->cand);
-    // two workgroups per CU: fewer of them meet on the global bins of the
-    // common operation counts (28 -> 22 us and 40 -> 37 us against four)
-    hist_kernel<<<vol->n_cu * 2, 256, 0, s>>>(vol->cand, n_bins);
-    scan_kernel<<<1, 1024, 0, s>>>(vol->cand, n_bins);
-    scatter_kernel<<<vol->n_cu * 2, 256, 0, s>>>(vol->cand, vol->dev, n_bins);
+    }
+    hist_kernel<<<(kSegs + 1) * kChunkRow, 256, 0, s>>>(vol->cand, n_bins);
+    scatter_kernel<<<(kSegs + 1) * kChunkRow, 256, 0, s>>>(vol->cand, vol->dev, n_bins);
 }
 
 // The persistent voxel pass with schedule `sch`; `packed`: every operation
@@ -1477,8 +1492,6 @@ sc_status run_candidates(sc_volume* vol, const OpDesc* ops, int n_ops, const sc_
 {
     BatchHdr* hdr = stage_hdr(vol);
     hdr->n_ops = n_ops;
-    hdr->tiles_x = (in->width + kTileBatch - 1) / kTileBatch;
-    hdr->tiles_y = (in->height + kTileBatch - 1) / kTileBatch;
     hdr->n_tile_ops = 0;
     // the frustum-cell operations read cell depth ranges when every one of
     // them has a packed keyframe
@@ -1488,6 +1501,16 @@ sc_status run_candidates(sc_volume* vol, const OpDesc* ops, int n_ops, const sc_
             hdr->tile_ops[hdr->n_tile_ops++] = (int16_t)o;
             from_cells = from_cells && ops[o].cells != nullptr;
         }
+    // 32-pixel tiles for unpacked keyframes whose 64-pixel tiles span more than
+    // four blocks at 2 m: such a tile's blocks crowd its LDS set.  Sixteen
+    // keyframes at 320x240 (1 cm voxels, six blocks): candidate stage 291 us
+    // on 64-pixel tiles, 136 on 32; at 640x480 (three blocks) 152 and 134, but
+    // eight keyframes 78 and 133.  Packed keyframes' bit maps do not crowd:
+    // 85 and 140 us for sixteen at 640x480, 93 and 95 at 320x240
+    const bool small = !from_cells && (float)kTileBatch * 2.0f > 4.0f * 8.0f * vol->p.voxel_size * in->fx;
+    const int tile = small ? kTilePlain : kTileBatch;
+    hdr->tiles_x = (in->width + tile - 1) / tile;
+    hdr->tiles_y = (in->height + tile - 1) / tile;
     const size_t hdr_bytes = offsetof(BatchHdr, tile_ops) + sizeof(int16_t) * (size_t)std::max(hdr->n_tile_ops, 1);
     if (hipMemcpyAsync(vol->d_ops, ops, sizeof(OpDesc) * n_ops, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(vol->d_hdr, hdr, hdr_bytes, hipMemcpyHostToDevice, s) != hipSuccess)
@@ -1495,8 +1518,9 @@ sc_status run_candidates(sc_volume* vol, const OpDesc* ops, int n_ops, const sc_
     // the staging buffer may be refilled once these copies have run
     const sc_status st = stage_end(vol, s);
     if (st != SC_OK) return st;
-    hipGraphExec_t& pre = vol->graph_pre[from_cells ? 1 : 0];
-    if (!pre) pre = capture(vol, [&](hipStream_t cs) { launch_candidates(vol, from_cells, cs); });
+    const int variant = from_cells ? 1 : small ? 2 : 0;
+    hipGraphExec_t& pre = vol->graph_pre[variant];
+    if (!pre) pre = capture(vol, [&](hipStream_t cs) { launch_candidates(vol, variant, cs); });
     if (!pre || hipGraphLaunch(pre, s) != hipSuccess) return SC_EDEVICE;
     return SC_OK;
 }

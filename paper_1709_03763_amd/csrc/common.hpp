@@ -113,13 +113,16 @@ struct CandDev {
     uint64_t* skey;       // block key of each sorted entry
     int32_t* sslot;       // pool slot of each sorted entry's block before the pass (-1: not allocated)
     uint32_t* counters;   // [0..1] list length of the plain path (parity),
-                          // [4] batch candidates, [5] batch work cursor, [6] batch tile cursor
-    uint32_t* bins;       // per-operation-count histogram / offsets (batched path)
+                          // [4] batch candidates, [5] batch work cursor
+    uint32_t* seg;        // batched path: occupied buckets, kSegs lists of seg_cap, then one of every bucket
+    uint32_t* seg_n;      // their lengths, kRecCountStride words apart (may exceed seg_cap: the rest is in the last)
+    uint32_t* bins;       // per-operation-count histogram, then the cursors within the counts (batched path)
     uint32_t* cursors;    // two sets (candidate stage, voxel pass) of kCursors work cursors, kCursorStride words apart
     uint32_t* big;        // [0] tiles whose block box exceeds the bit map, then up to kBigCap of their items
     unsigned long long* stats;  // cumulative: candidate blocks, (block, op) pairs, voxel updates, blocks written
     uint32_t mask_bits;   // cand buckets - 1
     uint32_t cap;         // list capacity (plain path)
+    uint32_t seg_cap;     // capacity of a list of the batched path
     int32_t words;        // 64-bit mask words per bucket
 };
 
@@ -130,13 +133,14 @@ constexpr int kCursors = 32;
 constexpr int kCursorStride = 1024;  // 32-bit words
 constexpr int kCursorDone = 512;     // word of the bit mask of exhausted ranges (its own cache line)
 constexpr int kCursorSet = kCursors * kCursorStride;  // words per set
+constexpr int kSegs = 32;       // candidate lists of the batched path
 constexpr int kBigCap = 16384;  // listed tiles with an oversized block box (beyond: every tile is redone)
 
 // Batched-update header in device memory, so a captured graph can be
 // replayed with a different number of operations.
 struct BatchHdr {
     int32_t n_ops;
-    int32_t tiles_x, tiles_y;
+    int32_t tiles_x, tiles_y;        // of the tile size that the candidate stage was captured with
     int32_t n_tile_ops;              // operations whose candidates come from frustum cells
     int16_t tile_ops[kMaxBatchOps];  // their indices (the others take a touched-block record)
 };
@@ -161,14 +165,15 @@ struct sc_volume {
     hipStream_t cap_stream;  // private stream used for graph capture
     hipEvent_t staged[2];    // recorded after each staging buffer's descriptors were copied to the device
     int stage;               // staging buffer the next chunk fills
-    hipGraphExec_t graph_pre[2];  // captured candidate stage (init, candidates, histogram, scan, scatter): pixels, cell ranges
+    hipGraphExec_t graph_pre[3];  // captured candidate stage (init, candidates, histogram, scatter): pixels, cell
+                                  // ranges, pixels on small tiles
     hipGraphExec_t graph_main[8]; // captured voxel pass per voxels-per-lane choice, unpacked / packed keyframes
     int graph_keys[8];       // schedule the voxel-pass graph of each slot was captured with
     hipEvent_t* timing_ev;   // optional per-launch event pairs (2 * timing_cap)
     int timing_cap, timing_n;
     sc_schedule sched;
     int n_cu;
-    int cand_wgs[2];         // resident workgroups per CU of the batched candidate kernel: pixels, cell ranges
+    int cand_wgs[3];         // resident workgroups per CU of the batched candidate kernel, as graph_pre
     int plain_wgs;           // resident workgroups per CU of the plain update kernel
     double* adj_acc;         // device, 3 x kAdjChunk: pose terms of one backward chunk (zero between calls)
     struct RecordRegistry* rec;  // touched-block records of integrations (host index, device lists)

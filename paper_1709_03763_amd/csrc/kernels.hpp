@@ -874,15 +874,67 @@ __device__ inline void cand_append(const CandDev& cd, const VolDev& v, uint32_t 
         set_error(v.err, SC_EHASHFULL);
 }
 
-// Per-lane insertion with its own list append (the rare LDS-overflow path;
-// no list when count is null).
+// The batched path's lists of new candidates: entry idx of list s, or, past
+// its end, the last list, which has room for every bucket.
+__device__ inline void seg_put(const CandDev& cd, int s, uint32_t idx, uint32_t gb)
+{
+    if (s == kSegs || idx >= cd.seg_cap) {
+        s = kSegs;
+        idx = atomicAdd(cd.seg_n + kSegs * kRecCountStride, 1u);
+    }
+    cd.seg[(size_t)s * cd.seg_cap + idx] = gb;
+}
+
+// Reserves cnt entries of list s.
+__device__ inline uint32_t seg_reserve(const CandDev& cd, int s, uint32_t cnt)
+{
+    return atomicAdd(cd.seg_n + s * kRecCountStride, cnt);
+}
+
+// Per-lane insertion with its own list append (the rare paths): the plain
+// path's list, or the batched path's when count is null.
 __device__ inline int cand_insert(const CandDev& cd, const VolDev& v, uint64_t key, int bx, int by, int bz,
                                   uint32_t* count)
 {
     bool fresh;
     const int gb = cand_claim(cd, v, key, bx, by, bz, fresh);
-    if (fresh && count) cand_append(cd, v, atomicAdd(count, 1u), gb);
+    if (fresh) {
+        if (count)
+            cand_append(cd, v, atomicAdd(count, 1u), gb);
+        else
+            seg_put(cd, kSegs, 0u, (uint32_t)gb);
+    }
     return gb;
+}
+
+// New candidates of one tile (or record part) of the batched path, held in
+// LDS until the workgroup appends them with one atomic.
+constexpr uint32_t kFresh = 512;
+struct FreshList {
+    uint32_t* buf;  // kFresh
+    uint32_t* n;    // 0 before the first tile
+    int seg;
+};
+
+__device__ inline void fresh_put(const CandDev& cd, const FreshList& f, uint32_t gb)
+{
+    const uint32_t pos = atomicAdd(f.n, 1u);
+    if (pos < kFresh)
+        f.buf[pos] = gb;
+    else
+        seg_put(cd, kSegs, 0u, gb);
+}
+
+// Every thread of the workgroup.  `base`: one word of LDS.
+__device__ inline void fresh_flush(const CandDev& cd, const FreshList& f, uint32_t* base)
+{
+    __syncthreads();
+    const uint32_t n = min(*f.n, kFresh);
+    if (threadIdx.x == 0 && n) *base = seg_reserve(cd, f.seg, n);
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) seg_put(cd, f.seg, *base + j, f.buf[j]);
+    if (threadIdx.x == 0) *f.n = 0u;
+    __syncthreads();
 }
 
 // LDS slot of a block: low coordinate bits, no multiplies (a tile's blocks
@@ -1102,7 +1154,7 @@ struct BitIns {
 // done: the caller takes the hash set).  `red` holds 8 floats of LDS.
 template <int TILE>
 __device__ inline bool cand_tile_bits(const OpDesc& op, const VolDev& v, const CandDev& cd, int tx, int ty, int op_bit,
-                                      uint32_t* bits, uint16_t* idx, float* red)
+                                      uint32_t* bits, uint16_t* idx, float* red, const FreshList& fl)
 {
     constexpr int kCells = TILE / 4;
     constexpr int kThreads = kCells * kCells;
@@ -1160,6 +1212,7 @@ __device__ inline bool cand_tile_bits(const OpDesc& op, const VolDev& v, const C
                 bool fresh;
                 const int gb = cand_claim(cd, v, pack_key(bx, by, bz), bx, by, bz, fresh);
                 if (gb >= 0) cand_mark(cd, gb, op_bit);
+                if (fresh) fresh_put(cd, fl, (uint32_t)gb);
             }
         }
         wave_lds_sync();
@@ -1200,12 +1253,11 @@ __device__ inline bool cand_tile_bits(const OpDesc& op, const VolDev& v, const C
 // blocks of the frustum cells' boxes are deduplicated in an LDS hash set, then
 // inserted once per
 // tile into the global candidate table; with op_bit >= 0 the operation's bit
-// is set in the block's mask.  With count non-null, new candidates are also
-// appended to the candidate list (the plain path); the batched path finds
-// them by scanning the table instead.
+// is set in the block's mask.  New candidates are appended to the plain path's
+// list, or, when count is null, to list `seg` of the batched path.
 template <int TILE, int CELL, bool kFromCells = false>
 __device__ inline void cand_tile(const OpDesc& op, const VolDev& v, const CandDev& cd, uint32_t* count, int tx,
-                                 int ty, int op_bit, uint64_t* lds, uint16_t* idx)
+                                 int ty, int op_bit, uint64_t* lds, uint16_t* idx, int seg = 0)
 {
     constexpr int kCells = TILE / CELL;
     constexpr int kThreads = CandCfg<TILE, CELL>::threads;
@@ -1280,9 +1332,9 @@ __device__ inline void cand_tile(const OpDesc& op, const VolDev& v, const CandDe
     // insert the tile's blocks: each wavefront first compacts the occupied
     // entries of its part of the set into its index list (about one in twenty
     // is occupied), then claims them 64 at a time, so it waits for about one
-    // claim latency rather than one per round holding an occupied entry.  With
-    // a list, each claimed entry is replaced by its bucket if it is a new
-    // candidate, and the tile appends them with one atomic (with one per
+    // claim latency rather than one per round holding an occupied entry.  Each
+    // claimed entry is replaced by its bucket if it is a new candidate, and the
+    // tile appends them with one atomic (with one per
     // wavefront and round, queued on the counter, a 640x480 keyframe's
     // candidates took 15 us, so 11)
     const int lane = tid & 63;
@@ -1309,29 +1361,32 @@ __device__ inline void cand_tile(const OpDesc& op, const VolDev& v, const CandDe
             unpack_key(key, bx, by, bz);
             gb = cand_claim(cd, v, key, bx, by, bz, fresh);
             if (gb >= 0 && op_bit >= 0) cand_mark(cd, gb, op_bit);
-            if (count) lds[wl[r]] = fresh ? (uint64_t)gb : kKeyEmpty;
+            lds[wl[r]] = fresh ? (uint64_t)gb : kKeyEmpty;
         }
         n_fresh += __popcll(__ballot(fresh));
     }
-    if (count) {
-        __shared__ uint32_t part[kThreads / 64], base;
-        if (lane == 0) part[tid >> 6] = (uint32_t)n_fresh;
-        __syncthreads();
-        if (tid == 0) {
-            uint32_t sum = 0u;
-            for (int w = 0; w < kThreads / 64; ++w) sum += part[w];
-            base = sum ? atomicAdd(count, sum) : 0u;
+    __shared__ uint32_t part[kThreads / 64], base;
+    if (lane == 0) part[tid >> 6] = (uint32_t)n_fresh;
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t sum = 0u;
+        for (int w = 0; w < kThreads / 64; ++w) sum += part[w];
+        if (sum) base = count ? atomicAdd(count, sum) : seg_reserve(cd, seg, sum);
+    }
+    __syncthreads();
+    uint32_t to = base;
+    for (int w = 0; w < (tid >> 6); ++w) to += part[w];
+    for (int r0 = 0; r0 < n; r0 += 64) {
+        const int r = r0 + lane;
+        const uint64_t e = r < n ? lds[wl[r]] : kKeyEmpty;
+        const uint64_t bal = __ballot(e != kKeyEmpty);
+        if (e != kKeyEmpty) {
+            if (count)
+                cand_append(cd, v, to + lanes_below(bal), (int)e);
+            else
+                seg_put(cd, seg, to + lanes_below(bal), (uint32_t)e);
         }
-        __syncthreads();
-        uint32_t to = base;
-        for (int w = 0; w < (tid >> 6); ++w) to += part[w];
-        for (int r0 = 0; r0 < n; r0 += 64) {
-            const int r = r0 + lane;
-            const uint64_t e = r < n ? lds[wl[r]] : kKeyEmpty;
-            const uint64_t bal = __ballot(e != kKeyEmpty);
-            if (e != kKeyEmpty) cand_append(cd, v, to + lanes_below(bal), (int)e);
-            to += (uint32_t)__popcll(bal);
-        }
+        to += (uint32_t)__popcll(bal);
     }
 }
 

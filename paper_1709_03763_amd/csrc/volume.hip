@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) void reset_kernel(VolDev v, CandDev c, double*
         fill_words(c.mask, sizeof(uint64_t) * cand * c.words, 0u);
     }
     fill_words(c.counters, sizeof(uint32_t) * 64, 0u);
-    fill_words(c.bins, sizeof(uint32_t) * (kMaxBatchOps + 2), 0u);
+    fill_words(c.bins, sizeof(uint32_t) * 2 * (kMaxBatchOps + 2), 0u);
     fill_words(c.cursors, sizeof(uint32_t) * 2 * kCursorSet, 0u);
     fill_words(c.big, sizeof(uint32_t), 0u);
     fill_words(c.stats, sizeof(unsigned long long) * 4 * kStatSlots * kStatStride, 0u);
@@ -720,8 +720,7 @@ sc_status sc_volume_create(const sc_volume_params* p, sc_volume** out)
     vol->p = *p;
     vol->device = dev;
     vol->n_cu = prop.multiProcessorCount;
-    vol->cand_wgs[0] = cand_batch_resident_wgs(false);
-    vol->cand_wgs[1] = cand_batch_resident_wgs(true);
+    for (int k = 0; k < 3; ++k) vol->cand_wgs[k] = cand_batch_resident_wgs(k);
     {
         int n = 0;
         const void* k = p->color_mode == SC_COLOR_F32 ? (const void*)update_plain_kernel<SC_COLOR_F32, false>
@@ -757,6 +756,7 @@ sc_status sc_volume_create(const sc_volume_params* p, sc_volume** out)
     c.mask_bits = (uint32_t)(cb - 1);
     c.cap = (uint32_t)(cb / 2);
     c.words = (p->max_batch_ops + 63) / 64;
+    c.seg_cap = (uint32_t)(cb / 16);  // twice an even share; what does not fit goes to the last list
     bool ok = true;
     ok &= hipMalloc(&d.keys, sizeof(uint64_t) * p->n_buckets) == hipSuccess;
     ok &= hipMalloc(&d.vals, sizeof(int32_t) * p->n_buckets) == hipSuccess;
@@ -771,7 +771,9 @@ sc_status sc_volume_create(const sc_volume_params* p, sc_volume** out)
     ok &= hipMalloc(&c.skey, sizeof(uint64_t) * cb) == hipSuccess;
     ok &= hipMalloc(&c.sslot, sizeof(int32_t) * cb) == hipSuccess;
     ok &= hipMalloc(&c.counters, 64 * sizeof(uint32_t)) == hipSuccess;
-    ok &= hipMalloc(&c.bins, sizeof(uint32_t) * (kMaxBatchOps + 2)) == hipSuccess;
+    ok &= hipMalloc(&c.bins, sizeof(uint32_t) * 2 * (kMaxBatchOps + 2)) == hipSuccess;
+    ok &= hipMalloc(&c.seg, sizeof(uint32_t) * ((size_t)kSegs * c.seg_cap + cb)) == hipSuccess;
+    ok &= hipMalloc(&c.seg_n, sizeof(uint32_t) * (kSegs + 1) * kRecCountStride) == hipSuccess;
     ok &= hipMalloc(&c.cursors, sizeof(uint32_t) * 2 * kCursorSet) == hipSuccess;
     ok &= hipMalloc(&c.big, sizeof(uint32_t) * (kBigCap + 1)) == hipSuccess;
     ok &= hipMalloc(&c.stats, sizeof(unsigned long long) * 4 * kStatSlots * kStatStride) == hipSuccess;
@@ -825,6 +827,8 @@ void sc_volume_destroy(sc_volume* vol)
     hipFree(vol->cand.sorted);
     hipFree(vol->cand.counters);
     hipFree(vol->cand.bins);
+    hipFree(vol->cand.seg);
+    hipFree(vol->cand.seg_n);
     hipFree(vol->cand.cursors);
     hipFree(vol->cand.big);
     hipFree(vol->d_ops);
