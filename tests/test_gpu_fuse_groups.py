@@ -1,0 +1,75 @@
+"""Keyframe fusion over the group's size, and the packed records, against the
+oracle (bit-exact: integers and FP32 values decided by the same written
+operations)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1709_03763_amd import scsurf, synth
+from test_gpu_fuse import _plane_frames
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(kf, ref):
+    np.testing.assert_array_equal(kf.weight.cpu().numpy(), ref["weight"])
+    np.testing.assert_array_equal(kf.depth.cpu().numpy(), ref["depth"])
+    np.testing.assert_array_equal(kf.color.cpu().numpy(), ref["color"])
+
+
+@pytest.mark.parametrize("n,W,H", [(1, 13, 5), (2, 64, 3), (3, 65, 4), (4, 31, 9), (5, 63, 3), (6, 17, 8), (7, 40, 7),
+                                   (8, 64, 4), (9, 33, 6), (10, 21, 20), (64, 19, 8)])
+def test_colour_median_by_group_size(n, W, H):
+    """Every form of the median (1 to 8 frames in registers, more by
+    bisection), the last workgroup of 64 pixels partly empty; and near
+    frames, whose weights' total needs more than 32 bits."""
+    print(f"[gpu] colour median {n} frames {W}x{H}", flush=True)
+    intr, z, rgb, R, t = _plane_frames(W, H, n, 1000 + n)
+    rgb = np.random.default_rng(n).integers(0, 256, rgb.shape, dtype=np.uint8)
+    for scale in (1.0, 0.03):
+        zs, ts = (z * np.float32(scale)).astype(np.float32), t * scale
+        zm = 2.0 ** -5 if scale < 1 else 0.3
+        kf = scsurf.kf_fuse(torch.from_numpy(zs).cuda(), torch.from_numpy(rgb).cuda(), R, ts, intr,
+                            params=scsurf.fuse_params(z_min=zm))
+        _check(kf, oracle.kf_fuse(zs, rgb, intr, R, ts, z_min=zm))
+
+
+def test_colour_output_of_any_alignment():
+    print("[gpu] unaligned colour output", flush=True)
+    W, H, n = 35, 6, 3
+    intr, z, rgb, R, t = _plane_frames(W, H, n, 4)
+    ref = oracle.kf_fuse(z, rgb, intr, R, t)
+    for off in (1, 2, 3):
+        buf = torch.full((4 * W * H + 8,), 77, dtype=torch.uint8, device="cuda")
+        out = scsurf.Keyframe(torch.empty((H, W), device="cuda"), torch.empty((H, W), device="cuda"),
+                              buf[off:off + 4 * W * H].view(H, W, 4))
+        _check(scsurf.kf_fuse(torch.from_numpy(z).cuda(), torch.from_numpy(rgb).cuda(), R, t, intr, out=out), ref)
+        edge = torch.cat([buf[:off], buf[off + 4 * W * H:]])
+        assert (edge == 77).all()
+
+
+@pytest.mark.parametrize("W,H", [(1, 1), (3, 4), (63, 5), (64, 8), (65, 7), (130, 9)])
+def test_pack_edges(W, H):
+    """Records and cell ranges around 64 columns and 4 rows."""
+    print(f"[gpu] pack {W}x{H}", flush=True)
+    rng = np.random.default_rng(W * 10 + H)
+    z = rng.uniform(-0.2, 3.0, (H, W)).astype(np.float32)
+    w = rng.uniform(-0.2, 2.0, (H, W)).astype(np.float32)
+    c = rng.integers(0, 256, (H, W, 4), dtype=np.uint8)
+    kf = scsurf.keyframe_pack(scsurf.Keyframe(*(torch.from_numpy(a).cuda() for a in (z, w, c))))
+    q = (np.rint(w * np.float32(1024)) / np.float32(1024)).astype(np.float32)
+    rec = kf.packed.cpu().numpy()
+    pos = q > 0
+    np.testing.assert_array_equal(rec[..., 0].view(np.float32), np.where(pos, z, -np.inf))
+    np.testing.assert_array_equal(rec[..., 1].view(np.float32)[pos], q[pos])
+    np.testing.assert_array_equal(rec[..., 2].view(np.uint32), c.view(np.uint32)[..., 0])
+    ch, cw = (H + 3) // 4, (W + 3) // 4
+    total = scsurf.lib().sc_keyframe_pack_bytes(W, H) // 4
+    cells = kf.packed.as_strided((total,), (1,)).cpu().numpy()[4 * H * W:].view(np.float32).reshape(ch, cw, 2)
+    for i in range(ch):
+        for j in range(cw):
+            s = np.s_[4 * i:4 * i + 4, 4 * j:4 * j + 4]
+            v = z[s][pos[s] & (z[s] > 0)]
+            lo, hi = (v.min(), v.max()) if v.size else (np.inf, -np.inf)
+            assert (cells[i, j, 0], cells[i, j, 1]) == (np.float32(lo), np.float32(hi))

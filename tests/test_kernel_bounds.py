@@ -175,3 +175,31 @@ def test_median_rule_picks_exactly_the_lower_weighted_median():
                 passed.append(j)
         assert len(passed) == 1, (trial, passed)
         assert c[passed[0]] == brute
+
+
+def test_median_of_rounded_values_is_the_rounded_median():
+    """The colour kernel's form: of observations rounded to 8 bits first, the
+    smallest value up to which the weights reach half the total (found from
+    the observations' own sums, or by bisection of 256 values) is the lower
+    weighted median of the unrounded ones, rounded."""
+    rng = np.random.default_rng(23)
+    for trial in range(5000):
+        m = int(rng.integers(1, 65))
+        c = rng.uniform(0, 65280, m) if trial % 2 else rng.integers(0, 8, m) * 128.0 + rng.uniform(-1, 1, m)
+        w = rng.integers(0, 2 ** int(rng.integers(1, 32)), m, dtype=np.int64)
+        total = int(w.sum())
+        if total == 0:
+            continue
+        order = np.argsort(c, kind="stable")
+        cum = np.cumsum(w[order])
+        med = c[order][np.argmax((2 * cum >= total) & (w[order] > 0))]
+        exp = int(np.clip(np.rint(F32(med) / F32(256)), 0, 255))
+        r = np.clip(np.rint(f32(c) / F32(256)), 0, 255).astype(np.int64)
+        r[w == 0] = 0
+        upto = np.array([w[r <= v].sum() for v in range(256)])
+        assert min(int(v) for v in r if 2 * upto[v] >= total) == exp
+        lo, hi = 0, 255
+        for _ in range(8):
+            mid = (lo + hi) >> 1
+            lo, hi = (lo, mid) if 2 * upto[mid] >= total else (mid + 1, hi)
+        assert hi == exp
