@@ -378,38 +378,53 @@ __global__ void export_kernel(VolDev v, int64_t n, int32_t* xyz, float* D, float
 }
 
 // Packed record of a pixel: the quantised weight, and the depth only where
-// that weight is positive (-inf elsewhere, which fails every band test).
-__global__ void pack_kernel(const float* depth, const float* weight, const uint32_t* color, uint4* out, int64_t n)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float w = qweight(weight[i]);
-        const float z = (w > 0.0f) ? depth[i] : -__builtin_inff();
-        out[i] = make_uint4(__float_as_uint(z), __float_as_uint(w), color[i], 0u);
-    }
-}
-
-// Depth range {zmin, zmax} of the valid pixels (positive quantised weight,
+// that weight is positive (-inf elsewhere, which fails every band test); and
+// the depth range {zmin, zmax} of the valid pixels (positive quantised weight,
 // 0 < depth < 1e30) of each 4 x 4 cell, {+inf, -inf} without one: the
 // candidate stage's per-cell test without reading the pixels.
-__global__ void pack_cells_kernel(const float* depth, const float* weight, float2* cells, int width, int height,
-                                  int cells_w, int64_t n_cells)
+// A wavefront takes 64 columns of one row of cells, a lane a column of four
+// pixels (its loads issue together), and four lanes share a cell.  Bound: the
+// launch and one round of loads; records and cells in two kernels, the cells
+// reading every pixel again, took 3.6 + 5.4 us at 640x480, now 4.3.
+__global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ depth, const float* __restrict__ weight,
+                                                   const uint32_t* __restrict__ color, uint4* out, float2* cells,
+                                                   int width, int height, int cells_w, int64_t n_items)
 {
-    for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n_cells;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        const int cy = (int)(c / cells_w), cx = (int)(c - (int64_t)cy * cells_w);
-        float zmin = __builtin_inff(), zmax = -__builtin_inff();
-        for (int q = 0; q < 16; ++q) {
-            const int u = 4 * cx + (q & 3), v = 4 * cy + (q >> 2);
-            if (u >= width || v >= height) continue;
-            const int64_t pix = (int64_t)v * width + u;
-            const float z = depth[pix];
-            if (qweight(weight[pix]) > 0.0f && z > 0.0f && z < 1.0e30f) {
-                zmin = fminf(zmin, z);
-                zmax = fmaxf(zmax, z);
-            }
-        }
-        cells[c] = make_float2(zmin, zmax);
+    const int lane = threadIdx.x & 63;
+    const int strips = (width + 63) / 64;
+    const int64_t item = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6);
+    if (item >= n_items) return;
+    const int cy = (int)(item / strips), u = (int)(item - (int64_t)cy * strips) * 64 + lane;
+    float z[4], w[4];
+    uint32_t c[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int y = 4 * cy + r;
+        const bool in = u < width && y < height;
+        const int64_t i = in ? (int64_t)y * width + u : 0;
+        z[r] = depth[i];
+        w[r] = in ? weight[i] : 0.0f;
+        c[r] = color[i];
     }
+    float zmin = __builtin_inff(), zmax = -__builtin_inff();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int y = 4 * cy + r;
+        const float q = qweight(w[r]);
+        if (u < width && y < height)
+            out[(int64_t)y * width + u] =
+                make_uint4(__float_as_uint(q > 0.0f ? z[r] : -__builtin_inff()), __float_as_uint(q), c[r], 0u);
+        if (q > 0.0f && z[r] > 0.0f && z[r] < 1.0e30f) {
+            zmin = fminf(zmin, z[r]);
+            zmax = fmaxf(zmax, z[r]);
+        }
+    }
+#pragma unroll
+    for (int o = 1; o < 4; o <<= 1) {
+        zmin = fminf(zmin, __shfl_xor(zmin, o));
+        zmax = fmaxf(zmax, __shfl_xor(zmax, o));
+    }
+    if ((lane & 3) == 0 && u < width) cells[(int64_t)cy * cells_w + (u >> 2)] = make_float2(zmin, zmax);
 }
 
 // ---------------------------------------------------------------------------
@@ -919,15 +934,11 @@ sc_status sc_keyframe_pack(const sc_keyframe* kf, int32_t width, int32_t height,
         packed_bytes < need)
         return SC_EINVAL;
     const int64_t n = (int64_t)width * height;
-    const int grid = (int)std::min<int64_t>((n + 255) / 256, 65536);
-    pack_kernel<<<grid, 256, 0, (hipStream_t)stream>>>(kf->depth, kf->weight,
-                                                        reinterpret_cast<const uint32_t*>(kf->color),
-                                                        reinterpret_cast<uint4*>(packed), n);
-    const int cells_w = (width + 3) / 4;
-    const int64_t n_cells = (int64_t)cells_w * ((height + 3) / 4);
-    pack_cells_kernel<<<(int)std::min<int64_t>((n_cells + 255) / 256, 65536), 256, 0, (hipStream_t)stream>>>(
-        kf->depth, kf->weight, reinterpret_cast<float2*>(reinterpret_cast<uint4*>(packed) + n), width, height, cells_w,
-        n_cells);
+    const int cells_w = (width + 3) / 4, cells_h = (height + 3) / 4;
+    const int64_t items = (int64_t)((width + 63) / 64) * cells_h;  // wavefronts
+    pack_kernel<<<(unsigned)((items + 3) / 4), 256, 0, (hipStream_t)stream>>>(
+        kf->depth, kf->weight, reinterpret_cast<const uint32_t*>(kf->color), reinterpret_cast<uint4*>(packed),
+        reinterpret_cast<float2*>(reinterpret_cast<uint4*>(packed) + n), width, height, cells_w, items);
     return hipGetLastError() == hipSuccess ? SC_OK : SC_EDEVICE;
 }
 
