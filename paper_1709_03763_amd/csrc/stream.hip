@@ -22,25 +22,41 @@
 #include "internal.hpp"
 #include "kernels.hpp"
 
-// Host side of the streaming mode: where each host-held block lives, the
-// host copies, and pinned / device staging for the transfers.
+// A block on its way: its host record, and its pool slot (out) with the slot
+// of the block that takes its place (out: -1 for none).  The kernels read the
+// list in pinned memory.
+struct StreamItem {
+    uint64_t key;
+    unsigned char* host;
+    int32_t slot, mover;
+};
+
+// What an operation's stage tells the host: requested and candidate blocks,
+// allocated blocks, sticky error.
+struct StreamReport {
+    uint32_t n_req, n_cand, n_blocks;
+    int32_t err;
+};
+
+// Host side of the streaming mode.  The records lie in chunks of pinned
+// memory, which the kernels write and read themselves: no staging copy on
+// either side, and the host waits once an operation, for the report.
 struct StreamStore {
     bool enabled = false;
-    size_t block_bytes = 0;                      // one block's record in the pool
-    std::unordered_map<uint64_t, size_t> where;  // block key -> host slot
-    std::vector<unsigned char> arena;            // host slots x block_bytes
-    std::vector<size_t> free_slots;
-    size_t n_slots = 0;
-    unsigned char* h_stage = nullptr;  // pinned, blocks
-    unsigned char* d_stage = nullptr;  // device, blocks
-    size_t stage_cap = 0;              // blocks
-    uint64_t* h_keys = nullptr;        // pinned
-    uint64_t* d_keys = nullptr;        // device: requested keys
-    uint64_t* d_all = nullptr;         // device: every candidate key of the operation or chunk
-    int32_t* d_slots = nullptr;        // device
-    int32_t* h_slots = nullptr;        // pinned
+    size_t block_bytes = 0;                              // one block's record in the pool
+    std::unordered_map<uint64_t, unsigned char*> where;  // block key -> host record
+    std::vector<std::pair<unsigned char*, size_t>> chunks;  // pinned, blocks
+    size_t cur = 0, pos = 0;                             // first record never used: in chunk cur at pos
+    std::vector<unsigned char*> free_recs;
+    StreamItem* in = nullptr;   // pinned lists
+    StreamItem* out = nullptr;
+    size_t in_cap = 0, out_cap = 0;
+    StreamReport* report = nullptr;  // pinned
+    uint64_t* h_keys = nullptr;      // pinned: requested keys, or those of the device blocks
+    uint64_t* d_all = nullptr;       // device: every candidate key of the operation or chunk
     size_t keys_cap = 0;
-    uint32_t* d_req = nullptr;         // device counter
+    uint32_t* d_req = nullptr;       // device counter, zero between operations
+    hipEvent_t done = nullptr;       // after the last kernel that uses the lists or records
     int64_t blocks_out = 0, blocks_in = 0;
 };
 
@@ -68,17 +84,32 @@ __device__ inline void hash_put(const VolDev& v, uint64_t key, int slot)
     set_error(v.err, SC_EHASHFULL);
 }
 
+// Appends the requested keys of a wavefront to the list in pinned memory: one
+// counter update, and the keys leave in one piece.
+__device__ inline void request(bool mine, uint64_t key, uint64_t* req, uint32_t* count, uint32_t cap)
+{
+    const uint64_t m = __ballot(mine);
+    if (m == 0ull) return;
+    const int lane = threadIdx.x & 63;
+    uint32_t base = 0;
+    if (lane == 0) base = atomicAdd(count, (uint32_t)__popcll(m));
+    base = __shfl(base, 0);
+    const uint32_t p = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+    if (mine && p < cap) req[p] = key;
+}
+
 // Keys of the batched candidate blocks (all of them into `all`, count in
 // cd.counters[4]) and of those without a device slot (new blocks, or blocks
 // held by the host store) into `req`.
 __global__ void stream_req_batch_kernel(CandDev cd, uint64_t* all, uint64_t* req, uint32_t* count, uint32_t cap)
 {
     const uint32_t n = min(cd.counters[4], cap);
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        all[i] = cd.skey[i];
-        if (cd.sslot[i] >= 0) continue;
-        const uint32_t p = atomicAdd(count, 1u);
-        if (p < cap) req[p] = cd.skey[i];
+    // whole wavefronts stay in the loop
+    for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {
+        const uint32_t i = i0 + threadIdx.x;
+        const uint64_t key = i < n ? cd.skey[i] : 0ull;
+        if (i < n) all[i] = key;
+        request(i < n && cd.sslot[min(i, n - 1)] < 0, key, req, count, cap);
     }
 }
 
@@ -88,30 +119,63 @@ __global__ void stream_req_plain_kernel(CandDev cd, VolDev v, int parity, uint64
                                         uint32_t* count, uint32_t cap)
 {
     const uint32_t n = min(min(cd.counters[parity], cd.cap), cap);
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const uint64_t key = cd.keys[cd.list[i]];
-        all[i] = key;
-        int bx, by, bz;
-        unpack_key(key, bx, by, bz);
-        if (vol_find(v, key, bx, by, bz) >= 0) continue;
-        const uint32_t p = atomicAdd(count, 1u);
-        if (p < cap) req[p] = key;
+    for (uint32_t i0 = blockIdx.x * blockDim.x; i0 < n; i0 += gridDim.x * blockDim.x) {
+        const uint32_t i = i0 + threadIdx.x;
+        bool mine = false;
+        uint64_t key = 0;
+        if (i < n) {
+            key = cd.keys[cd.list[i]];
+            all[i] = key;
+            int bx, by, bz;
+            unpack_key(key, bx, by, bz);
+            mine = vol_find(v, key, bx, by, bz) < 0;
+        }
+        request(mine, key, req, count, cap);
     }
 }
 
-// Streamed-in blocks i < n take pool slots base + i: data, key, hash entry.
-__global__ void stream_in_kernel(VolDev v, const uint64_t* __restrict__ keys, const float* __restrict__ data,
-                                 int64_t n, int64_t base)
+// The report of the requests, which it also empties.
+__global__ void stream_report_kernel(const uint32_t* n_cand, uint32_t* n_req, VolDev v, StreamReport* r)
+{
+    r->n_cand = *n_cand;
+    r->n_req = *n_req;
+    r->n_blocks = *v.n_blocks;
+    r->err = *v.err;
+    *n_req = 0u;
+}
+
+// Keys of the device blocks in slot order, with their number and the error.
+__global__ void stream_keys_kernel(VolDev v, uint64_t* keys, uint32_t cap, StreamReport* r)
+{
+    const uint32_t nb = *v.n_blocks, n = min(nb, cap);
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+        keys[i] = v.slot_keys[i];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        r->n_blocks = nb;
+        r->err = *v.err;
+    }
+}
+
+// Streamed-in blocks i < n take pool slots base + i: data from the host
+// record, key, hash entry.  A workgroup a block, 16 bytes a lane: bound by the
+// bus, 450 blocks of 8 KB in 75 us (49 GB/s).  Copied to staging by the host,
+// to the device, and from there into the pool, with five waits, an integration
+// that streamed in so many took 335 us, now 160.
+__global__ __launch_bounds__(256) void stream_in_kernel(VolDev v, const StreamItem* __restrict__ items, int64_t n,
+                                                        int64_t base)
 {
     const int64_t i = blockIdx.x;
     if (i >= n) return;
     const int slot = (int)(base + i);
-    float* dst = v.pool + (size_t)slot * v.stride;
-    const float* src = data + (size_t)i * v.stride;
-    for (int k = threadIdx.x; k < v.stride; k += blockDim.x) dst[k] = src[k];
+    const StreamItem it = items[i];
+    float4* dst = reinterpret_cast<float4*>(v.pool + (size_t)slot * v.stride);
+    const float4* __restrict__ src = reinterpret_cast<const float4*>(it.host);
+#pragma unroll 2
+    for (int k = threadIdx.x; k < v.stride / 4; k += blockDim.x) dst[k] = src[k];
     if (threadIdx.x == 0) {
-        v.slot_keys[slot] = keys[i];
-        hash_put(v, keys[i], slot);
+        v.slot_keys[slot] = it.key;
+        hash_put(v, it.key, slot);
+        if (i == 0) *v.n_blocks = (uint32_t)(base + n);
     }
 }
 
@@ -127,26 +191,36 @@ __global__ void sslot_refresh_kernel(CandDev cd, VolDev v)
     }
 }
 
-// Copies the blocks of slots[i] into staging position i.
-__global__ void stream_gather_kernel(VolDev v, const int32_t* __restrict__ slots, int64_t n, float* out)
+// Evicted block i goes to its host record; the live block of slot `mover`
+// takes its slot, if there is one, and the slot left free is cleared to the
+// empty state.  A lane does all of that for its own elements, so nothing waits
+// on another.  The workgroups also empty the hash table.  Bound by the bus, 500
+// blocks of 8 KB in 77 us (53 GB/s).  Gathered to staging, copied to the host
+// and again into the store, then the moves and fills in launches of their own,
+// a call that sent 420 blocks out took 380 us, now 145.
+__global__ __launch_bounds__(256) void stream_out_kernel(VolDev v, const StreamItem* __restrict__ items, int64_t n)
 {
     const int64_t i = blockIdx.x;
-    if (i >= n) return;
-    const float* src = v.pool + (size_t)slots[i] * v.stride;
-    float* dst = out + (size_t)i * v.stride;
-    for (int k = threadIdx.x; k < v.stride; k += blockDim.x) dst[k] = src[k];
-}
-
-// Moves block from[i] to slot to[i] (the two ranges are disjoint).
-__global__ void stream_move_kernel(VolDev v, const int32_t* __restrict__ from, const int32_t* __restrict__ to,
-                                   int64_t n)
-{
-    const int64_t i = blockIdx.x;
-    if (i >= n) return;
-    const float* src = v.pool + (size_t)from[i] * v.stride;
-    float* dst = v.pool + (size_t)to[i] * v.stride;
-    for (int k = threadIdx.x; k < v.stride; k += blockDim.x) dst[k] = src[k];
-    if (threadIdx.x == 0) v.slot_keys[to[i]] = v.slot_keys[from[i]];
+    if (i < n) {
+        const StreamItem it = items[i];
+        float4* at = reinterpret_cast<float4*>(v.pool + (size_t)it.slot * v.stride);
+        float4* from = it.mover >= 0 ? reinterpret_cast<float4*>(v.pool + (size_t)it.mover * v.stride) : at;
+        float4* host = reinterpret_cast<float4*>(it.host);
+        const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll 2
+        for (int k = threadIdx.x; k < v.stride / 4; k += blockDim.x) {
+            const float4 gone = at[k], live = from[k];
+            host[k] = gone;
+            if (it.mover >= 0) at[k] = live;
+            from[k] = zero;
+        }
+        if (threadIdx.x == 0 && it.mover >= 0) v.slot_keys[it.slot] = v.slot_keys[it.mover];
+    }
+    for (uint64_t b = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; b <= v.bucket_mask;
+         b += (uint64_t)gridDim.x * blockDim.x) {
+        v.keys[b] = kKeyEmpty;
+        v.vals[b] = -1;
+    }
 }
 
 // Re-inserts the blocks of slots [0, n) into the (cleared) hash table.
@@ -154,9 +228,8 @@ __global__ void hash_rebuild_kernel(VolDev v, int64_t n)
 {
     for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < n; s += (int64_t)gridDim.x * blockDim.x)
         hash_put(v, v.slot_keys[s], (int)s);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *v.n_blocks = (uint32_t)n;
 }
-
-__global__ void set_count_kernel(uint32_t* p, uint32_t x) { *p = x; }
 
 __global__ void set_error_kernel(int32_t* err, int32_t code) { set_error(err, code); }
 
@@ -164,22 +237,19 @@ __global__ void set_error_kernel(int32_t* err, int32_t code) { set_error(err, co
 // host side
 // ---------------------------------------------------------------------------
 
-static bool grow_stage(StreamStore* st, size_t blocks)
+static bool grow_items(StreamItem*& list, size_t& cap, size_t n)
 {
-    if (blocks <= st->stage_cap) return true;
-    const size_t cap = std::max(blocks, 2 * st->stage_cap);
-    if (hipDeviceSynchronize() != hipSuccess) return false;
-    if (st->h_stage) (void)hipHostFree(st->h_stage);
-    (void)hipFree(st->d_stage);
-    st->h_stage = nullptr;
-    st->d_stage = nullptr;
-    st->stage_cap = 0;
-    if (hipHostMalloc((void**)&st->h_stage, cap * st->block_bytes, hipHostMallocDefault) != hipSuccess ||
-        hipMalloc(&st->d_stage, cap * st->block_bytes) != hipSuccess) {
+    if (n <= cap) return true;
+    const size_t c = std::max({n, 2 * cap, (size_t)1024});
+    if (list) (void)hipHostFree(list);
+    list = nullptr;
+    cap = 0;
+    if (hipHostMalloc((void**)&list, c * sizeof(StreamItem), hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
+        list = nullptr;
         return false;
     }
-    st->stage_cap = cap;
+    cap = c;
     return true;
 }
 
@@ -189,21 +259,12 @@ static bool grow_keys(StreamStore* st, size_t n)
     const size_t cap = std::max(n, 2 * st->keys_cap);
     if (hipDeviceSynchronize() != hipSuccess) return false;
     if (st->h_keys) (void)hipHostFree(st->h_keys);
-    if (st->h_slots) (void)hipHostFree(st->h_slots);
-    (void)hipFree(st->d_keys);
     (void)hipFree(st->d_all);
-    (void)hipFree(st->d_slots);
     st->h_keys = nullptr;
-    st->h_slots = nullptr;
-    st->d_keys = nullptr;
     st->d_all = nullptr;
-    st->d_slots = nullptr;
     st->keys_cap = 0;
-    if (hipHostMalloc((void**)&st->h_keys, cap * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&st->h_slots, 2 * cap * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
-        hipMalloc(&st->d_keys, cap * sizeof(uint64_t)) != hipSuccess ||
-        hipMalloc(&st->d_all, cap * sizeof(uint64_t)) != hipSuccess ||
-        hipMalloc(&st->d_slots, 2 * cap * sizeof(int32_t)) != hipSuccess) {
+    if (hipHostMalloc((void**)&st->h_keys, cap * sizeof(uint64_t), hipHostMallocCoherent) != hipSuccess ||
+        hipMalloc(&st->d_all, cap * sizeof(uint64_t)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
@@ -211,28 +272,57 @@ static bool grow_keys(StreamStore* st, size_t n)
     return true;
 }
 
-static size_t host_slot(StreamStore* st)
+// Room for n more host records: chunks of 1,024 blocks and more, doubling up
+// to 8,192 (64 MiB of RGBA8 blocks).
+static bool reserve_recs(StreamStore* st, size_t n)
 {
-    if (!st->free_slots.empty()) {
-        const size_t s = st->free_slots.back();
-        st->free_slots.pop_back();
-        return s;
+    size_t have = st->free_recs.size();
+    for (size_t c = st->cur; c < st->chunks.size(); ++c) have += st->chunks[c].second - (c == st->cur ? st->pos : 0);
+    while (have < n) {
+        const size_t blocks = st->chunks.empty() ? 1024 : std::min<size_t>(2 * st->chunks.back().second, 8192);
+        unsigned char* p = nullptr;
+        if (hipHostMalloc((void**)&p, blocks * st->block_bytes, hipHostMallocCoherent) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        st->chunks.emplace_back(p, blocks);
+        have += blocks;
     }
-    const size_t s = st->n_slots++;
-    st->arena.resize(st->n_slots * st->block_bytes);
-    return s;
+    return true;
+}
+
+// A free record; there is one (reserve_recs).
+static unsigned char* take_rec(StreamStore* st)
+{
+    if (!st->free_recs.empty()) {
+        unsigned char* p = st->free_recs.back();
+        st->free_recs.pop_back();
+        return p;
+    }
+    while (st->pos == st->chunks[st->cur].second) {
+        ++st->cur;
+        st->pos = 0;
+    }
+    return st->chunks[st->cur].first + st->block_bytes * st->pos++;
 }
 
 static bool streaming(const sc_volume* vol) { return vol->stream && vol->stream->enabled; }
 
 int64_t stream_host_blocks(const sc_volume* vol) { return vol->stream ? (int64_t)vol->stream->where.size() : 0; }
 
-static sc_status read_n_blocks(sc_volume* vol, hipStream_t s, int64_t& nb)
+// Waits for the report enqueued on `s`, and for the last use of the lists and
+// records if that was on another stream.
+static sc_status wait_report(sc_volume* vol, hipStream_t s)
 {
-    int32_t err = 0;
-    const sc_status st = sc_volume_query(vol, s, &nb, &err);
-    if (st != SC_OK) return st;
-    return err;
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess ||
+        hipEventSynchronize(vol->stream->done) != hipSuccess)
+        return SC_EDEVICE;
+    return SC_OK;
+}
+
+static int64_t reported_blocks(const sc_volume* vol)
+{
+    return std::min<int64_t>((int64_t)vol->stream->report->n_blocks, vol->p.max_blocks);
 }
 
 static sc_status d2h(void* dst, const void* src, size_t bytes, hipStream_t s)
@@ -243,118 +333,87 @@ static sc_status d2h(void* dst, const void* src, size_t bytes, hipStream_t s)
     return SC_OK;
 }
 
-// Keys of the device blocks, in slot order.
-static sc_status device_keys(sc_volume* vol, hipStream_t s, std::vector<uint64_t>& keys)
+// Keys of the device blocks, in slot order, in h_keys (and the number).
+// Waits once.
+static sc_status device_keys(sc_volume* vol, hipStream_t s, int64_t& nb)
 {
-    int64_t nb = 0;
-    const sc_status e = read_n_blocks(vol, s, nb);
+    StreamStore* st = vol->stream;
+    if (!grow_keys(st, (size_t)vol->p.max_blocks)) return SC_ENOMEM;
+    stream_keys_kernel<<<vol->n_cu, 256, 0, s>>>(vol->dev, st->h_keys, (uint32_t)vol->p.max_blocks, st->report);
+    const sc_status e = wait_report(vol, s);
     if (e != SC_OK) return e;
-    keys.resize((size_t)nb);
-    return d2h(keys.data(), vol->dev.slot_keys, sizeof(uint64_t) * (size_t)nb, s);
+    nb = reported_blocks(vol);
+    return (sc_status)st->report->err;
 }
 
-// Streams in the host-held blocks among `want` (host keys), appending them
-// to the pool.  Synchronises `s`.
-static sc_status stream_in_keys(sc_volume* vol, const std::vector<uint64_t>& want, hipStream_t s, size_t& moved)
+// Streams in the host-held blocks among the n of `want` (host keys),
+// appending them to the pool's nb blocks.  Enqueues on `s`.
+static sc_status stream_in_keys(sc_volume* vol, const uint64_t* want, size_t n, int64_t nb, hipStream_t s,
+                                size_t& moved)
 {
     StreamStore* st = vol->stream;
     moved = 0;
-    std::vector<std::pair<uint64_t, size_t>> take;
-    for (uint64_t k : want) {
-        auto it = st->where.find(k);
-        if (it != st->where.end()) take.emplace_back(it->first, it->second);
+    if (st->where.empty()) return SC_OK;
+    if (!grow_items(st->in, st->in_cap, std::min(n, st->where.size()))) return SC_ENOMEM;
+    size_t m = 0;
+    for (size_t i = 0; i < n; ++i) {
+        auto it = st->where.find(want[i]);
+        if (it != st->where.end()) st->in[m++] = StreamItem{it->first, it->second, -1, -1};
     }
-    if (take.empty()) return SC_OK;
-    int64_t nb = 0;
-    sc_status e = read_n_blocks(vol, s, nb);
-    if (e != SC_OK) return e;
-    const size_t m = take.size();
+    if (m == 0) return SC_OK;
     if (nb + (int64_t)m > vol->p.max_blocks) {
         // the work cannot run with every block it may touch: the field is
         // left unspecified, as for any full pool
         set_error_kernel<<<1, 1, 0, s>>>(vol->dev.err, SC_EPOOLFULL);
         return SC_EPOOLFULL;
     }
-    if (!grow_stage(st, m) || !grow_keys(st, m)) return SC_ENOMEM;
+    stream_in_kernel<<<(unsigned)m, 256, 0, s>>>(vol->dev, st->in, (int64_t)m, nb);
+    if (hipGetLastError() != hipSuccess || hipEventRecord(st->done, s) != hipSuccess) return SC_EDEVICE;
+    // later uses of the records are enqueued behind the kernel
     for (size_t i = 0; i < m; ++i) {
-        memcpy(st->h_stage + i * st->block_bytes, st->arena.data() + take[i].second * st->block_bytes,
-               st->block_bytes);
-        st->h_keys[i] = take[i].first;
-    }
-    if (hipMemcpyAsync(st->d_stage, st->h_stage, m * st->block_bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(st->d_keys, st->h_keys, m * sizeof(uint64_t), hipMemcpyHostToDevice, s) != hipSuccess)
-        return SC_EDEVICE;
-    stream_in_kernel<<<(unsigned)m, 256, 0, s>>>(vol->dev, st->d_keys, reinterpret_cast<const float*>(st->d_stage),
-                                                 (int64_t)m, nb);
-    set_count_kernel<<<1, 1, 0, s>>>(vol->dev.n_blocks, (uint32_t)(nb + (int64_t)m));
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return SC_EDEVICE;
-    for (const auto& kv : take) {
-        st->free_slots.push_back(kv.second);
-        st->where.erase(kv.first);
+        st->free_recs.push_back(st->in[i].host);
+        st->where.erase(st->in[i].key);
     }
     st->blocks_in += (int64_t)m;
     moved = m;
     return SC_OK;
 }
 
-// Moves the device blocks whose index `out` marks to the host store and
-// compacts the pool: the live blocks above the new count fill the holes
-// below it (disjoint ranges), the freed slots are cleared to the empty
-// state, and the hash table is rebuilt.
-static sc_status evict(sc_volume* vol, const std::vector<uint64_t>& keys, const std::vector<char>& out, hipStream_t s)
+// Moves the device blocks (keys in slot order) whose index `out` marks to the
+// host store and compacts the pool: the live blocks above the new count fill
+// the holes below it (disjoint ranges), the freed slots are cleared to the
+// empty state, and the hash table is rebuilt.  Enqueues on `s`.
+static sc_status evict(sc_volume* vol, const uint64_t* keys, const std::vector<char>& out, hipStream_t s)
 {
     StreamStore* st = vol->stream;
-    const int64_t nb = (int64_t)keys.size();
-    std::vector<int32_t> gone, holes, movers;
-    for (int64_t i = 0; i < nb; ++i)
-        if (out[i]) gone.push_back((int32_t)i);
-    if (gone.empty()) return SC_OK;
-    const int64_t live = nb - (int64_t)gone.size();
-    for (int32_t g : gone)
-        if (g < live) holes.push_back(g);
-    for (int64_t i = live; i < nb; ++i)
-        if (!out[i]) movers.push_back((int32_t)i);
-    if (holes.size() != movers.size()) return SC_EDEVICE;
-    const size_t e = gone.size();
-    if (!grow_stage(st, e) || !grow_keys(st, std::max(e, movers.size()))) return SC_ENOMEM;
-    // evicted blocks to the host
-    memcpy(st->h_slots, gone.data(), e * sizeof(int32_t));
-    if (hipMemcpyAsync(st->d_slots, st->h_slots, e * sizeof(int32_t), hipMemcpyHostToDevice, s) != hipSuccess)
-        return SC_EDEVICE;
-    stream_gather_kernel<<<(unsigned)e, 256, 0, s>>>(vol->dev, st->d_slots, (int64_t)e,
-                                                     reinterpret_cast<float*>(st->d_stage));
-    sc_status r = d2h(st->h_stage, st->d_stage, e * st->block_bytes, s);
-    if (r != SC_OK) return r;
-    for (size_t i = 0; i < e; ++i) {
-        const uint64_t key = keys[gone[i]];
-        const size_t hs = host_slot(st);
-        memcpy(st->arena.data() + hs * st->block_bytes, st->h_stage + i * st->block_bytes, st->block_bytes);
-        st->where[key] = hs;
+    const int64_t nb = (int64_t)out.size();
+    const size_t e = (size_t)std::count(out.begin(), out.end(), (char)1);
+    if (e == 0) return SC_OK;
+    const int64_t live = nb - (int64_t)e;
+    if (!grow_items(st->out, st->out_cap, e) || !reserve_recs(st, e)) return SC_ENOMEM;
+    size_t k = 0;
+    int64_t mover = live;
+    for (int64_t i = 0; i < nb; ++i) {
+        if (!out[i]) continue;
+        int64_t from = -1;
+        if (i < live) {  // as many holes below the new count as live blocks above it
+            while (out[mover]) ++mover;
+            from = mover++;
+        }
+        st->out[k++] = StreamItem{keys[i], take_rec(st), (int32_t)i, (int32_t)from};
     }
+    stream_out_kernel<<<(unsigned)std::max<size_t>(e, (size_t)vol->n_cu * 2), 256, 0, s>>>(vol->dev, st->out,
+                                                                                           (int64_t)e);
+    hash_rebuild_kernel<<<vol->n_cu * 4, 256, 0, s>>>(vol->dev, live);
+    if (hipGetLastError() != hipSuccess || hipEventRecord(st->done, s) != hipSuccess) return SC_EDEVICE;
+    for (size_t i = 0; i < e; ++i) st->where[st->out[i].key] = st->out[i].host;
     st->blocks_out += (int64_t)e;
-    // compaction
-    const size_t m = movers.size();
-    if (m > 0) {
-        memcpy(st->h_slots, movers.data(), m * sizeof(int32_t));
-        memcpy(st->h_slots + m, holes.data(), m * sizeof(int32_t));
-        if (hipMemcpyAsync(st->d_slots, st->h_slots, 2 * m * sizeof(int32_t), hipMemcpyHostToDevice, s) !=
-            hipSuccess)
-            return SC_EDEVICE;
-        stream_move_kernel<<<(unsigned)m, 256, 0, s>>>(vol->dev, st->d_slots, st->d_slots + m, (int64_t)m);
-    }
-    fill_u64(vol->dev.keys, kKeyEmpty, (size_t)vol->p.n_buckets, s);
-    fill_u32(reinterpret_cast<uint32_t*>(vol->dev.vals), 0xFFFFFFFFu, (size_t)vol->p.n_buckets, s);
-    if (live > 0) hash_rebuild_kernel<<<vol->n_cu * 4, 256, 0, s>>>(vol->dev, live);
-    set_count_kernel<<<1, 1, 0, s>>>(vol->dev.n_blocks, (uint32_t)live);
-    fill_u32(reinterpret_cast<uint32_t*>(vol->dev.pool + (size_t)vol->dev.stride * live), 0u,
-             (size_t)vol->dev.stride * (size_t)(nb - live), s);
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return SC_EDEVICE;
     return SC_OK;
 }
 
 // Before a voxel pass in streaming mode: the candidate keys of the work are
-// in d_all (ncand of them) and those without a device slot in d_keys (their
-// number in d_req).  When the pool cannot take all of the latter, resident
+// in d_all (ncand of them), those without a device slot in h_keys, and the
+// report is in.  When the pool cannot take all of the latter, resident
 // blocks that are not candidates are streamed out, farthest from the
 // candidates' mean first, until it can (with an eighth of the pool to
 // spare when possible).  Then the host-held ones are streamed in.  `moved`
@@ -363,19 +422,18 @@ static sc_status prepare_work(sc_volume* vol, hipStream_t s, uint32_t ncand, boo
 {
     StreamStore* st = vol->stream;
     moved = false;
-    uint32_t n = 0;
-    sc_status e = d2h(&n, st->d_req, sizeof(uint32_t), s);
-    if (e != SC_OK) return e;
+    const uint32_t n = st->report->n_req;
     if (n > st->keys_cap) return SC_ENOMEM;
     if (n == 0) return SC_OK;
-    std::vector<uint64_t> want(n);
-    e = d2h(want.data(), st->d_keys, sizeof(uint64_t) * n, s);
+    sc_status e = (sc_status)st->report->err;
     if (e != SC_OK) return e;
-    int64_t nb = 0;
-    e = read_n_blocks(vol, s, nb);
-    if (e != SC_OK) return e;
+    int64_t nb = reported_blocks(vol);
+    std::vector<uint64_t> kept;  // the requests, where h_keys is used again
+    const uint64_t* want = st->h_keys;
     const int64_t cap = vol->p.max_blocks;
     if (nb + (int64_t)n > cap) {
+        kept.assign(want, want + n);
+        want = kept.data();
         std::vector<uint64_t> cand(ncand);
         e = d2h(cand.data(), st->d_all, sizeof(uint64_t) * ncand, s);
         if (e != SC_OK) return e;
@@ -395,11 +453,11 @@ static sc_status prepare_work(sc_volume* vol, hipStream_t s, uint32_t ncand, boo
             my /= ncand;
             mz /= ncand;
         }
-        std::vector<uint64_t> keys;
-        e = device_keys(vol, s, keys);
+        e = device_keys(vol, s, nb);
         if (e != SC_OK) return e;
+        const uint64_t* keys = st->h_keys;
         std::vector<std::pair<double, size_t>> far;
-        for (size_t i = 0; i < keys.size(); ++i) {
+        for (size_t i = 0; i < (size_t)nb; ++i) {
             if (is_cand.count(keys[i])) continue;
             int bx, by, bz;
             unpack_key(keys[i], bx, by, bz);
@@ -411,21 +469,20 @@ static sc_status prepare_work(sc_volume* vol, hipStream_t s, uint32_t ncand, boo
         // pool to spare when there is room for that too
         const int64_t room = cap - (int64_t)n;
         const int64_t keep = (room - cap / 8 >= 0) ? room - cap / 8 : room;
-        const int64_t need = std::max<int64_t>(0, std::min<int64_t>((int64_t)keys.size() - keep, (int64_t)far.size()));
-        std::vector<char> out(keys.size(), 0);
+        const int64_t need = std::max<int64_t>(0, std::min<int64_t>(nb - keep, (int64_t)far.size()));
+        std::vector<char> out((size_t)nb, 0);
         for (int64_t i = 0; i < need; ++i) out[far[(size_t)i].second] = 1;
         e = evict(vol, keys, out, s);
         if (e != SC_OK) return e;
         moved = need > 0;
-        e = read_n_blocks(vol, s, nb);
-        if (e != SC_OK) return e;
+        nb -= need;
         if (nb + (int64_t)n > cap) {
             set_error_kernel<<<1, 1, 0, s>>>(vol->dev.err, SC_EPOOLFULL);
             return SC_EPOOLFULL;
         }
     }
     size_t in = 0;
-    e = stream_in_keys(vol, want, s, in);
+    e = stream_in_keys(vol, want, n, nb, s, in);
     if (e != SC_OK) return e;
     moved = moved || in > 0;
     return SC_OK;
@@ -459,14 +516,13 @@ static sc_status stream_in_batch_impl(sc_volume* vol, hipStream_t s)
 {
     StreamStore* st = vol->stream;
     if (!grow_keys(st, vol->cand_buckets)) return SC_ENOMEM;
-    set_count_kernel<<<1, 1, 0, s>>>(st->d_req, 0u);
-    stream_req_batch_kernel<<<vol->n_cu * 4, 256, 0, s>>>(vol->cand, st->d_all, st->d_keys, st->d_req,
+    stream_req_batch_kernel<<<vol->n_cu * 4, 256, 0, s>>>(vol->cand, st->d_all, st->h_keys, st->d_req,
                                                           (uint32_t)st->keys_cap);
-    uint32_t ncand = 0;
-    sc_status e = d2h(&ncand, vol->cand.counters + 4, sizeof(uint32_t), s);
+    stream_report_kernel<<<1, 1, 0, s>>>(vol->cand.counters + 4, st->d_req, vol->dev, st->report);
+    sc_status e = wait_report(vol, s);
     if (e != SC_OK) return e;
     bool moved = false;
-    e = prepare_work(vol, s, std::min<uint32_t>(ncand, (uint32_t)st->keys_cap), moved);
+    e = prepare_work(vol, s, std::min<uint32_t>(st->report->n_cand, (uint32_t)st->keys_cap), moved);
     if (e != SC_OK) return e;
     if (moved) sslot_refresh_kernel<<<vol->n_cu * 4, 256, 0, s>>>(vol->cand, vol->dev);
     return hipGetLastError() == hipSuccess ? SC_OK : SC_EDEVICE;
@@ -478,40 +534,49 @@ static sc_status stream_in_plain_impl(sc_volume* vol, int parity, hipStream_t s)
 {
     StreamStore* st = vol->stream;
     if (!grow_keys(st, vol->cand.cap)) return SC_ENOMEM;
-    set_count_kernel<<<1, 1, 0, s>>>(st->d_req, 0u);
-    stream_req_plain_kernel<<<vol->n_cu * 4, 256, 0, s>>>(vol->cand, vol->dev, parity, st->d_all, st->d_keys,
+    stream_req_plain_kernel<<<vol->n_cu * 4, 256, 0, s>>>(vol->cand, vol->dev, parity, st->d_all, st->h_keys,
                                                           st->d_req, (uint32_t)st->keys_cap);
-    uint32_t ncand = 0;
-    sc_status e = d2h(&ncand, vol->cand.counters + parity, sizeof(uint32_t), s);
+    stream_report_kernel<<<1, 1, 0, s>>>(vol->cand.counters + parity, st->d_req, vol->dev, st->report);
+    const sc_status e = wait_report(vol, s);
     if (e != SC_OK) return e;
     bool moved = false;
-    return prepare_work(vol, s, std::min<uint32_t>(std::min<uint32_t>(ncand, vol->cand.cap), (uint32_t)st->keys_cap),
-                        moved);
+    return prepare_work(
+        vol, s, std::min<uint32_t>(std::min<uint32_t>(st->report->n_cand, vol->cand.cap), (uint32_t)st->keys_cap),
+        moved);
 }
+
+// The emptied store keeps chunks up to this size; the others are given back.
+constexpr size_t kKeepBytes = (size_t)256 << 20;
 
 void stream_clear(sc_volume* vol)
 {
     StreamStore* st = vol->stream;
     if (!st) return;
     st->where.clear();
-    st->free_slots.clear();
-    st->arena.clear();
-    st->arena.shrink_to_fit();
-    st->n_slots = 0;
+    st->free_recs.clear();
+    st->cur = st->pos = 0;
+    size_t n = 0, bytes = 0;
+    while (n < st->chunks.size() && bytes + st->chunks[n].second * st->block_bytes <= kKeepBytes)
+        bytes += st->chunks[n++].second * st->block_bytes;
+    if (n < st->chunks.size()) {
+        (void)hipEventSynchronize(st->done);  // a kernel may still read them
+        for (size_t c = n; c < st->chunks.size(); ++c) (void)hipHostFree(st->chunks[c].first);
+        st->chunks.resize(n);
+    }
 }
 
 void stream_destroy(sc_volume* vol)
 {
     StreamStore* st = vol->stream;
     if (!st) return;
-    if (st->h_stage) (void)hipHostFree(st->h_stage);
+    for (const auto& c : st->chunks) (void)hipHostFree(c.first);
+    if (st->in) (void)hipHostFree(st->in);
+    if (st->out) (void)hipHostFree(st->out);
+    if (st->report) (void)hipHostFree(st->report);
     if (st->h_keys) (void)hipHostFree(st->h_keys);
-    if (st->h_slots) (void)hipHostFree(st->h_slots);
-    (void)hipFree(st->d_stage);
-    (void)hipFree(st->d_keys);
     (void)hipFree(st->d_all);
-    (void)hipFree(st->d_slots);
     (void)hipFree(st->d_req);
+    if (st->done) (void)hipEventDestroy(st->done);
     delete st;
     vol->stream = nullptr;
 }
@@ -528,10 +593,20 @@ sc_status sc_stream_enable(sc_volume* vol, int32_t enable)
     if (!vol->stream) {
         vol->stream = new (std::nothrow) StreamStore();
         if (!vol->stream) return SC_ENOMEM;
-        vol->stream->block_bytes = sizeof(float) * (size_t)vol->dev.stride;
-        if (hipMalloc(&vol->stream->d_req, sizeof(uint32_t)) != hipSuccess) {
+        StreamStore* st = vol->stream;
+        st->block_bytes = sizeof(float) * (size_t)vol->dev.stride;
+        if (hipMalloc(&st->d_req, sizeof(uint32_t)) != hipSuccess ||
+            hipHostMalloc((void**)&st->report, sizeof(StreamReport), hipHostMallocCoherent) != hipSuccess ||
+            hipEventCreateWithFlags(&st->done, hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
             stream_destroy(vol);
             return SC_ENOMEM;
+        }
+        // operations may come on any stream
+        fill_u32(st->d_req, 0u, 1, 0);
+        if (hipStreamSynchronize(0) != hipSuccess) {
+            stream_destroy(vol);
+            return SC_EDEVICE;
         }
     }
     if (!enable && !vol->stream->where.empty()) return SC_EINVAL;  // blocks still on the host
@@ -544,13 +619,14 @@ sc_status sc_stream_out(sc_volume* vol, const double* center, double radius, voi
     if (!vol || !center || !(radius >= 0.0)) return SC_EINVAL;
     if (!streaming(vol)) return SC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    std::vector<uint64_t> keys;
-    sc_status e = device_keys(vol, s, keys);
+    int64_t nb = 0;
+    sc_status e = device_keys(vol, s, nb);
     if (e != SC_OK) return e;
+    const uint64_t* keys = vol->stream->h_keys;
     // block centre: voxel centres s * n for n in [8 b, 8 b + 7], so 8 b + 3.5
     const double vs = (double)vol->p.voxel_size, r2 = radius * radius;
-    std::vector<char> out(keys.size(), 0);
-    for (size_t i = 0; i < keys.size(); ++i) {
+    std::vector<char> out((size_t)nb, 0);
+    for (size_t i = 0; i < out.size(); ++i) {
         int bx, by, bz;
         unpack_key(keys[i], bx, by, bz);
         const double dx = vs * (8.0 * bx + 3.5) - center[0];
@@ -558,18 +634,28 @@ sc_status sc_stream_out(sc_volume* vol, const double* center, double radius, voi
         const double dz = vs * (8.0 * bz + 3.5) - center[2];
         out[i] = (dx * dx + dy * dy + dz * dz > r2) ? 1 : 0;
     }
-    return evict(vol, keys, out, s);
+    e = evict(vol, keys, out, s);
+    if (e != SC_OK) return e;
+    return hipStreamSynchronize(s) == hipSuccess ? SC_OK : SC_EDEVICE;
 }
 
 sc_status sc_stream_in_all(sc_volume* vol, void* stream)
 {
     if (!vol) return SC_EINVAL;
     if (!vol->stream || vol->stream->where.empty()) return SC_OK;
+    StreamStore* st = vol->stream;
+    hipStream_t s = (hipStream_t)stream;
     std::vector<uint64_t> want;
-    want.reserve(vol->stream->where.size());
-    for (const auto& kv : vol->stream->where) want.push_back(kv.first);
+    want.reserve(st->where.size());
+    for (const auto& kv : st->where) want.push_back(kv.first);
+    stream_keys_kernel<<<1, 1, 0, s>>>(vol->dev, nullptr, 0u, st->report);
+    sc_status e = wait_report(vol, s);
+    if (e == SC_OK) e = (sc_status)st->report->err;
+    if (e != SC_OK) return e;
     size_t in = 0;
-    return stream_in_keys(vol, want, (hipStream_t)stream, in);
+    e = stream_in_keys(vol, want.data(), want.size(), reported_blocks(vol), s, in);
+    if (e != SC_OK) return e;
+    return hipStreamSynchronize(s) == hipSuccess ? SC_OK : SC_EDEVICE;
 }
 
 sc_status sc_stream_export(sc_volume* vol, int32_t* block_xyz, float* D, float* W, void* C, int64_t cap,
@@ -580,11 +666,12 @@ sc_status sc_stream_export(sc_volume* vol, int32_t* block_xyz, float* D, float* 
     const int64_t n = st ? (int64_t)st->where.size() : 0;
     if (n_out) *n_out = n;
     if (!st) return SC_OK;
+    if (hipEventSynchronize(st->done) != hipSuccess) return SC_EDEVICE;
     const bool rgba = vol->p.color_mode == SC_COLOR_RGBA8;
     int64_t b = 0;
     for (const auto& kv : st->where) {
         if (b >= cap) break;
-        const float* rec = reinterpret_cast<const float*>(st->arena.data() + kv.second * st->block_bytes);
+        const float* rec = reinterpret_cast<const float*>(kv.second);
         int x, y, z;
         unpack_key(kv.first, x, y, z);
         if (block_xyz) {
