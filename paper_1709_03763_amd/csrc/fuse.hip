@@ -11,16 +11,17 @@
 //   color_prep     unsharp mask C + (C - G * C), G the binomial [1 4 6 4 1]/16
 //                  kernel, exact in units of 1/256, and the re-blur measure's
 //                  integer luminance sums (exact int64 per-tile partials)
-//   blur_final     per-frame sums of the partials and w_b (inside the
-//                  depth-weight launch when fusing)
+//   blur_final     per-frame sums of the partials and w_b (inside the warp
+//                  launch when fusing)
 //   color_kernel   the keyframe depth and weight from the accumulators, then
 //                  the back-warp of each keyframe pixel into every frame,
 //                  bilinear sample of the sharpened colour, weight w_b * w_z,
 //                  per-channel lower weighted median
 //
-// A fusion is four launches: colour prep, depth weight (which also forms
-// w_b from the colour-prep partials, clears the accumulators and stores the
-// relative poses, passed to it as arguments), warp and colour.
+// A fusion is three launches: colour prep and depth weight together (which
+// also clears the accumulators and stores the relative poses, passed to it as
+// arguments), warp (which also forms w_b from the colour-prep partials) and
+// colour.
 //
 // Decisions are FP32 with the written operation order (-ffp-contract=off).
 #include <string.h>
@@ -50,17 +51,11 @@ struct PoseChunk {
     float Rb[kStageFrames][12];
 };
 
-// Work of one fusion done by the depth-weight launch, which follows the
-// colour prep and precedes the warp and colour kernels on its stream: frame
-// 0's workgroups clear the fixed-point accumulators of their tile's pixels,
-// workgroup (0, 0) stores the first `count` relative poses, and the first
-// workgroup of each frame adds up that frame's colour-prep partials into w_b.
-// Null pointers and count 0 skip it (the standalone depth weight).
+// Work of one fusion done beside the colour prep and the depth weight: frame
+// 0's depth tiles clear the fixed-point accumulators of their pixels, and the
+// first one stores the first `count` relative poses.
 struct FuseInit {
     unsigned long long* acc;  // KW then KZ, 2 x H W
-    const long long* parts;   // colour-prep partials, 4 per tile and frame
-    double* wb;               // w_b per frame
-    int32_t prep_tiles;       // colour-prep tiles per frame
     FuseFrames* fr;
     int32_t count;
     PoseChunk poses;
@@ -134,22 +129,22 @@ constexpr int kDwTW = 64, kDwTH = 16;
 constexpr int kDwLW = kDwTW + 2, kDwLH = kDwTH + 2;
 constexpr int kDwStage = (kDwLW * kDwLH + 255) / 256;  // staged pixels per thread (256 threads)
 
-__global__ __launch_bounds__(256) void depth_weight_kernel(const float* __restrict__ Z, int n, sc_intrinsics in,
-                                                           sc_fuse_params p, int tiles_x, int tiles,
-                                                           float* __restrict__ wz, const FuseInit init)
+struct DwLds {
+    float x[kDwLH][kDwLW], y[kDwLH][kDwLW], z[kDwLH][kDwLW];
+};
+
+// Tile `tile` of frame f; `acc` (or null): the accumulators that frame 0's
+// tiles clear.
+__device__ inline void depth_weight_tile(const float* __restrict__ Z, int f, int tile, const sc_intrinsics& in,
+                                         const sc_fuse_params& p, int tiles_x, float* __restrict__ wz,
+                                         unsigned long long* acc, DwLds& lds)
 {
-    __shared__ float sx[kDwLH][kDwLW], sy[kDwLH][kDwLW], sz[kDwLH][kDwLW];
+    auto& sx = lds.x;
+    auto& sy = lds.y;
+    auto& sz = lds.z;
     const int W = in.width, H = in.height;
     const int64_t np = (int64_t)W * H;
-    const int f = blockIdx.y, tile = blockIdx.x;
-    if (f >= n || tile >= tiles) return;
     const int u0 = (tile % tiles_x) * kDwTW, v0 = (tile / tiles_x) * kDwTH;
-    if (f == 0 && tile == 0) {
-        for (int i = threadIdx.x; i < init.count * 12; i += blockDim.x) {
-            init.fr->Rf[i / 12][i % 12] = init.poses.Rf[i / 12][i % 12];
-            init.fr->Rb[i / 12][i % 12] = init.poses.Rb[i / 12][i % 12];
-        }
-    }
     const float* Zf = Z + (size_t)f * np;
     // staging: every depth load of a thread issues before the divisions
     float zs[kDwStage];
@@ -203,15 +198,21 @@ __global__ __launch_bounds__(256) void depth_weight_kernel(const float* __restri
             }
         }
         wz[(size_t)f * np + (size_t)v * W + u] = out;
-        if (init.acc && f == 0) {
-            init.acc[(size_t)v * W + u] = 0ull;
-            init.acc[np + (size_t)v * W + u] = 0ull;
+        if (acc && f == 0) {
+            acc[(size_t)v * W + u] = 0ull;
+            acc[np + (size_t)v * W + u] = 0ull;
         }
     }
-    if (init.parts && tile == 0) {
-        __shared__ long long red[4][4];
-        blur_reduce(init.parts + (size_t)f * init.prep_tiles * 4, init.prep_tiles, red, init.wb + f);
-    }
+}
+
+__global__ __launch_bounds__(256) void depth_weight_kernel(const float* __restrict__ Z, int n, sc_intrinsics in,
+                                                           sc_fuse_params p, int tiles_x, int tiles,
+                                                           float* __restrict__ wz)
+{
+    __shared__ DwLds lds;
+    const int f = blockIdx.y, tile = blockIdx.x;
+    if (f >= n || tile >= tiles) return;
+    depth_weight_tile(Z, f, tile, in, p, tiles_x, wz, nullptr, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -230,15 +231,23 @@ __global__ __launch_bounds__(256) void depth_weight_kernel(const float* __restri
 // (the tile and kWpM pixels on each side); each window pixel that received
 // any then goes to the device-wide accumulators with one pair of atomics,
 // and samples that land outside the window go there directly.  The sums are
-// exact integers, so the grouping does not change them.
+// exact integers, so the grouping does not change them.  The first n
+// workgroups add up the frames' colour-prep partials instead.
 constexpr int kWpT = 16, kWpM = 8, kWpL = kWpT + 2 * kWpM;
 constexpr int kWpE = 4, kWpD = kWpE * kWpT;
 
 __global__ __launch_bounds__(256) void warp_kernel(const float* __restrict__ Z, const float* __restrict__ wz, int n,
                                                    sc_intrinsics in, float z_nom, int tiles_x,
                                                    const FuseFrames* __restrict__ fr, unsigned long long* KW,
-                                                   unsigned long long* KZ)
+                                                   unsigned long long* KZ, const long long* __restrict__ parts,
+                                                   int prep_tiles, double* wb)
 {
+    if ((int)blockIdx.x < n) {  // the frame's w_b, for the colour kernel
+        __shared__ long long red[4][4];
+        blur_reduce(parts + (size_t)blockIdx.x * prep_tiles * 4, prep_tiles, red, wb + blockIdx.x);
+        return;
+    }
+    const int tile = (int)blockIdx.x - n;
     __shared__ unsigned long long lw[kWpL * kWpL], lz[kWpL * kWpL];
     __shared__ int2 shift[kMaxFrames];
     const int W = in.width, H = in.height;
@@ -267,7 +276,7 @@ __global__ __launch_bounds__(256) void warp_kernel(const float* __restrict__ Z, 
         shift[threadIdx.x] = d;
     }
     __syncthreads();
-    const int ku = ((int)blockIdx.x % tiles_x - kWpE) * kWpT, kv = ((int)blockIdx.x / tiles_x - kWpE) * kWpT;
+    const int ku = (tile % tiles_x - kWpE) * kWpT, kv = (tile / tiles_x - kWpE) * kWpT;
     const int wx0 = ku - kWpM, wy0 = kv - kWpM;
     const int tx = (int)threadIdx.x & (kWpT - 1), ty = (int)threadIdx.x / kWpT;
     // frames in groups of kWpF: every load of a group issues before its samples are warped
@@ -353,19 +362,24 @@ constexpr int kPrepLW = kPrepTW + 9, kPrepLH = kPrepTH + 9;
 constexpr int kPrepHalo = 5;
 constexpr int kPrepStage = (kPrepLW * kPrepLH + 255) / 256;  // staged pixels per thread (256 threads)
 
+struct PrepLds {
+    uint64_t pix[kPrepLH][kPrepLW];
+    uint64_t hsum[kPrepTH + 4][kPrepTW];  // horizontal binomial of staged rows 3 .. 22
+    uint8_t lum[kPrepLH][kPrepLW];  // luma <= 255; bytes keep the workgroup under 26.7 KB of LDS (six per CU)
+    long long red[4][4];
+};
+
 // kOutCh: 3 (packed RGB, the standalone output) or 4 (RGB and a zero, one
 // 8-byte store per pixel; the layout the colour kernel gathers from).
 template <int kOutCh>
-__global__ __launch_bounds__(256) void color_prep_kernel(const uint8_t* __restrict__ rgb, int n, int W, int H,
-                                                         int tiles_x, int tiles, uint16_t* __restrict__ out,
-                                                         long long* __restrict__ parts)
+__device__ inline void color_prep_tile(const uint8_t* __restrict__ rgb, int f, int tile, int W, int H, int tiles_x,
+                                       int tiles, uint16_t* __restrict__ out, long long* __restrict__ parts,
+                                       PrepLds& lds)
 {
-    __shared__ uint64_t pix[kPrepLH][kPrepLW];
-    __shared__ uint64_t hsum[kPrepTH + 4][kPrepTW];  // horizontal binomial of staged rows 3 .. 22
-    __shared__ uint8_t lum[kPrepLH][kPrepLW];  // luma <= 255; bytes keep the workgroup under 26.7 KB of LDS (six per CU)
-    __shared__ long long red[4][4];
-    const int f = blockIdx.y, tile = blockIdx.x;
-    if (f >= n || tile >= tiles) return;
+    auto& pix = lds.pix;
+    auto& hsum = lds.hsum;
+    auto& lum = lds.lum;
+    auto& red = lds.red;
     const int u0 = (tile % tiles_x) * kPrepTW, v0 = (tile / tiles_x) * kPrepTH;
     const int64_t np = (int64_t)W * H;
     const uint8_t* C = rgb + (size_t)f * np * 3;
@@ -453,6 +467,46 @@ __global__ __launch_bounds__(256) void color_prep_kernel(const uint8_t* __restri
     }
 }
 
+__global__ __launch_bounds__(256) void color_prep_kernel(const uint8_t* __restrict__ rgb, int n, int W, int H,
+                                                         int tiles_x, int tiles, uint16_t* __restrict__ out,
+                                                         long long* __restrict__ parts)
+{
+    __shared__ PrepLds lds;
+    const int f = blockIdx.y, tile = blockIdx.x;
+    if (f >= n || tile >= tiles) return;
+    color_prep_tile<3>(rgb, f, tile, W, H, tiles_x, tiles, out, parts, lds);
+}
+
+// A fusion's colour prep (four channels) and depth weight in one launch: of a
+// frame's workgroups the first prep_tiles take the colour tiles, the others
+// the depth tiles.  Neither needs the other, and each alone waits for its loads with the
+// CUs half empty at its end: 640x480, 5 frames 16.2 + 11.5 us in two launches,
+// now 22 in one; 60 frames 104 + 72 us, now 172.
+__global__ __launch_bounds__(256) void fuse_front_kernel(const uint8_t* __restrict__ rgb, const float* __restrict__ Z,
+                                                         sc_intrinsics in, sc_fuse_params p, int prep_x,
+                                                         int prep_tiles, int dw_x,
+                                                         uint16_t* __restrict__ cs, long long* __restrict__ parts,
+                                                         float* __restrict__ wz, const FuseInit init)
+{
+    __shared__ union {
+        PrepLds prep;
+        DwLds dw;
+    } lds;
+    const int f = blockIdx.y;
+    if ((int)blockIdx.x < prep_tiles) {
+        color_prep_tile<4>(rgb, f, blockIdx.x, in.width, in.height, prep_x, prep_tiles, cs, parts, lds.prep);
+        return;
+    }
+    const int tile = (int)blockIdx.x - prep_tiles;
+    if (f == 0 && tile == 0) {
+        for (int i = threadIdx.x; i < init.count * 12; i += blockDim.x) {
+            init.fr->Rf[i / 12][i % 12] = init.poses.Rf[i / 12][i % 12];
+            init.fr->Rb[i / 12][i % 12] = init.poses.Rb[i / 12][i % 12];
+        }
+    }
+    depth_weight_tile(Z, f, tile, in, p, dw_x, wz, init.acc, lds.dw);
+}
+
 // One workgroup per frame (standalone colour pre-processing).
 __global__ __launch_bounds__(256) void blur_final_kernel(const long long* __restrict__ parts, int n, int tiles,
                                                          double* wb)
@@ -474,151 +528,84 @@ __global__ __launch_bounds__(256) void blur_final_kernel(const long long* __rest
 // the 2^-20 grid, and the median the smallest value up to which the weights
 // reach half their total.
 //
-// A workgroup takes 64 consecutive keyframe pixels, one a lane, and its
-// wavefronts the frames in turn: a wavefront's lanes read neighbouring pixels
-// of one frame, and the frame's pose is uniform.  Every wavefront forms its
-// pixels' depth from the fixed-point accumulators (W* = sum(w), Z* =
-// sum(w z) / sum(w), rounded once to FP32) and back-warps them; the
-// observations go to LDS by frame.  Then a wavefront takes a channel, a lane
-// its pixel: up to eight frames every observation's sum of weights at or below
-// it (N = the number of frames, all in registers), more of them a bisection
-// of the 256 values (N = 0).
-// Bound: the gathers' latency for a few frames, the vector ALU for many
-// (eight sums of n weights a channel).  One thread a (pixel, frame), its
-// frame's neighbours in other workgroups and n comparisons of (value, frame)
-// each with 64-bit sums: 640x480, 5 frames 20.4 us, 60 frames 611 us, now
-// 17.3 us and 136 us.
-constexpr int kColorWaves = 4;
+// Up to eight frames (N = their number) a wavefront takes 64 consecutive
+// keyframe pixels through everything, a lane a pixel: its depth from the
+// fixed-point accumulators (W* = sum(w), Z* = sum(w z) / sum(w), rounded once
+// to FP32), the back-warp into each frame, whose lanes read neighbouring
+// pixels, and the median from the observations' sums of weights at or below
+// each, all in registers.  With more frames the eight wavefronts of a
+// workgroup share the 64 pixels: each takes every eighth frame, the
+// observations meet in LDS by frame, and a wavefront takes a channel's median
+// by a bisection of the 256 values.
+// Bound: the vector ALU (about 150 instructions a pixel and frame).  One thread
+// a (pixel, frame), its frame's neighbours in other workgroups and n
+// comparisons of (value, frame) each with 64-bit sums: 640x480, 5 frames 20.4
+// us, 60 frames 611 us, now 14 and 132 us (5 frames through LDS, every
+// wavefront forming the depths: 17.3).
+constexpr int kColorWaves = 8;
 
-// Sum of the weights of the observations of channel `sh` with value at most
-// `mid`.
-template <class T>
-__device__ inline T weight_upto(const uint2* obs, int n, int lane, int sh, uint32_t mid)
+// Keyframe pixel idx: its point (and Z*) and W*; W* = 0 without depth.
+__device__ inline float color_point(const unsigned long long* __restrict__ KW,
+                                    const unsigned long long* __restrict__ KZ, int idx, const sc_intrinsics& in,
+                                    float P[3])
 {
-    T s = 0;
-#pragma unroll 4
-    for (int l = 0; l < n; ++l) {
-        const uint2 o = obs[l * 64 + lane];
-        s += ((o.x >> sh) & 255u) <= mid ? o.y : 0u;
-    }
-    return s;
-}
-
-// The same sums in T (32 bits where twice the total fits).
-template <int N, class T>
-__device__ inline uint32_t lower_median(const uint2* obs, int n, int lane, int sh, T total)
-{
-    if (N > 0) {
-        uint2 o[N > 0 ? N : 1];
-#pragma unroll
-        for (int l = 0; l < N; ++l) {
-            o[l] = obs[l * 64 + lane];
-            o[l].x = (o[l].x >> sh) & 255u;
-        }
-        uint32_t best = 255u;
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            T s = 0;
-#pragma unroll
-            for (int l = 0; l < N; ++l) s += o[l].x <= o[i].x ? o[l].y : 0u;
-            if (2 * s >= total) best = min(best, o[i].x);
-        }
-        return best;
-    }
-    uint32_t lo = 0u, hi = 255u;
-#pragma unroll 1
-    for (int step = 0; step < 8; ++step) {
-        const uint32_t mid = (lo + hi) >> 1;
-        const bool up = 2 * weight_upto<T>(obs, n, lane, sh, mid) >= total;
-        hi = up ? mid : hi;
-        lo = up ? lo : mid + 1u;
-    }
-    return hi;
-}
-
-template <int N>
-__global__ __launch_bounds__(64 * kColorWaves) void color_kernel(const float* __restrict__ Z,
-                                                                 const float* __restrict__ wz,
-                                                                 const uint16_t* __restrict__ cs,
-                                                                 const double* __restrict__ wb, int n_frames,
-                                                                 sc_intrinsics in, float occ_rel,
-                                                                 const FuseFrames* __restrict__ fr,
-                                                                 const unsigned long long* __restrict__ KW,
-                                                                 const unsigned long long* __restrict__ KZ, float* Zs,
-                                                                 float* Ws, uint8_t* rgba)
-{
-    extern __shared__ uint2 obs[];  // [frame][pixel]: 8-bit channels, weight (0: no observation)
-    __shared__ uint8_t med[3][64];
-    const int n = N ? N : n_frames;
-    const int W = in.width, H = in.height;
+    P[0] = P[1] = P[2] = 0.0f;
     // np <= 16384^2 < 2^31: pixel indices and their division in 32 bits
-    const int np = W * H;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), waves = (int)blockDim.x >> 6;
-    const int idx = (int)blockIdx.x * 64 + lane;
-    float P[3] = {0.0f, 0.0f, 0.0f}, kw_out = 0.0f;
-    const long long kw = idx < np ? (long long)KW[idx] : 0ll;
-    if (kw > 0) {
-        const int v = idx / W, u = idx - v * W;
-        const float zk = (float)(((double)(long long)KZ[idx] / (double)kw) * 0x1p-20);
-        backproject((float)u, (float)v, zk, in, P);
-        kw_out = (float)((double)kw / 1024.0);
-    }
-    for (int i = wave; i < n; i += waves) {
-        uint2 o = make_uint2(0u, 0u);
-        float q[3], uf, vf;
-        int iu, iv;
-        xform(fr->Rb[i], P, q);
-        if (kw_out > 0.0f && project(in, q, uf, vf, iu, iv)) {
-            const float x0 = floorf(uf), y0 = floorf(vf);
-            if (x0 >= 0.0f && x0 + 1.0f <= (float)(W - 1) && y0 >= 0.0f && y0 + 1.0f <= (float)(H - 1)) {
-                const size_t base = (size_t)i * np;
-                const float wzi = wz[base + (size_t)iv * W + iu];
-                const float zi = Z[base + (size_t)iv * W + iu];
-                const float ax = uf - x0, ay = vf - y0;
-                const int ix = (int)x0, iy = (int)y0;
-                // four channels of 16 bits per pixel, 8-byte aligned
-                const uint2* C0 = reinterpret_cast<const uint2*>(cs) + base + (size_t)iy * W + ix;
-                const uint2* C1 = C0 + W;
-                const uint2 p00 = C0[0], p10 = C0[1], p01 = C1[0], p11 = C1[1];
-                const float wcs = rintf(((float)wb[i] * wzi) * 1048576.0f);
-                if (wzi > 0.0f && fabsf(zi - q[2]) <= occ_rel * q[2] && wcs > 0.0f) {
-                    auto ch = [](uint2 p, int k) {
-                        return (float)(k == 0 ? (p.x & 0xFFFFu) : k == 1 ? (p.x >> 16) : (p.y & 0xFFFFu));
-                    };
+    const long long kw = idx < in.width * in.height ? (long long)KW[idx] : 0ll;
+    if (kw <= 0) return 0.0f;
+    const int v = idx / in.width, u = idx - v * in.width;
+    const float zk = (float)(((double)(long long)KZ[idx] / (double)kw) * 0x1p-20);
+    backproject((float)u, (float)v, zk, in, P);
+    return (float)((double)kw / 1024.0);
+}
+
+// Frame i's observation of point P: 8-bit channels and weight (0: none).
+__device__ inline uint2 color_observe(const float* __restrict__ Z, const float* __restrict__ wz,
+                                      const uint16_t* __restrict__ cs, const double* __restrict__ wb, int i,
+                                      const sc_intrinsics& in, float occ_rel, const FuseFrames* __restrict__ fr,
+                                      bool live, const float P[3])
+{
+    const int W = in.width, H = in.height;
+    uint2 o = make_uint2(0u, 0u);
+    float q[3], uf, vf;
+    int iu, iv;
+    xform(fr->Rb[i], P, q);
+    if (!live || !project(in, q, uf, vf, iu, iv)) return o;
+    const float x0 = floorf(uf), y0 = floorf(vf);
+    if (!(x0 >= 0.0f && x0 + 1.0f <= (float)(W - 1) && y0 >= 0.0f && y0 + 1.0f <= (float)(H - 1))) return o;
+    const size_t base = (size_t)i * (W * H);
+    const float wzi = wz[base + (size_t)iv * W + iu];
+    const float zi = Z[base + (size_t)iv * W + iu];
+    const float ax = uf - x0, ay = vf - y0;
+    const int ix = (int)x0, iy = (int)y0;
+    // four channels of 16 bits per pixel, 8-byte aligned
+    const uint2* C0 = reinterpret_cast<const uint2*>(cs) + base + (size_t)iy * W + ix;
+    const uint2* C1 = C0 + W;
+    const uint2 p00 = C0[0], p10 = C0[1], p01 = C1[0], p11 = C1[1];
+    const float wcs = rintf(((float)wb[i] * wzi) * 1048576.0f);
+    if (!(wzi > 0.0f && fabsf(zi - q[2]) <= occ_rel * q[2] && wcs > 0.0f)) return o;
+    auto ch = [](uint2 p, int k) {
+        return (float)(k == 0 ? (p.x & 0xFFFFu) : k == 1 ? (p.x >> 16) : (p.y & 0xFFFFu));
+    };
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        const float c00 = ch(p00, k), c10 = ch(p10, k);
-                        const float c01 = ch(p01, k), c11 = ch(p11, k);
-                        const float top = c00 + ax * (c10 - c00);
-                        const float bot = c01 + ax * (c11 - c01);
-                        const float val = rintf((top + ay * (bot - top)) / 256.0f);
-                        o.x |= (uint32_t)fminf(fmaxf(val, 0.0f), 255.0f) << (8 * k);
-                    }
-                    o.y = (uint32_t)wcs;
-                }
-            }
-        }
-        obs[i * 64 + lane] = o;
+    for (int k = 0; k < 3; ++k) {
+        const float c00 = ch(p00, k), c10 = ch(p10, k);
+        const float c01 = ch(p01, k), c11 = ch(p11, k);
+        const float top = c00 + ax * (c10 - c00);
+        const float bot = c01 + ax * (c11 - c01);
+        const float val = rintf((top + ay * (bot - top)) / 256.0f);
+        o.x |= (uint32_t)fminf(fmaxf(val, 0.0f), 255.0f) << (8 * k);
     }
-    __syncthreads();
-    for (int k = wave; k < 3; k += waves) {
-        uint64_t total = 0;
-        for (int l = 0; l < n; ++l) total += obs[l * 64 + lane].y;
-        // the total bounds every sum
-        med[k][lane] = (uint8_t)(__ballot(total >= (1ull << 31)) == 0ull
-                                     ? lower_median<N, uint32_t>(obs, n, lane, 8 * k, (uint32_t)total)
-                                     : lower_median<N, uint64_t>(obs, n, lane, 8 * k, total));
-    }
-    __syncthreads();
-    if (wave != 0 || idx >= np) return;
-    bool any = false;  // some frame observed the pixel
-    for (int l = 0; l < n; ++l) any = any || obs[l * 64 + lane].y != 0u;
-    Ws[idx] = any ? kw_out : 0.0f;
-    Zs[idx] = any ? P[2] : 0.0f;
-    const uint32_t c =
-        any ? (uint32_t)med[0][lane] | ((uint32_t)med[1][lane] << 8) | ((uint32_t)med[2][lane] << 16) | 0xFF000000u
-            : 0u;
+    o.y = (uint32_t)wcs;
+    return o;
+}
+
+__device__ inline void color_store(int idx, bool any, float w, float z, uint32_t rgb, float* Zs, float* Ws,
+                                   uint8_t* rgba)
+{
+    Ws[idx] = any ? w : 0.0f;
+    Zs[idx] = any ? z : 0.0f;
+    const uint32_t c = any ? rgb | 0xFF000000u : 0u;
     if (((uintptr_t)rgba & 3u) == 0u) {
         reinterpret_cast<uint32_t*>(rgba)[idx] = c;
     } else {
@@ -626,14 +613,101 @@ __global__ __launch_bounds__(64 * kColorWaves) void color_kernel(const float* __
     }
 }
 
-template <int N>
-static void launch_color_n(int grid, int n, hipStream_t s, const float* Z, const float* wz, const uint16_t* cs,
-                           const double* wb, const sc_intrinsics& in, float occ_rel, const FuseFrames* fr,
-                           const unsigned long long* acc, float* Zs, float* Ws, uint8_t* rgba)
+// Channel `sh` of N observations, its sums in T.
+template <int N, class T>
+__device__ inline uint32_t median_regs(const uint2 (&o)[N], int sh, T total)
 {
-    const int waves = std::min(n, kColorWaves);
-    color_kernel<N><<<grid, 64 * waves, sizeof(uint2) * 64 * (size_t)n, s>>>(
-        Z, wz, cs, wb, n, in, occ_rel, fr, acc, acc + (size_t)in.width * in.height, Zs, Ws, rgba);
+    uint32_t best = 255u;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint32_t v = (o[i].x >> sh) & 255u;
+        T s = 0;
+#pragma unroll
+        for (int l = 0; l < N; ++l) s += ((o[l].x >> sh) & 255u) <= v ? o[l].y : 0u;
+        if (2 * s >= total) best = min(best, v);
+    }
+    return best;
+}
+
+template <int N>
+__global__ __launch_bounds__(256) void color_kernel(const float* __restrict__ Z, const float* __restrict__ wz,
+                                                    const uint16_t* __restrict__ cs, const double* __restrict__ wb,
+                                                    sc_intrinsics in, float occ_rel,
+                                                    const FuseFrames* __restrict__ fr,
+                                                    const unsigned long long* __restrict__ KW,
+                                                    const unsigned long long* __restrict__ KZ, float* Zs, float* Ws,
+                                                    uint8_t* rgba)
+{
+    const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
+    float P[3];
+    const float w = color_point(KW, KZ, idx, in, P);
+    uint2 o[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = color_observe(Z, wz, cs, wb, i, in, occ_rel, fr, w > 0.0f, P);
+    uint64_t total = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) total += o[i].y;
+    // the total bounds every sum: in 32 bits where twice it fits
+    uint32_t rgb = 0u;
+    const bool small = __ballot(total >= (1ull << 31)) == 0ull;
+#pragma unroll
+    for (int sh = 0; sh < 24; sh += 8)
+        rgb |= (small ? median_regs<N, uint32_t>(o, sh, (uint32_t)total) : median_regs<N, uint64_t>(o, sh, total))
+               << sh;
+    if (idx < in.width * in.height) color_store(idx, total != 0, w, P[2], rgb, Zs, Ws, rgba);
+}
+
+// Channel `sh` of the n observations in LDS, its sums in T.
+template <class T>
+__device__ inline uint32_t median_lds(const uint2* obs, int n, int lane, int sh, T total)
+{
+    uint32_t lo = 0u, hi = 255u;
+#pragma unroll 1
+    for (int step = 0; step < 8; ++step) {
+        const uint32_t mid = (lo + hi) >> 1;
+        T s = 0;
+#pragma unroll 4
+        for (int l = 0; l < n; ++l) {
+            const uint2 o = obs[l * 64 + lane];
+            s += ((o.x >> sh) & 255u) <= mid ? o.y : 0u;
+        }
+        const bool up = 2 * s >= total;
+        hi = up ? mid : hi;
+        lo = up ? lo : mid + 1u;
+    }
+    return hi;
+}
+
+__global__ __launch_bounds__(64 * kColorWaves) void color_many_kernel(
+    const float* __restrict__ Z, const float* __restrict__ wz, const uint16_t* __restrict__ cs,
+    const double* __restrict__ wb, int n, sc_intrinsics in, float occ_rel, const FuseFrames* __restrict__ fr,
+    const unsigned long long* __restrict__ KW, const unsigned long long* __restrict__ KZ, float* Zs, float* Ws,
+    uint8_t* rgba)
+{
+    extern __shared__ uint2 obs[];  // [frame][pixel]
+    __shared__ uint8_t med[3][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int idx = (int)blockIdx.x * 64 + lane;
+    float P[3];
+    const float w = color_point(KW, KZ, idx, in, P);
+    for (int i = wave; i < n; i += kColorWaves)
+        obs[i * 64 + lane] = color_observe(Z, wz, cs, wb, i, in, occ_rel, fr, w > 0.0f, P);
+    __syncthreads();
+    if (wave < 3) {
+        uint64_t total = 0;
+        for (int l = 0; l < n; ++l) total += obs[l * 64 + lane].y;
+        med[wave][lane] =
+            (uint8_t)(__ballot(total >= (1ull << 31)) == 0ull
+                          ? median_lds<uint32_t>(obs, n, lane, 8 * wave, (uint32_t)total)
+                          : median_lds<uint64_t>(obs, n, lane, 8 * wave, total));
+    }
+    __syncthreads();
+    if (wave != 0 || idx >= in.width * in.height) return;
+    bool any = false;  // some frame observed the pixel
+    for (int l = 0; l < n; ++l) any = any || obs[l * 64 + lane].y != 0u;
+    color_store(idx, any, w, P[2],
+                (uint32_t)med[0][lane] | ((uint32_t)med[1][lane] << 8) | ((uint32_t)med[2][lane] << 16), Zs, Ws, rgba);
 }
 
 // ---------------------------------------------------------------------------
@@ -798,29 +872,8 @@ static void rel_pose(const sc_pose& A, const sc_pose& B, float out[12])
     }
 }
 
-static void launch_depth_weight(const float* depth, int n, const sc_intrinsics& in, const sc_fuse_params& p, float* out,
-                                const FuseInit& init, hipStream_t s)
-{
-    const int tiles_x = (in.width + kDwTW - 1) / kDwTW;
-    const int tiles = tiles_x * ((in.height + kDwTH - 1) / kDwTH);
-    depth_weight_kernel<<<dim3((unsigned)tiles, (unsigned)n), 256, 0, s>>>(depth, n, in, p, tiles_x, tiles, out, init);
-}
-
-// wb null: the partials only, sharpened colour with four channels per pixel
-// (a fusion forms w_b in its depth-weight launch); else three channels and
-// w_b.
-static void launch_color_prep(const uint8_t* rgb, int n, int W, int H, uint16_t* sharp, long long* parts, double* wb,
-                              hipStream_t s)
-{
-    const int tiles = prep_tiles(W, H);
-    const dim3 grid((unsigned)tiles, (unsigned)n);
-    if (wb) {
-        color_prep_kernel<3><<<grid, 256, 0, s>>>(rgb, n, W, H, prep_tiles_x(W), tiles, sharp, parts);
-        blur_final_kernel<<<n, 256, 0, s>>>(parts, n, tiles, wb);
-    } else {
-        color_prep_kernel<4><<<grid, 256, 0, s>>>(rgb, n, W, H, prep_tiles_x(W), tiles, sharp, parts);
-    }
-}
+static int dw_tiles_x(int W) { return (W + kDwTW - 1) / kDwTW; }
+static int dw_tiles(int W, int H) { return dw_tiles_x(W) * ((H + kDwTH - 1) / kDwTH); }
 
 // Relative poses of frames first .. first + count - 1 into the device table.
 __global__ void stage_poses_kernel(PoseChunk c, int first, int count, FuseFrames* fr)
@@ -843,7 +896,7 @@ struct FuseBufs {
 };
 
 // The fusion kernels of one keyframe.  The relative poses of the first
-// kStageFrames frames travel in the depth-weight launch; those of later
+// kStageFrames frames travel in the first launch; those of later
 // frames are stored by stage_poses_kernel launches enqueued first.
 static void launch_fuse(const FuseBufs& b, const float* depth, const uint8_t* rgb, const sc_pose* poses, int n_frames,
                         int ref, const sc_intrinsics& in, const sc_fuse_params& params, float* kf_depth,
@@ -852,9 +905,6 @@ static void launch_fuse(const FuseBufs& b, const float* depth, const uint8_t* rg
     const int64_t np = (int64_t)in.width * in.height;
     FuseInit init;
     init.acc = b.acc;
-    init.parts = b.parts;
-    init.wb = b.wb;
-    init.prep_tiles = prep_tiles(in.width, in.height);
     init.fr = b.fr;
     for (int i0 = kStageFrames; i0 < n_frames; i0 += kStageFrames) {
         const int cnt = std::min(kStageFrames, n_frames - i0);
@@ -869,17 +919,18 @@ static void launch_fuse(const FuseBufs& b, const float* depth, const uint8_t* rg
         rel_pose(poses[ref], poses[j], init.poses.Rf[j]);
         rel_pose(poses[j], poses[ref], init.poses.Rb[j]);
     }
-    launch_color_prep(rgb, n_frames, in.width, in.height, b.cs, b.parts, nullptr, s);
-    launch_depth_weight(depth, n_frames, in, params, b.wz, init, s);
+    const int pt = prep_tiles(in.width, in.height), dt = dw_tiles(in.width, in.height);
+    fuse_front_kernel<<<dim3((unsigned)(pt + dt), (unsigned)n_frames), 256, 0, s>>>(
+        rgb, depth, in, params, prep_tiles_x(in.width), pt, dw_tiles_x(in.width), b.cs, b.parts, b.wz, init);
     // target tiles over the image and kWpE more on each side
     const int wtx = (in.width + kWpT - 1) / kWpT + 2 * kWpE, wty = (in.height + kWpT - 1) / kWpT + 2 * kWpE;
     const float z_nom = 0.5f * (params.z_min + params.z_max);
-    warp_kernel<<<(unsigned)(wtx * wty), 256, 0, s>>>(depth, b.wz, n_frames, in, z_nom, wtx, b.fr, b.acc,
-                                                       b.acc + np);
-    const int grid = (int)((np + 63) / 64);
+    warp_kernel<<<(unsigned)(n_frames + wtx * wty), 256, 0, s>>>(depth, b.wz, n_frames, in, z_nom, wtx, b.fr, b.acc,
+                                                                 b.acc + np, b.parts, pt, b.wb);
+    const unsigned long long *KW = b.acc, *KZ = b.acc + np;
     auto color = [&](auto n) {
-        launch_color_n<decltype(n)::value>(grid, n_frames, s, depth, b.wz, b.cs, b.wb, in, params.occ_rel, b.fr, b.acc,
-                                           kf_depth, kf_weight, kf_rgba);
+        color_kernel<decltype(n)::value><<<(unsigned)((np + 255) / 256), 256, 0, s>>>(
+            depth, b.wz, b.cs, b.wb, in, params.occ_rel, b.fr, KW, KZ, kf_depth, kf_weight, kf_rgba);
     };
     switch (n_frames) {
     case 1: color(std::integral_constant<int, 1>{}); break;
@@ -890,7 +941,9 @@ static void launch_fuse(const FuseBufs& b, const float* depth, const uint8_t* rg
     case 6: color(std::integral_constant<int, 6>{}); break;
     case 7: color(std::integral_constant<int, 7>{}); break;
     case 8: color(std::integral_constant<int, 8>{}); break;
-    default: color(std::integral_constant<int, 0>{});
+    default:
+        color_many_kernel<<<(unsigned)((np + 63) / 64), 64 * kColorWaves, sizeof(uint2) * 64 * (size_t)n_frames, s>>>(
+            depth, b.wz, b.cs, b.wb, n_frames, in, params.occ_rel, b.fr, KW, KZ, kf_depth, kf_weight, kf_rgba);
     }
 }
 
@@ -957,7 +1010,9 @@ sc_status sc_depth_weight(const float* depth, int32_t n_frames, const sc_intrins
                           float* wz_out, void* stream)
 {
     if (!depth || !wz_out || n_frames <= 0 || n_frames > 65535 || !intr_valid(intr) || !params) return SC_EINVAL;
-    launch_depth_weight(depth, n_frames, *intr, *params, wz_out, FuseInit{}, (hipStream_t)stream);
+    const int tiles = dw_tiles(intr->width, intr->height);
+    depth_weight_kernel<<<dim3((unsigned)tiles, (unsigned)n_frames), 256, 0, (hipStream_t)stream>>>(
+        depth, n_frames, *intr, *params, dw_tiles_x(intr->width), tiles, wz_out);
     return hipGetLastError() == hipSuccess ? SC_OK : SC_EDEVICE;
 }
 
@@ -971,7 +1026,10 @@ sc_status sc_color_prep(const uint8_t* rgb, int32_t n_frames, int32_t width, int
     const sc_status st =
         ws_reserve((size_t)width * height, (size_t)n_frames, 4 * (size_t)prep_tiles(width, height) * n_frames);
     if (st != SC_OK) return st;
-    launch_color_prep(rgb, n_frames, width, height, sharp_out, g_ws.parts, wb_out, (hipStream_t)stream);
+    const int tiles = prep_tiles(width, height);
+    color_prep_kernel<<<dim3((unsigned)tiles, (unsigned)n_frames), 256, 0, (hipStream_t)stream>>>(
+        rgb, n_frames, width, height, prep_tiles_x(width), tiles, sharp_out, g_ws.parts);
+    blur_final_kernel<<<n_frames, 256, 0, (hipStream_t)stream>>>(g_ws.parts, n_frames, tiles, wb_out);
     return hipGetLastError() == hipSuccess ? SC_OK : SC_EDEVICE;
 }
 
