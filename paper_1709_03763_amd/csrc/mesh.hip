@@ -700,9 +700,10 @@ __global__ __launch_bounds__(256) void nn_scatter_kernel(const float* __restrict
 }
 
 // The 27 cells, the query's own first, then those sharing a face, an edge, a
-// corner: (dx + 1) | (dy + 1) << 2 | (dz + 1) << 4.
+// corner: d + 1 along each axis, two bits a cell, and the cells with each d.
 struct NnOrder {
-    uint8_t v[27];
+    uint64_t d[3];
+    uint32_t mask[3][3];
 };
 constexpr NnOrder nn_order()
 {
@@ -712,30 +713,72 @@ constexpr NnOrder nn_order()
         for (int z = 0; z < 3; ++z)
             for (int y = 0; y < 3; ++y)
                 for (int x = 0; x < 3; ++x)
-                    if ((x != 1) + (y != 1) + (z != 1) == away) o.v[n++] = (uint8_t)(x | (y << 2) | (z << 4));
+                    if ((x != 1) + (y != 1) + (z != 1) == away) {
+                        o.d[0] |= (uint64_t)x << (2 * n);
+                        o.d[1] |= (uint64_t)y << (2 * n);
+                        o.d[2] |= (uint64_t)z << (2 * n);
+                        o.mask[0][x] |= 1u << n;
+                        o.mask[1][y] |= 1u << n;
+                        o.mask[2][z] |= 1u << n;
+                        ++n;
+                    }
     return o;
 }
-static __device__ constexpr NnOrder kNnOrder = nn_order();
+constexpr NnOrder kNnOrder = nn_order();
 
-// One thread per query.  The query's own cell comes first; another cell is
-// looked up only when its box is nearer than the best distance so far (and
-// the radius), which leaves one or two of the 27 for a query near the
-// surface.  The box distance is taken low by 2^-21 of the coordinate and the
-// edge, more than the roundings of the cell coordinate and of the products
-// here, so that a cell holding a nearer point is never left out and the
-// minimum is that over all 27 cells.  Bound: the latency of the probes and of
-// the points' loads, 64 addresses each (1.0 M random queries against 2.0 M
-// vertices, radius five voxels: 2036 us with every cell read, in three 4-byte
-// loads a point, 381 us so; a call with its grid 2.6 -> 0.5 ms).
+// Points of cell (cx, cy, cz): [a, e).
+__device__ inline void nn_range(const NnGrid& g, int cx, int cy, int cz, uint32_t& a, uint32_t& e)
+{
+    const uint64_t key = pack_key(cx, cy, cz);
+    uint32_t h = hash_block(cx, cy, cz) & g.mask;
+    a = e = 0u;
+    for (uint32_t probe = 0; probe <= g.mask; ++probe) {
+        const uint4 w = reinterpret_cast<const uint4*>(g.cells)[h];
+        const uint64_t k = ((uint64_t)w.y << 32) | w.x;
+        if (k == key) {
+            a = w.z;
+            e = w.z + w.w;
+        }
+        if (k == key || k == kKeyEmpty) break;
+        h = (h + 1) & g.mask;
+    }
+}
+
+// kNnLanes lanes per query, which take a cell's points in turn.  The query's
+// own cell comes first; another cell is looked up only when its box is nearer
+// than the best distance so far (and the radius), which leaves one or two of
+// the 27 for a query near the surface.  Each query walks its own set of them,
+// so that a wavefront takes as many rounds as its longest set and not one for
+// each cell that some query needs.  The box distance is taken low by 2^-21 of
+// the coordinate and the edge, more than the roundings of the cell coordinate
+// and of the products here, so that a cell holding a nearer point is never
+// left out and the minimum is that over all 27 cells.  Bound: the vector ALU,
+// the rounds that only some of the queries need.  1.0 M random queries against
+// 2.0 M vertices and the reverse, radius five voxels: 2036 us a call with every
+// cell read, in three 4-byte loads a point, 400 with the cells by their boxes,
+// 288 with a set a query and two lanes (one lane 303, four 344).
 // The distances' sum: per-workgroup partials in FP64, added by nn_sum_kernel
 // (one atomic a wavefront on the sum had serialised).
+constexpr int kNnLanes = 2;
+
+__device__ inline float nn_group_min(float x)
+{
+    // lanes exchanged by 1 and 2 within four, then the halves of eight
+    if (kNnLanes > 1) x = fminf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false)));
+    if (kNnLanes > 2) x = fminf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false)));
+    if (kNnLanes > 4)
+        x = fminf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, false)));
+    return x;
+}
+
 __global__ __launch_bounds__(256) void nn_query_kernel(const float* __restrict__ q, int64_t n, NnGrid g, bool empty,
                                                        float radius, float* dist, double* partial)
 {
     __shared__ double part[4];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t sub = threadIdx.x & (kNnLanes - 1);
     double mine = 0.0;
-    if (i < n) {
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kNnLanes; i < n;
+         i += (int64_t)gridDim.x * blockDim.x / kNnLanes) {
         const float x[3] = {q[3 * i], q[3 * i + 1], q[3 * i + 2]};
         float best = __builtin_inff();
         if (!empty) {
@@ -752,40 +795,48 @@ __global__ __launch_bounds__(256) void nn_query_kernel(const float* __restrict__
             }
             // nothing beyond the radius counts
             const float cap = radius * radius * (1.0f + 0x1p-16f);
-            for (int j = 0; j < 27; ++j) {
-                const int o = kNnOrder.v[j];
-                const int d[3] = {(o & 3) - 1, ((o >> 2) & 3) - 1, (o >> 4) - 1};
-                float away = 0.0f;
-#pragma unroll
-                for (int r = 0; r < 3; ++r) away += d[r] < 0 ? lo[r] : d[r] > 0 ? hi[r] : 0.0f;
-                if (away * (1.0f - 0x1p-20f) > fminf(best, cap)) continue;
-                const int cx = c[0] + d[0], cy = c[1] + d[1], cz = c[2] + d[2];
-                const uint64_t key = pack_key(cx, cy, cz);
-                uint32_t h = hash_block(cx, cy, cz) & g.mask;
-                uint32_t a = 0u, e = 0u;
-                for (uint32_t probe = 0; probe <= g.mask; ++probe) {
-                    const uint4 w = reinterpret_cast<const uint4*>(g.cells)[h];
-                    const uint64_t k = ((uint64_t)w.y << 32) | w.x;
-                    if (k == key) {
-                        a = w.z;
-                        e = w.z + w.w;
-                    }
-                    if (k == key || k == kKeyEmpty) break;
-                    h = (h + 1) & g.mask;
-                }
+            auto look = [&](int cx, int cy, int cz) {
+                uint32_t a, e;
+                nn_range(g, cx, cy, cz, a, e);
 #pragma unroll 4
-                for (uint32_t k = a; k < e; ++k) {
+                for (uint32_t k = a + sub; k < e; k += kNnLanes) {
                     const float4 p = g.pts[k];
                     const float ex = x[0] - p.x;
                     const float ey = x[1] - p.y;
                     const float ez = x[2] - p.z;
                     best = fminf(best, (ex * ex + ey * ey) + ez * ez);
                 }
+                best = nn_group_min(best);  // a group's lanes are here together
+            };
+            look(c[0], c[1], c[2]);
+            // the other cells, those out of reach along one axis left out at once
+            constexpr float low = 1.0f - 0x1p-20f;
+            const float reach = fminf(best, cap);
+            uint32_t left = ~1u;
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+                left &= (kNnOrder.mask[r][1] | (lo[r] * low > reach ? 0u : kNnOrder.mask[r][0])) |
+                        (hi[r] * low > reach ? 0u : kNnOrder.mask[r][2]);
+            while (left != 0u) {
+                const int j = __ffs((int)left) - 1;
+                left &= left - 1u;
+                int d[3];
+                float away = 0.0f;
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    const uint32_t w = j < 16 ? (uint32_t)kNnOrder.d[r] : (uint32_t)(kNnOrder.d[r] >> 32);
+                    d[r] = (int)((w >> ((2 * j) & 31)) & 3u) - 1;
+                    away += d[r] < 0 ? lo[r] : d[r] > 0 ? hi[r] : 0.0f;
+                }
+                if (away * low > fminf(best, cap)) continue;
+                look(c[0] + d[0], c[1] + d[1], c[2] + d[2]);
             }
         }
         const float d = fminf(sqrtf(best), radius);
-        if (dist) dist[i] = d;
-        mine = (double)d;
+        if (sub == 0u) {
+            if (dist) dist[i] = d;
+            mine += (double)d;
+        }
     }
     if (partial) {
 #pragma unroll
@@ -929,7 +980,7 @@ sc_status sc_nn_distance(const float* ref, int64_t n_ref, const float* query, in
     g.inv = 1.0f / g.edge;
     const uint32_t slots = pow2_at_least((uint64_t)(2 * std::max<int64_t>(n_ref, 1)));
     g.mask = slots - 1;
-    const int64_t wgs = (n_query + 255) / 256;
+    const int64_t wgs = std::min<int64_t>((n_query * kNnLanes + 255) / 256, 1 << 22);
     Scratch buf;
     uint2* slot_rank = nullptr;
     double* partial = nullptr;
