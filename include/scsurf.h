@@ -220,6 +220,12 @@ sc_status kf_fuse(const float* depth, const uint8_t* rgb, const sc_pose* poses, 
                   const sc_intrinsics* intr, const sc_fuse_params* params, float* kf_depth, float* kf_weight,
                   uint8_t* kf_rgba, void* stream);
 
+/* kf_fuse of frames that lie apart: depth and rgb are host arrays of
+ * n_frames device pointers (H x W float, H x W x 3 uint8). */
+sc_status kf_fuse_frames(const float* const* depth, const uint8_t* const* rgb, const sc_pose* poses, int32_t n_frames,
+                         int32_t ref, const sc_intrinsics* intr, const sc_fuse_params* params, float* kf_depth,
+                         float* kf_weight, uint8_t* kf_rgba, void* stream);
+
 /* kf_fuse for callers that cannot allocate (code under HIP graph capture,
  * serving loops, harnesses that forbid hipMalloc): the same arguments,
  * kernels and results, with every intermediate buffer (per-frame weights,

@@ -41,25 +41,49 @@ constexpr int kMaxFrames = 64;
 struct FuseFrames {
     float Rf[kMaxFrames][12];  // forward: T*^-1 T_i, rows of R then t
     float Rb[kMaxFrames][12];  // backward: T_i^-1 T*
+    const float* Z[kMaxFrames];    // depth, H x W
+    const uint8_t* C[kMaxFrames];  // colour, H x W x 3
 };
 
-// Relative poses passed by value, kStageFrames frames per launch, so that no
-// host staging buffer or copy is needed.
+// Relative poses and images passed by value, kStageFrames frames per launch, so
+// that no host staging buffer or copy is needed.
 constexpr int kStageFrames = 32;
 struct PoseChunk {
     float Rf[kStageFrames][12];
     float Rb[kStageFrames][12];
+    const float* Z[kStageFrames];
+    const uint8_t* C[kStageFrames];
 };
 
 // Work of one fusion done beside the colour prep and the depth weight: frame
 // 0's depth tiles clear the fixed-point accumulators of their pixels, and the
-// first one stores the first `count` relative poses.
+// first one stores the first `count` relative poses and images.
 struct FuseInit {
     unsigned long long* acc;  // KW then KZ, 2 x H W
     FuseFrames* fr;
+    // the first frame's images where the others follow them (n x H x W), else
+    // null: an address from the table waits for a load of its own
+    const float* Z0;
+    const uint8_t* C0;
     int32_t count;
     PoseChunk poses;
 };
+
+// A frame's images: their addresses come from memory, so that the compiler has
+// to be told that they are global ones.
+typedef __attribute__((address_space(1))) const float FrameDepth;
+typedef __attribute__((address_space(1))) const uint8_t FrameColor;
+
+// An address that is the same in every lane, in scalar registers: a load that
+// brings it is then waited for once and not before each load through it.
+template <class T>
+__device__ inline const T* uniform(const T* p)
+{
+    const uint64_t a = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return (const T*)(((uint64_t)hi << 32) | lo);
+}
 
 __device__ inline bool zvalid(float z, float zmin, float zmax) { return z >= zmin && z <= zmax; }
 
@@ -133,9 +157,9 @@ struct DwLds {
     float x[kDwLH][kDwLW], y[kDwLH][kDwLW], z[kDwLH][kDwLW];
 };
 
-// Tile `tile` of frame f; `acc` (or null): the accumulators that frame 0's
+// Tile `tile` of frame f (depth Zf); `acc` (or null): the accumulators that frame 0's
 // tiles clear.
-__device__ inline void depth_weight_tile(const float* __restrict__ Z, int f, int tile, const sc_intrinsics& in,
+__device__ inline void depth_weight_tile(FrameDepth* __restrict__ Zf, int f, int tile, const sc_intrinsics& in,
                                          const sc_fuse_params& p, int tiles_x, float* __restrict__ wz,
                                          unsigned long long* acc, DwLds& lds)
 {
@@ -145,7 +169,6 @@ __device__ inline void depth_weight_tile(const float* __restrict__ Z, int f, int
     const int W = in.width, H = in.height;
     const int64_t np = (int64_t)W * H;
     const int u0 = (tile % tiles_x) * kDwTW, v0 = (tile / tiles_x) * kDwTH;
-    const float* Zf = Z + (size_t)f * np;
     // staging: every depth load of a thread issues before the divisions
     float zs[kDwStage];
 #pragma unroll
@@ -212,7 +235,7 @@ __global__ __launch_bounds__(256) void depth_weight_kernel(const float* __restri
     __shared__ DwLds lds;
     const int f = blockIdx.y, tile = blockIdx.x;
     if (f >= n || tile >= tiles) return;
-    depth_weight_tile(Z, f, tile, in, p, tiles_x, wz, nullptr, lds);
+    depth_weight_tile((FrameDepth*)(Z + (size_t)f * in.width * in.height), f, tile, in, p, tiles_x, wz, nullptr, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -236,7 +259,7 @@ __global__ __launch_bounds__(256) void depth_weight_kernel(const float* __restri
 constexpr int kWpT = 16, kWpM = 8, kWpL = kWpT + 2 * kWpM;
 constexpr int kWpE = 4, kWpD = kWpE * kWpT;
 
-__global__ __launch_bounds__(256) void warp_kernel(const float* __restrict__ Z, const float* __restrict__ wz, int n,
+__global__ __launch_bounds__(256) void warp_kernel(const float* __restrict__ wz, int n,
                                                    sc_intrinsics in, float z_nom, int tiles_x,
                                                    const FuseFrames* __restrict__ fr, unsigned long long* KW,
                                                    unsigned long long* KZ, const long long* __restrict__ parts,
@@ -292,9 +315,9 @@ __global__ __launch_bounds__(256) void warp_kernel(const float* __restrict__ Z, 
                 const int2 d = shift[f];
                 const int u = ku + tx - d.x, v = kv + ty - d.y;
                 if (u >= 0 && u < W && v >= 0 && v < H) {
-                    const size_t pix = (size_t)f * np + (size_t)v * W + u;
-                    wg[j] = wz[pix];
-                    zg[j] = Z[pix];
+                    const size_t pix = (size_t)v * W + u;
+                    wg[j] = wz[(size_t)f * np + pix];
+                    zg[j] = ((FrameDepth*)fr->Z[f])[pix];
                 }
             }
         }
@@ -372,7 +395,7 @@ struct PrepLds {
 // kOutCh: 3 (packed RGB, the standalone output) or 4 (RGB and a zero, one
 // 8-byte store per pixel; the layout the colour kernel gathers from).
 template <int kOutCh>
-__device__ inline void color_prep_tile(const uint8_t* __restrict__ rgb, int f, int tile, int W, int H, int tiles_x,
+__device__ inline void color_prep_tile(FrameColor* __restrict__ C, int f, int tile, int W, int H, int tiles_x,
                                        int tiles, uint16_t* __restrict__ out, long long* __restrict__ parts,
                                        PrepLds& lds)
 {
@@ -382,7 +405,6 @@ __device__ inline void color_prep_tile(const uint8_t* __restrict__ rgb, int f, i
     auto& red = lds.red;
     const int u0 = (tile % tiles_x) * kPrepTW, v0 = (tile / tiles_x) * kPrepTH;
     const int64_t np = (int64_t)W * H;
-    const uint8_t* C = rgb + (size_t)f * np * 3;
     // staging: every load of a thread issues before its first LDS store
     uint32_t st[kPrepStage];
 #pragma unroll
@@ -392,7 +414,7 @@ __device__ inline void color_prep_tile(const uint8_t* __restrict__ rgb, int f, i
         if (p < kPrepLW * kPrepLH) {
             const int i = p % kPrepLW, j = p / kPrepLW;
             const int uu = clampi(u0 - kPrepHalo + i, 0, W - 1), vv = clampi(v0 - kPrepHalo + j, 0, H - 1);
-            const uint8_t* q = C + 3 * ((size_t)vv * W + uu);
+            FrameColor* q = C + 3 * ((size_t)vv * W + uu);
             st[k] = (uint32_t)q[0] | ((uint32_t)q[1] << 8) | ((uint32_t)q[2] << 16);
         }
     }
@@ -474,7 +496,7 @@ __global__ __launch_bounds__(256) void color_prep_kernel(const uint8_t* __restri
     __shared__ PrepLds lds;
     const int f = blockIdx.y, tile = blockIdx.x;
     if (f >= n || tile >= tiles) return;
-    color_prep_tile<3>(rgb, f, tile, W, H, tiles_x, tiles, out, parts, lds);
+    color_prep_tile<3>((FrameColor*)(rgb + (size_t)f * W * H * 3), f, tile, W, H, tiles_x, tiles, out, parts, lds);
 }
 
 // A fusion's colour prep (four channels) and depth weight in one launch: of a
@@ -482,8 +504,7 @@ __global__ __launch_bounds__(256) void color_prep_kernel(const uint8_t* __restri
 // the depth tiles.  Neither needs the other, and each alone waits for its loads with the
 // CUs half empty at its end: 640x480, 5 frames 16.2 + 11.5 us in two launches,
 // now 22 in one; 60 frames 104 + 72 us, now 172.
-__global__ __launch_bounds__(256) void fuse_front_kernel(const uint8_t* __restrict__ rgb, const float* __restrict__ Z,
-                                                         sc_intrinsics in, sc_fuse_params p, int prep_x,
+__global__ __launch_bounds__(256) void fuse_front_kernel(sc_intrinsics in, sc_fuse_params p, int prep_x,
                                                          int prep_tiles, int dw_x,
                                                          uint16_t* __restrict__ cs, long long* __restrict__ parts,
                                                          float* __restrict__ wz, const FuseInit init)
@@ -494,7 +515,9 @@ __global__ __launch_bounds__(256) void fuse_front_kernel(const uint8_t* __restri
     } lds;
     const int f = blockIdx.y;
     if ((int)blockIdx.x < prep_tiles) {
-        color_prep_tile<4>(rgb, f, blockIdx.x, in.width, in.height, prep_x, prep_tiles, cs, parts, lds.prep);
+        const uint8_t* C = init.C0 ? init.C0 + (size_t)f * in.width * in.height * 3
+                                   : f < init.count ? init.poses.C[f] : init.fr->C[f];
+        color_prep_tile<4>((FrameColor*)uniform(C), f, blockIdx.x, in.width, in.height, prep_x, prep_tiles, cs, parts, lds.prep);
         return;
     }
     const int tile = (int)blockIdx.x - prep_tiles;
@@ -503,8 +526,11 @@ __global__ __launch_bounds__(256) void fuse_front_kernel(const uint8_t* __restri
             init.fr->Rf[i / 12][i % 12] = init.poses.Rf[i / 12][i % 12];
             init.fr->Rb[i / 12][i % 12] = init.poses.Rb[i / 12][i % 12];
         }
+        for (int i = threadIdx.x; i < init.count; i += blockDim.x) init.fr->Z[i] = init.poses.Z[i];
     }
-    depth_weight_tile(Z, f, tile, in, p, dw_x, wz, init.acc, lds.dw);
+    const float* Z = init.Z0 ? init.Z0 + (size_t)f * in.width * in.height
+                             : f < init.count ? init.poses.Z[f] : init.fr->Z[f];
+    depth_weight_tile((FrameDepth*)uniform(Z), f, tile, in, p, dw_x, wz, init.acc, lds.dw);
 }
 
 // One workgroup per frame (standalone colour pre-processing).
@@ -560,7 +586,7 @@ __device__ inline float color_point(const unsigned long long* __restrict__ KW,
 }
 
 // Frame i's observation of point P: 8-bit channels and weight (0: none).
-__device__ inline uint2 color_observe(const float* __restrict__ Z, const float* __restrict__ wz,
+__device__ inline uint2 color_observe(const float* __restrict__ wz,
                                       const uint16_t* __restrict__ cs, const double* __restrict__ wb, int i,
                                       const sc_intrinsics& in, float occ_rel, const FuseFrames* __restrict__ fr,
                                       bool live, const float P[3])
@@ -575,7 +601,7 @@ __device__ inline uint2 color_observe(const float* __restrict__ Z, const float* 
     if (!(x0 >= 0.0f && x0 + 1.0f <= (float)(W - 1) && y0 >= 0.0f && y0 + 1.0f <= (float)(H - 1))) return o;
     const size_t base = (size_t)i * (W * H);
     const float wzi = wz[base + (size_t)iv * W + iu];
-    const float zi = Z[base + (size_t)iv * W + iu];
+    const float zi = ((FrameDepth*)fr->Z[i])[(size_t)iv * W + iu];
     const float ax = uf - x0, ay = vf - y0;
     const int ix = (int)x0, iy = (int)y0;
     // four channels of 16 bits per pixel, 8-byte aligned
@@ -630,7 +656,7 @@ __device__ inline uint32_t median_regs(const uint2 (&o)[N], int sh, T total)
 }
 
 template <int N>
-__global__ __launch_bounds__(256) void color_kernel(const float* __restrict__ Z, const float* __restrict__ wz,
+__global__ __launch_bounds__(256) void color_kernel(const float* __restrict__ wz,
                                                     const uint16_t* __restrict__ cs, const double* __restrict__ wb,
                                                     sc_intrinsics in, float occ_rel,
                                                     const FuseFrames* __restrict__ fr,
@@ -643,7 +669,7 @@ __global__ __launch_bounds__(256) void color_kernel(const float* __restrict__ Z,
     const float w = color_point(KW, KZ, idx, in, P);
     uint2 o[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) o[i] = color_observe(Z, wz, cs, wb, i, in, occ_rel, fr, w > 0.0f, P);
+    for (int i = 0; i < N; ++i) o[i] = color_observe(wz, cs, wb, i, in, occ_rel, fr, w > 0.0f, P);
     uint64_t total = 0;
 #pragma unroll
     for (int i = 0; i < N; ++i) total += o[i].y;
@@ -679,7 +705,7 @@ __device__ inline uint32_t median_lds(const uint2* obs, int n, int lane, int sh,
 }
 
 __global__ __launch_bounds__(64 * kColorWaves) void color_many_kernel(
-    const float* __restrict__ Z, const float* __restrict__ wz, const uint16_t* __restrict__ cs,
+    const float* __restrict__ wz, const uint16_t* __restrict__ cs,
     const double* __restrict__ wb, int n, sc_intrinsics in, float occ_rel, const FuseFrames* __restrict__ fr,
     const unsigned long long* __restrict__ KW, const unsigned long long* __restrict__ KZ, float* Zs, float* Ws,
     uint8_t* rgba)
@@ -692,7 +718,7 @@ __global__ __launch_bounds__(64 * kColorWaves) void color_many_kernel(
     float P[3];
     const float w = color_point(KW, KZ, idx, in, P);
     for (int i = wave; i < n; i += kColorWaves)
-        obs[i * 64 + lane] = color_observe(Z, wz, cs, wb, i, in, occ_rel, fr, w > 0.0f, P);
+        obs[i * 64 + lane] = color_observe(wz, cs, wb, i, in, occ_rel, fr, w > 0.0f, P);
     __syncthreads();
     if (wave < 3) {
         uint64_t total = 0;
@@ -875,12 +901,17 @@ static void rel_pose(const sc_pose& A, const sc_pose& B, float out[12])
 static int dw_tiles_x(int W) { return (W + kDwTW - 1) / kDwTW; }
 static int dw_tiles(int W, int H) { return dw_tiles_x(W) * ((H + kDwTH - 1) / kDwTH); }
 
-// Relative poses of frames first .. first + count - 1 into the device table.
+// Relative poses and images of frames first .. first + count - 1 into the
+// device table.
 __global__ void stage_poses_kernel(PoseChunk c, int first, int count, FuseFrames* fr)
 {
     for (int i = threadIdx.x; i < count * 12; i += blockDim.x) {
         fr->Rf[first + i / 12][i % 12] = c.Rf[i / 12][i % 12];
         fr->Rb[first + i / 12][i % 12] = c.Rb[i / 12][i % 12];
+    }
+    for (int i = threadIdx.x; i < count; i += blockDim.x) {
+        fr->Z[first + i] = c.Z[i];
+        fr->C[first + i] = c.C[i];
     }
 }
 
@@ -898,39 +929,45 @@ struct FuseBufs {
 // The fusion kernels of one keyframe.  The relative poses of the first
 // kStageFrames frames travel in the first launch; those of later
 // frames are stored by stage_poses_kernel launches enqueued first.
-static void launch_fuse(const FuseBufs& b, const float* depth, const uint8_t* rgb, const sc_pose* poses, int n_frames,
-                        int ref, const sc_intrinsics& in, const sc_fuse_params& params, float* kf_depth,
+static void launch_fuse(const FuseBufs& b, const float* const* depth, const uint8_t* const* rgb, const sc_pose* poses,
+                        int n_frames, int ref, const sc_intrinsics& in, const sc_fuse_params& params, float* kf_depth,
                         float* kf_weight, uint8_t* kf_rgba, hipStream_t s)
 {
     const int64_t np = (int64_t)in.width * in.height;
     FuseInit init;
     init.acc = b.acc;
     init.fr = b.fr;
+    init.Z0 = depth[0];
+    init.C0 = rgb[0];
+    for (int i = 1; i < n_frames; ++i) {
+        if (depth[i] != depth[0] + i * np) init.Z0 = nullptr;
+        if (rgb[i] != rgb[0] + i * np * 3) init.C0 = nullptr;
+    }
+    auto stage = [&](int i, int j) {
+        rel_pose(poses[ref], poses[i], init.poses.Rf[j]);
+        rel_pose(poses[i], poses[ref], init.poses.Rb[j]);
+        init.poses.Z[j] = depth[i];
+        init.poses.C[j] = rgb[i];
+    };
     for (int i0 = kStageFrames; i0 < n_frames; i0 += kStageFrames) {
         const int cnt = std::min(kStageFrames, n_frames - i0);
-        for (int j = 0; j < cnt; ++j) {
-            rel_pose(poses[ref], poses[i0 + j], init.poses.Rf[j]);
-            rel_pose(poses[i0 + j], poses[ref], init.poses.Rb[j]);
-        }
+        for (int j = 0; j < cnt; ++j) stage(i0 + j, j);
         stage_poses_kernel<<<1, 256, 0, s>>>(init.poses, i0, cnt, b.fr);
     }
     init.count = std::min(kStageFrames, n_frames);
-    for (int j = 0; j < init.count; ++j) {
-        rel_pose(poses[ref], poses[j], init.poses.Rf[j]);
-        rel_pose(poses[j], poses[ref], init.poses.Rb[j]);
-    }
+    for (int j = 0; j < init.count; ++j) stage(j, j);
     const int pt = prep_tiles(in.width, in.height), dt = dw_tiles(in.width, in.height);
     fuse_front_kernel<<<dim3((unsigned)(pt + dt), (unsigned)n_frames), 256, 0, s>>>(
-        rgb, depth, in, params, prep_tiles_x(in.width), pt, dw_tiles_x(in.width), b.cs, b.parts, b.wz, init);
+        in, params, prep_tiles_x(in.width), pt, dw_tiles_x(in.width), b.cs, b.parts, b.wz, init);
     // target tiles over the image and kWpE more on each side
     const int wtx = (in.width + kWpT - 1) / kWpT + 2 * kWpE, wty = (in.height + kWpT - 1) / kWpT + 2 * kWpE;
     const float z_nom = 0.5f * (params.z_min + params.z_max);
-    warp_kernel<<<(unsigned)(n_frames + wtx * wty), 256, 0, s>>>(depth, b.wz, n_frames, in, z_nom, wtx, b.fr, b.acc,
+    warp_kernel<<<(unsigned)(n_frames + wtx * wty), 256, 0, s>>>(b.wz, n_frames, in, z_nom, wtx, b.fr, b.acc,
                                                                  b.acc + np, b.parts, pt, b.wb);
     const unsigned long long *KW = b.acc, *KZ = b.acc + np;
     auto color = [&](auto n) {
         color_kernel<decltype(n)::value><<<(unsigned)((np + 255) / 256), 256, 0, s>>>(
-            depth, b.wz, b.cs, b.wb, in, params.occ_rel, b.fr, KW, KZ, kf_depth, kf_weight, kf_rgba);
+            b.wz, b.cs, b.wb, in, params.occ_rel, b.fr, KW, KZ, kf_depth, kf_weight, kf_rgba);
     };
     switch (n_frames) {
     case 1: color(std::integral_constant<int, 1>{}); break;
@@ -943,7 +980,7 @@ static void launch_fuse(const FuseBufs& b, const float* depth, const uint8_t* rg
     case 8: color(std::integral_constant<int, 8>{}); break;
     default:
         color_many_kernel<<<(unsigned)((np + 63) / 64), 64 * kColorWaves, sizeof(uint2) * 64 * (size_t)n_frames, s>>>(
-            depth, b.wz, b.cs, b.wb, n_frames, in, params.occ_rel, b.fr, KW, KZ, kf_depth, kf_weight, kf_rgba);
+            b.wz, b.cs, b.wb, n_frames, in, params.occ_rel, b.fr, KW, KZ, kf_depth, kf_weight, kf_rgba);
     }
 }
 
@@ -956,7 +993,8 @@ static void launch_fuse(const FuseBufs& b, const float* depth, const uint8_t* rg
 // device with hipGetSymbolAddress and only that address is passed on.  Every
 // call on a device shares that device's copy, so calls that overlap on one
 // device race.
-constexpr size_t kScratchBytes = size_t(76) << 20;
+// 76 MiB for the images and 1 KiB for the frames' addresses.
+constexpr size_t kScratchBytes = (size_t(76) << 20) + sizeof(FuseFrames::Z) + sizeof(FuseFrames::C);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -1000,6 +1038,19 @@ static size_t fuse_layout(unsigned char* base, size_t np, size_t frames, size_t 
     return off;
 }
 
+// The frames of n x H x W (x 3) arrays.
+static bool frame_rows(const float* depth, const uint8_t* rgb, int n, const sc_intrinsics* in, const float** Z,
+                       const uint8_t** C)
+{
+    if (!depth || !rgb || n <= 0 || n > kMaxFrames || !intr_valid(in)) return false;
+    const size_t np = (size_t)in->width * in->height;
+    for (int i = 0; i < n; ++i) {
+        Z[i] = depth + i * np;
+        C[i] = rgb + i * np * 3;
+    }
+    return true;
+}
+
 }  // namespace sc
 
 using namespace sc;
@@ -1033,13 +1084,15 @@ sc_status sc_color_prep(const uint8_t* rgb, int32_t n_frames, int32_t width, int
     return hipGetLastError() == hipSuccess ? SC_OK : SC_EDEVICE;
 }
 
-sc_status kf_fuse(const float* depth, const uint8_t* rgb, const sc_pose* poses, int32_t n_frames, int32_t ref,
-                  const sc_intrinsics* intr, const sc_fuse_params* params, float* kf_depth, float* kf_weight,
-                  uint8_t* kf_rgba, void* stream)
+sc_status kf_fuse_frames(const float* const* depth, const uint8_t* const* rgb, const sc_pose* poses, int32_t n_frames,
+                         int32_t ref, const sc_intrinsics* intr, const sc_fuse_params* params, float* kf_depth,
+                         float* kf_weight, uint8_t* kf_rgba, void* stream)
 {
     if (!depth || !rgb || !poses || n_frames <= 0 || n_frames > kMaxFrames || ref < 0 || ref >= n_frames ||
         !intr_valid(intr) || !fuse_params_valid(params) || !kf_depth || !kf_weight || !kf_rgba)
         return SC_EINVAL;
+    for (int i = 0; i < n_frames; ++i)
+        if (!depth[i] || !rgb[i]) return SC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     const sc_intrinsics in = *intr;
     const int64_t np = (int64_t)in.width * in.height;
@@ -1051,12 +1104,24 @@ sc_status kf_fuse(const float* depth, const uint8_t* rgb, const sc_pose* poses, 
     return hipGetLastError() == hipSuccess ? SC_OK : SC_EDEVICE;
 }
 
+sc_status kf_fuse(const float* depth, const uint8_t* rgb, const sc_pose* poses, int32_t n_frames, int32_t ref,
+                  const sc_intrinsics* intr, const sc_fuse_params* params, float* kf_depth, float* kf_weight,
+                  uint8_t* kf_rgba, void* stream)
+{
+    const float* Z[kMaxFrames];
+    const uint8_t* C[kMaxFrames];
+    if (!frame_rows(depth, rgb, n_frames, intr, Z, C)) return SC_EINVAL;
+    return kf_fuse_frames(Z, C, poses, n_frames, ref, intr, params, kf_depth, kf_weight, kf_rgba, stream);
+}
+
 sc_status kf_fuse_noalloc(const float* depth, const uint8_t* rgb, const sc_pose* poses, int32_t n_frames, int32_t ref,
                           const sc_intrinsics* intr, const sc_fuse_params* params, float* kf_depth, float* kf_weight,
                           uint8_t* kf_rgba, void* stream)
 {
-    if (!depth || !rgb || !poses || n_frames <= 0 || n_frames > kMaxFrames || ref < 0 || ref >= n_frames ||
-        !intr_valid(intr) || !fuse_params_valid(params) || !kf_depth || !kf_weight || !kf_rgba)
+    const float* Z[kMaxFrames];
+    const uint8_t* C[kMaxFrames];
+    if (!frame_rows(depth, rgb, n_frames, intr, Z, C) || !poses || ref < 0 || ref >= n_frames ||
+        !fuse_params_valid(params) || !kf_depth || !kf_weight || !kf_rgba)
         return SC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     const sc_intrinsics in = *intr;
@@ -1068,7 +1133,7 @@ sc_status kf_fuse_noalloc(const float* depth, const uint8_t* rgb, const sc_pose*
     const sc_status st = scratch_address(&base);
     if (st != SC_OK) return st;
     fuse_layout(base, np, (size_t)n_frames, parts, b);
-    launch_fuse(b, depth, rgb, poses, n_frames, ref, in, *params, kf_depth, kf_weight, kf_rgba, s);
+    launch_fuse(b, Z, C, poses, n_frames, ref, in, *params, kf_depth, kf_weight, kf_rgba, s);
     return hipGetLastError() == hipSuccess ? SC_OK : SC_EDEVICE;
 }
 

@@ -64,7 +64,8 @@ class sc_schedule(ctypes.Structure):
 
 
 EXPORTS = ["sc_version", "sc_volume_create", "sc_volume_destroy", "sc_volume_reset", "sc_volume_query",
-           "sc_volume_export", "sc_depth_weight", "sc_color_prep", "kf_fuse", "kf_fuse_noalloc", "hash_alloc", "tsdf_integrate",
+           "sc_volume_export", "sc_depth_weight", "sc_color_prep", "kf_fuse", "kf_fuse_frames", "kf_fuse_noalloc", "hash_alloc",
+           "tsdf_integrate",
            "tsdf_integrate_batch",
            "tsdf_deintegrate", "sc_select", "sc_select_dist", "sc_relative_motion", "reintegrate_batch",
            "reintegrate_plain",
@@ -95,7 +96,7 @@ def lib():
     L.sc_volume_export.argtypes = [P, P, P, P, P, P, i64, ctypes.POINTER(i64)]
     L.sc_depth_weight.argtypes = [P, i32, ctypes.POINTER(sc_intrinsics), ctypes.POINTER(sc_fuse_params), P, P]
     L.sc_color_prep.argtypes = [P, i32, i32, i32, P, P, P]
-    for f in (L.kf_fuse, L.kf_fuse_noalloc):
+    for f in (L.kf_fuse, L.kf_fuse_frames, L.kf_fuse_noalloc):
         f.argtypes = [P, P, ctypes.POINTER(sc_pose), i32, i32, ctypes.POINTER(sc_intrinsics),
                       ctypes.POINTER(sc_fuse_params), P, P, P, P]
     L.hash_alloc.argtypes = [P, P, i64, P, P]
@@ -678,6 +679,40 @@ def _fuse(entry: str, depth: torch.Tensor, rgb: torch.Tensor, R, t, intr, params
 def kf_fuse(depth: torch.Tensor, rgb: torch.Tensor, R, t, intr, params=None, ref=0, stream=None, out=None) -> Keyframe:
     """Fuses frames (n,H,W) / (n,H,W,3) at poses (R, t) into one keyframe."""
     return _fuse("kf_fuse", depth, rgb, R, t, intr, params, ref, stream, out)
+
+
+def frames_fusible(depth, rgb) -> bool:
+    """Whether the frames can be fused where they lie (kf_fuse_frames): device
+    tensors of one size, contiguous, float32 depth and uint8 colour."""
+    z, c = depth[0], rgb[0]
+    return (z.is_cuda and z.dim() == 2 and c.shape == z.shape + (3,)
+            and all(x.shape == z.shape and x.device == z.device and x.dtype == torch.float32 and x.is_contiguous()
+                    for x in depth)
+            and all(x.shape == c.shape and x.device == z.device and x.dtype == torch.uint8 and x.is_contiguous()
+                    for x in rgb))
+
+
+def kf_fuse_frames(depth, rgb, R, t, intr, params=None, ref=0, stream=None) -> Keyframe:
+    """kf_fuse of a list of frames (H,W) / (H,W,3) without stacking them; the
+    frames must stay alive until the work on `stream` is done with them."""
+    if not frames_fusible(depth, rgb):
+        raise ValueError("frames must be contiguous device tensors of one size, float32 depth and uint8 rgb")
+    H, W = depth[0].shape
+    _check_shape(depth[0], _image_size(intr), "depth")
+    T = poses(R, t)
+    n = len(depth)
+    if len(T) != n or len(rgb) != n:
+        raise ValueError(f"{len(T)} poses and {len(rgb)} colour images for {n} frames")
+    dev = depth[0].device
+    out = Keyframe(torch.empty((H, W), dtype=torch.float32, device=dev),
+                   torch.empty((H, W), dtype=torch.float32, device=dev),
+                   torch.empty((H, W, 4), dtype=torch.uint8, device=dev))
+    p = params or fuse_params()
+    rows = ctypes.c_void_p * n
+    check(lib().kf_fuse_frames(rows(*[x.data_ptr() for x in depth]), rows(*[x.data_ptr() for x in rgb]), T, n, ref,
+                               ctypes.byref(intrinsics(intr)), ctypes.byref(p), out.depth.data_ptr(),
+                               out.weight.data_ptr(), out.color.data_ptr(), stream_handle(stream)), "kf_fuse_frames")
+    return out
 
 
 def kf_fuse_noalloc(depth: torch.Tensor, rgb: torch.Tensor, R, t, intr, params=None, ref=0, stream=None,

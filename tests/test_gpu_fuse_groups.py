@@ -73,3 +73,37 @@ def test_pack_edges(W, H):
             v = z[s][pos[s] & (z[s] > 0)]
             lo, hi = (v.min(), v.max()) if v.size else (np.inf, -np.inf)
             assert (cells[i, j, 0], cells[i, j, 1]) == (np.float32(lo), np.float32(hi))
+
+
+@pytest.mark.parametrize("n,apart", [(1, True), (5, True), (33, True), (64, False), (5, False)])
+def test_frames_where_they_lie(n, apart):
+    """Frames in tensors of their own (the last in 33 and 64 groups past the
+    first chunk of addresses) give the keyframe of the stacked ones."""
+    print(f"[gpu] {n} frames, {'apart' if apart else 'views of one tensor'}", flush=True)
+    W, H = 70, 19
+    intr, z, rgb, R, t = _plane_frames(W, H, n, n)
+    zs, cs = torch.from_numpy(z).cuda(), torch.from_numpy(rgb).cuda()
+    one = scsurf.kf_fuse(zs, cs, R, t, intr, ref=n // 2)
+    zl = [x.clone() if apart else x for x in zs]
+    # an odd address for every other colour image
+    cl = []
+    for i, x in enumerate(cs):
+        b = torch.empty(x.numel() + 1, dtype=torch.uint8, device="cuda")
+        b[i % 2:i % 2 + x.numel()] = x.reshape(-1)
+        cl.append(b[i % 2:i % 2 + x.numel()].view(H, W, 3) if apart else x)
+    got = scsurf.kf_fuse_frames(zl, cl, R, t, intr, ref=n // 2)
+    for a in ("depth", "weight", "color"):
+        assert torch.equal(getattr(got, a), getattr(one, a)), a
+
+
+def test_frames_that_cannot_be_fused_where_they_lie():
+    W, H = 20, 10
+    intr, z, rgb, R, t = _plane_frames(W, H, 2, 1)
+    zl, cl = list(torch.from_numpy(z).cuda()), list(torch.from_numpy(rgb).cuda())
+    assert scsurf.frames_fusible(zl, cl)
+    wide = torch.zeros((H, 2 * W), device="cuda")
+    for bad in ([zl[0], zl[1].double()], [zl[0], zl[1].cpu()], [zl[0], wide[:, ::2]], [zl[0], zl[1][:5]]):
+        assert not scsurf.frames_fusible(bad, cl)
+        with pytest.raises(ValueError):
+            scsurf.kf_fuse_frames(bad, cl, R, t, intr)
+    assert not scsurf.frames_fusible(zl, [cl[0], cl[1].int()])
