@@ -33,6 +33,7 @@
 
 #include "common.hpp"
 #include "internal.hpp"
+#include "kernels.hpp"
 
 namespace sc {
 
@@ -55,6 +56,16 @@ struct PoseChunk {
     const uint8_t* C[kStageFrames];
 };
 
+// Source tiles (16 x 16 pixels of a frame) by the keyframe tile that their
+// samples land near: up to `cap` items f << 20 | tile a keyframe tile, the
+// others in `over` (room for every source tile).
+struct WarpBins {
+    uint32_t* count;  // per keyframe tile, then the length of `over`
+    uint32_t* items;
+    uint32_t* over;
+    int32_t cap, tiles_x, tiles;
+};
+
 // Work of one fusion done beside the colour prep and the depth weight: frame
 // 0's depth tiles clear the fixed-point accumulators of their pixels, and the
 // first one stores the first `count` relative poses and images.
@@ -65,6 +76,7 @@ struct FuseInit {
     // null: an address from the table waits for a load of its own
     const float* Z0;
     const uint8_t* C0;
+    WarpBins bins;  // emptied, if there are any
     int32_t count;
     PoseChunk poses;
 };
@@ -107,6 +119,23 @@ __device__ inline bool project(const sc_intrinsics& in, const float q[3], float&
     vf = (in.fy * q[1]) / q[2] + in.cy;
     const float fu = floorf(uf + 0.5f), fv = floorf(vf + 0.5f);
     if (!(fu >= 0.0f && fu <= (float)(in.width - 1) && fv >= 0.0f && fv <= (float)(in.height - 1))) return false;
+    iu = (int)fu;
+    iv = (int)fv;
+    return true;
+}
+
+// project's pixel alone: the coordinate's rounding test on a one-ulp
+// reciprocal (pixel_coord_fast), the correctly rounded division only near a
+// rounding boundary.  The same pixels for depths below 2^43 m, where the depth
+// sums' integers end.
+__device__ inline bool project_pixel(const sc_intrinsics& in, const float q[3], int& iu, int& iv)
+{
+    if (!(q[2] > 0.0f)) return false;
+    const float r = __builtin_amdgcn_rcpf(q[2]);
+    const float wl = (float)(in.width - 1), hl = (float)(in.height - 1);
+    const float fu = pixel_coord_fast(in.fx * q[0], q[2], r, in.cx, wl);
+    const float fv = pixel_coord_fast(in.fy * q[1], q[2], r, in.cy, hl);
+    if (!(fu >= 0.0f && fu <= wl && fv >= 0.0f && fv <= hl)) return false;
     iu = (int)fu;
     iv = (int)fv;
     return true;
@@ -359,6 +388,170 @@ __global__ __launch_bounds__(256) void warp_kernel(const float* __restrict__ wz,
     }
 }
 
+// The warp of groups of many frames.  The displacement of a frame's pixels
+// follows their depths, and over many frames the camera moves far enough that
+// one displacement a frame leaves most samples outside the windows (60 frames
+// of a turning camera: 64 % of them, 160 of warp_kernel's 242 us in their
+// atomics).  Here each 16 x 16 source tile of a frame goes by its own: a thread
+// a source tile takes the depth at its centre (or at the first of four other
+// pixels that has one), moves that point into the keyframe and appends the
+// tile to the list of the keyframe tile it lands in (the nearest one up to a
+// tile outside the image, its own place from there on, which spreads them).
+// The assignment only decides where samples are added up.
+__global__ __launch_bounds__(256) void warp_bin_kernel(int n, sc_intrinsics in, sc_fuse_params p,
+                                                       const FuseFrames* __restrict__ fr, WarpBins b)
+{
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (i >= n * b.tiles) return;
+    const int f = i / b.tiles, tile = i - f * b.tiles;
+    const int u0 = (tile % b.tiles_x) * 16, v0 = (tile / b.tiles_x) * 16;
+    FrameDepth* Z = (FrameDepth*)fr->Z[f];
+    int u[5], v[5];
+    float z[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        u[k] = min(u0 + (k == 0 ? 8 : (k & 1) ? 3 : 12), in.width - 1);
+        v[k] = min(v0 + (k == 0 ? 8 : (k & 2) ? 3 : 12), in.height - 1);
+        z[k] = Z[(size_t)v[k] * in.width + u[k]];
+    }
+    float us = (float)u[0], vs = (float)v[0], zs = 0.5f * (p.z_min + p.z_max);
+#pragma unroll
+    for (int k = 4; k >= 0; --k)
+        if (zvalid(z[k], p.z_min, p.z_max)) {
+            us = (float)u[k];
+            vs = (float)v[k];
+            zs = z[k];
+        }
+    float P[3], q[3];
+    backproject(us, vs, zs, in, P);
+    xform(fr->Rf[f], P, q);
+    int bx = u0 / 16, by = v0 / 16;
+    if (q[2] > 0.0f) {
+        const float x = (in.fx * q[0]) / q[2] + in.cx, y = (in.fy * q[1]) / q[2] + in.cy;
+        if (x > -16.0f && x < (float)in.width + 16.0f && y > -16.0f && y < (float)in.height + 16.0f) {
+            bx = (int)fminf(fmaxf(x, 0.0f), (float)(in.width - 1)) / 16;
+            by = (int)fminf(fmaxf(y, 0.0f), (float)(in.height - 1)) / 16;
+        }
+    }
+    const uint32_t item = (uint32_t)f << 20 | (uint32_t)tile;
+    const int bin = by * b.tiles_x + bx;
+    const uint32_t at = atomicAdd(b.count + bin, 1u);
+    if (at < (uint32_t)b.cap) b.items[(size_t)bin * b.cap + at] = item;
+    else b.over[atomicAdd(b.count + b.tiles, 1u)] = item;
+}
+
+// Workgroups [0, n): the frames' w_b, as in warp_kernel; then one a keyframe
+// tile, which adds its list's samples into its LDS window and those outside the
+// window to memory; then kWpOver for the source tiles beyond the lists, whose
+// samples all go to memory.
+// Bound: the vector ALU and the loads' latency, four source tiles at a time.
+// 60 frames of 640x480: 0.9 % of the samples outside the windows, 110 us with
+// warp_bin_kernel's 13 (242 us by a displacement a frame).  With few frames the
+// second launch costs more than it saves (whole fusions of 6 frames of a
+// turning camera 70 us against 65, of 10 frames 109 against 120), so groups of
+// more than kWarpFew take this way.
+constexpr int kWpOver = 64, kWarpFew = 8;
+
+__global__ __launch_bounds__(256) void warp_bins_kernel(const float* __restrict__ wz, int n, sc_intrinsics in,
+                                                        const FuseFrames* __restrict__ fr, unsigned long long* KW,
+                                                        unsigned long long* KZ, const long long* __restrict__ parts,
+                                                        int prep_tiles, double* wb, WarpBins b)
+{
+    __shared__ unsigned long long lw[kWpL * kWpL], lz[kWpL * kWpL];
+    __shared__ uint32_t items[2 * kMaxFrames];
+    if ((int)blockIdx.x < n) {
+        __shared__ long long red[4][4];
+        blur_reduce(parts + (size_t)blockIdx.x * prep_tiles * 4, prep_tiles, red, wb + blockIdx.x);
+        return;
+    }
+    const int W = in.width, H = in.height;
+    const size_t np = (size_t)W * H;
+    const int tx = (int)threadIdx.x & 15, ty = (int)threadIdx.x >> 4;
+    // this thread's sample of a source tile
+    auto load = [&](uint32_t item, float& w, float& z) {
+        const int f = (int)(item >> 20), tile = (int)(item & 0xFFFFFu);
+        const int u = (tile % b.tiles_x) * 16 + tx, v = (tile / b.tiles_x) * 16 + ty;
+        w = z = 0.0f;
+        if (u < W && v < H) {
+            const uint32_t pix = (uint32_t)(v * W + u);
+            w = wz[f * np + pix];
+            z = ((FrameDepth*)fr->Z[f])[pix];
+        }
+    };
+    auto warp = [&](uint32_t item, float w, float z, int& iu, int& iv, long long& wk, long long& zk) {
+        const int f = (int)(item >> 20), tile = (int)(item & 0xFFFFFu);
+        float P[3], q[3];
+        backproject((float)((tile % b.tiles_x) * 16 + tx), (float)((tile / b.tiles_x) * 16 + ty), z, in, P);
+        xform(fr->Rf[f], P, q);
+        wk = (long long)rintf(w * kWeightScale);
+        zk = (long long)rintf(q[2] * 1048576.0f);
+        return project_pixel(in, q, iu, iv);
+    };
+    auto add = [&](int iu, int iv, long long wk, long long zk) {
+        const size_t t = (size_t)iv * W + iu;
+        atomicAdd(KW + t, (unsigned long long)wk);
+        atomicAdd(KZ + t, (unsigned long long)(wk * zk));
+    };
+    const int bin = (int)blockIdx.x - n;
+    if (bin >= b.tiles) {
+        const uint32_t m = b.count[b.tiles];
+        for (uint32_t i = (uint32_t)(bin - b.tiles); i < m; i += kWpOver) {
+            const uint32_t item = __builtin_amdgcn_readfirstlane(b.over[i]);
+            float w, z;
+            load(item, w, z);
+            if (!(w > 0.0f)) continue;
+            int iu, iv;
+            long long wk, zk;
+            if (warp(item, w, z, iu, iv, wk, zk)) add(iu, iv, wk, zk);
+        }
+        return;
+    }
+    const int m = (int)min(b.count[bin], (uint32_t)b.cap);
+    if (m == 0) return;
+    for (int e = threadIdx.x; e < m; e += blockDim.x) items[e] = b.items[(size_t)bin * b.cap + e];
+    for (int e = threadIdx.x; e < kWpL * kWpL; e += blockDim.x) {
+        lw[e] = 0ull;
+        lz[e] = 0ull;
+    }
+    __syncthreads();
+    const int wx0 = (bin % b.tiles_x) * 16 - kWpM, wy0 = (bin / b.tiles_x) * 16 - kWpM;
+    constexpr int kWpF = 4;
+    for (int i0 = 0; i0 < m; i0 += kWpF) {
+        float wg[kWpF], zg[kWpF];
+        uint32_t it[kWpF];
+#pragma unroll
+        for (int j = 0; j < kWpF; ++j) {
+            it[j] = __builtin_amdgcn_readfirstlane(items[min(i0 + j, m - 1)]);
+            load(it[j], wg[j], zg[j]);
+            if (i0 + j >= m) wg[j] = 0.0f;
+        }
+#pragma unroll
+        for (int j = 0; j < kWpF; ++j) {
+            if (!(wg[j] > 0.0f)) continue;
+            int iu, iv;
+            long long wk, zk;
+            if (!warp(it[j], wg[j], zg[j], iu, iv, wk, zk)) continue;
+            const int lx = iu - wx0, ly = iv - wy0;
+            if ((unsigned)lx < (unsigned)kWpL && (unsigned)ly < (unsigned)kWpL) {
+                atomicAdd(&lw[ly * kWpL + lx], (unsigned long long)wk);
+                atomicAdd(&lz[ly * kWpL + lx], (unsigned long long)(wk * zk));
+            } else {
+                add(iu, iv, wk, zk);
+            }
+        }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < kWpL * kWpL; e += blockDim.x) {
+        const unsigned long long a = lw[e];
+        if (a != 0ull) {
+            // only samples inside the image were added, so the pixel is too
+            const int64_t t = (int64_t)(wy0 + e / kWpL) * W + (wx0 + e % kWpL);
+            atomicAdd(KW + t, a);
+            atomicAdd(KZ + t, lz[e]);
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // colour pre-processing
 // ---------------------------------------------------------------------------
@@ -527,6 +720,12 @@ __global__ __launch_bounds__(256) void fuse_front_kernel(sc_intrinsics in, sc_fu
             init.fr->Rb[i / 12][i % 12] = init.poses.Rb[i / 12][i % 12];
         }
         for (int i = threadIdx.x; i < init.count; i += blockDim.x) init.fr->Z[i] = init.poses.Z[i];
+    }
+    if (f == 0 && init.bins.count && threadIdx.x < 5) {
+        // the tile's four keyframe tiles (64 x 16 pixels), and the overflow's length
+        const int bx = 4 * (tile % dw_x) + (int)threadIdx.x, by = tile / dw_x;
+        if (threadIdx.x < 4 && bx < init.bins.tiles_x) init.bins.count[by * init.bins.tiles_x + bx] = 0u;
+        if (threadIdx.x == 4 && tile == 0) init.bins.count[init.bins.tiles] = 0u;
     }
     const float* Z = init.Z0 ? init.Z0 + (size_t)f * in.width * in.height
                              : f < init.count ? init.poses.Z[f] : init.fr->Z[f];
@@ -749,6 +948,8 @@ struct FuseWs {
     unsigned long long* acc = nullptr;   // KW, KZ
     long long* parts = nullptr;          // 4 per colour-prep tile and frame
     size_t cap_parts = 0;
+    uint32_t* bins = nullptr;            // source tiles by keyframe tile (bins_words)
+    size_t cap_bins = 0;
     double* wb = nullptr;
     FuseFrames* d_fr = nullptr;
 };
@@ -759,8 +960,9 @@ static FuseWs g_ws;
 static int prep_tiles_x(int W) { return (W + kPrepTW - 1) / kPrepTW; }
 static int prep_tiles(int W, int H) { return prep_tiles_x(W) * ((H + kPrepTH - 1) / kPrepTH); }
 
-// np pixels per frame, frames frames, parts int64 colour-prep partials.
-static sc_status ws_reserve(size_t np, size_t frames, size_t parts)
+// np pixels per frame, frames frames, parts int64 colour-prep partials, bins
+// words of tile lists.
+static sc_status ws_reserve(size_t np, size_t frames, size_t parts, size_t bins)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return SC_EDEVICE;
@@ -772,6 +974,8 @@ static sc_status ws_reserve(size_t np, size_t frames, size_t parts)
         g_ws.acc = nullptr;
         g_ws.parts = nullptr;
         g_ws.cap_parts = 0;
+        g_ws.bins = nullptr;
+        g_ws.cap_bins = 0;
         g_ws.wb = nullptr;
         g_ws.d_fr = nullptr;
         g_ws.device = dev;
@@ -804,6 +1008,14 @@ static sc_status ws_reserve(size_t np, size_t frames, size_t parts)
         g_ws.cap_parts = 0;
         if (hipMalloc(&g_ws.parts, sizeof(long long) * parts) != hipSuccess) return SC_ENOMEM;
         g_ws.cap_parts = parts;
+    }
+    if (bins > g_ws.cap_bins) {
+        if (hipDeviceSynchronize() != hipSuccess) return SC_EDEVICE;
+        (void)hipFree(g_ws.bins);
+        g_ws.bins = nullptr;
+        g_ws.cap_bins = 0;
+        if (hipMalloc(&g_ws.bins, sizeof(uint32_t) * bins) != hipSuccess) return SC_ENOMEM;
+        g_ws.cap_bins = bins;
     }
     return SC_OK;
 }
@@ -924,7 +1136,26 @@ struct FuseBufs {
     long long* parts;
     double* wb;
     FuseFrames* fr;
+    uint32_t* bins;  // bins_words, or null
 };
+
+static size_t bins_words(int n, int W, int H)
+{
+    const size_t tiles = (size_t)((W + 15) / 16) * ((H + 15) / 16);
+    return n > kWarpFew ? tiles * (1 + 3 * (size_t)n) + 1 : 0;
+}
+
+static WarpBins warp_bins(uint32_t* words, int n, const sc_intrinsics& in)
+{
+    WarpBins b;
+    b.tiles_x = (in.width + 15) / 16;
+    b.tiles = b.tiles_x * ((in.height + 15) / 16);
+    b.cap = 2 * n;
+    b.count = words;
+    b.items = words + b.tiles + 1;
+    b.over = b.items + (size_t)b.tiles * b.cap;
+    return b;
+}
 
 // The fusion kernels of one keyframe.  The relative poses of the first
 // kStageFrames frames travel in the first launch; those of later
@@ -937,6 +1168,8 @@ static void launch_fuse(const FuseBufs& b, const float* const* depth, const uint
     FuseInit init;
     init.acc = b.acc;
     init.fr = b.fr;
+    const WarpBins bins = n_frames > kWarpFew && b.bins ? warp_bins(b.bins, n_frames, in) : WarpBins{};
+    init.bins = bins;
     init.Z0 = depth[0];
     init.C0 = rgb[0];
     for (int i = 1; i < n_frames; ++i) {
@@ -959,11 +1192,18 @@ static void launch_fuse(const FuseBufs& b, const float* const* depth, const uint
     const int pt = prep_tiles(in.width, in.height), dt = dw_tiles(in.width, in.height);
     fuse_front_kernel<<<dim3((unsigned)(pt + dt), (unsigned)n_frames), 256, 0, s>>>(
         in, params, prep_tiles_x(in.width), pt, dw_tiles_x(in.width), b.cs, b.parts, b.wz, init);
-    // target tiles over the image and kWpE more on each side
-    const int wtx = (in.width + kWpT - 1) / kWpT + 2 * kWpE, wty = (in.height + kWpT - 1) / kWpT + 2 * kWpE;
-    const float z_nom = 0.5f * (params.z_min + params.z_max);
-    warp_kernel<<<(unsigned)(n_frames + wtx * wty), 256, 0, s>>>(b.wz, n_frames, in, z_nom, wtx, b.fr, b.acc,
-                                                                 b.acc + np, b.parts, pt, b.wb);
+    if (bins.count) {
+        warp_bin_kernel<<<(unsigned)(((int64_t)n_frames * bins.tiles + 255) / 256), 256, 0, s>>>(n_frames, in, params,
+                                                                                                 b.fr, bins);
+        warp_bins_kernel<<<(unsigned)(n_frames + bins.tiles + kWpOver), 256, 0, s>>>(
+            b.wz, n_frames, in, b.fr, b.acc, b.acc + np, b.parts, pt, b.wb, bins);
+    } else {
+        // target tiles over the image and kWpE more on each side
+        const int wtx = (in.width + kWpT - 1) / kWpT + 2 * kWpE, wty = (in.height + kWpT - 1) / kWpT + 2 * kWpE;
+        const float z_nom = 0.5f * (params.z_min + params.z_max);
+        warp_kernel<<<(unsigned)(n_frames + wtx * wty), 256, 0, s>>>(b.wz, n_frames, in, z_nom, wtx, b.fr, b.acc,
+                                                                     b.acc + np, b.parts, pt, b.wb);
+    }
     const unsigned long long *KW = b.acc, *KZ = b.acc + np;
     auto color = [&](auto n) {
         color_kernel<decltype(n)::value><<<(unsigned)((np + 255) / 256), 256, 0, s>>>(
@@ -993,8 +1233,11 @@ static void launch_fuse(const FuseBufs& b, const float* const* depth, const uint
 // device with hipGetSymbolAddress and only that address is passed on.  Every
 // call on a device shares that device's copy, so calls that overlap on one
 // device race.
-// 76 MiB for the images and 1 KiB for the frames' addresses.
-constexpr size_t kScratchBytes = (size_t(76) << 20) + sizeof(FuseFrames::Z) + sizeof(FuseFrames::C);
+// 76 MiB for the images and 1 KiB for the frames' addresses decide what a call
+// takes; the source tiles' lists (under a hundredth of the images of a call
+// that large) come after them.
+constexpr size_t kScratchImages = (size_t(76) << 20) + sizeof(FuseFrames::Z) + sizeof(FuseFrames::C);
+constexpr size_t kScratchBytes = kScratchImages + (size_t(2) << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -1075,7 +1318,7 @@ sc_status sc_color_prep(const uint8_t* rgb, int32_t n_frames, int32_t width, int
         return SC_EINVAL;
     std::lock_guard<std::mutex> lk(g_ws.mu);
     const sc_status st =
-        ws_reserve((size_t)width * height, (size_t)n_frames, 4 * (size_t)prep_tiles(width, height) * n_frames);
+        ws_reserve((size_t)width * height, (size_t)n_frames, 4 * (size_t)prep_tiles(width, height) * n_frames, 0);
     if (st != SC_OK) return st;
     const int tiles = prep_tiles(width, height);
     color_prep_kernel<<<dim3((unsigned)tiles, (unsigned)n_frames), 256, 0, (hipStream_t)stream>>>(
@@ -1097,9 +1340,10 @@ sc_status kf_fuse_frames(const float* const* depth, const uint8_t* const* rgb, c
     const sc_intrinsics in = *intr;
     const int64_t np = (int64_t)in.width * in.height;
     std::lock_guard<std::mutex> lk(g_ws.mu);
-    sc_status st = ws_reserve((size_t)np, (size_t)n_frames, 4 * (size_t)prep_tiles(in.width, in.height) * n_frames);
+    sc_status st = ws_reserve((size_t)np, (size_t)n_frames, 4 * (size_t)prep_tiles(in.width, in.height) * n_frames,
+                              bins_words(n_frames, in.width, in.height));
     if (st != SC_OK) return st;
-    const FuseBufs b{g_ws.wz, g_ws.cs, g_ws.acc, g_ws.parts, g_ws.wb, g_ws.d_fr};
+    const FuseBufs b{g_ws.wz, g_ws.cs, g_ws.acc, g_ws.parts, g_ws.wb, g_ws.d_fr, g_ws.bins};
     launch_fuse(b, depth, rgb, poses, n_frames, ref, in, *params, kf_depth, kf_weight, kf_rgba, s);
     return hipGetLastError() == hipSuccess ? SC_OK : SC_EDEVICE;
 }
@@ -1128,11 +1372,14 @@ sc_status kf_fuse_noalloc(const float* depth, const uint8_t* rgb, const sc_pose*
     const size_t np = (size_t)in.width * in.height;
     const size_t parts = 4 * (size_t)prep_tiles(in.width, in.height) * n_frames;
     FuseBufs b;
-    if (fuse_layout(nullptr, np, (size_t)n_frames, parts, b) > kScratchBytes) return SC_ESCRATCH;
+    size_t bytes = fuse_layout(nullptr, np, (size_t)n_frames, parts, b);
+    if (bytes > kScratchImages) return SC_ESCRATCH;
     unsigned char* base = nullptr;
     const sc_status st = scratch_address(&base);
     if (st != SC_OK) return st;
     fuse_layout(base, np, (size_t)n_frames, parts, b);
+    const size_t lists = sizeof(uint32_t) * bins_words(n_frames, in.width, in.height);
+    b.bins = lists > 0 && bytes + lists <= kScratchBytes ? reinterpret_cast<uint32_t*>(base + bytes) : nullptr;
     launch_fuse(b, Z, C, poses, n_frames, ref, in, *params, kf_depth, kf_weight, kf_rgba, s);
     return hipGetLastError() == hipSuccess ? SC_OK : SC_EDEVICE;
 }

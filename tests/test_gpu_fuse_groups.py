@@ -1,6 +1,6 @@
-"""Keyframe fusion over the group's size, and the packed records, against the
-oracle (bit-exact: integers and FP32 values decided by the same written
-operations)."""
+"""Keyframe fusion over the group's size and the frames' displacement, frames
+where they lie, and the packed records, against the oracle (bit-exact:
+integers and FP32 values decided by the same written operations)."""
 import numpy as np
 import pytest
 import torch
@@ -107,3 +107,29 @@ def test_frames_that_cannot_be_fused_where_they_lie():
         with pytest.raises(ValueError):
             scsurf.kf_fuse_frames(bad, cl, R, t, intr)
     assert not scsurf.frames_fusible(zl, [cl[0], cl[1].int()])
+
+
+@pytest.mark.parametrize("W,H,few", [(100, 50, False), (161, 96, False), (100, 50, True), (33, 17, False)])
+def test_warp_displacements(W, H, few):
+    """Frames displaced by whole images: sideways to and past the image on
+    every side, turned by up to 30 degrees and right round (one whose centre
+    has no projection); depths of two planes, so that tiles' samples part; and
+    many frames at one place, past what a keyframe tile's list holds."""
+    print(f"[gpu] displaced frames {W}x{H}", flush=True)
+    n = 12
+    intr, z, rgb, R, t = _plane_frames(W, H, n, W)
+    w = 2.1 * 0.5 * (W - 1) / intr.fx  # about one image at the nominal depth
+    moves = [(0, 0), (0.2 * w, 0), (-0.9 * w, 0.1), (1.0 * w, 0), (-1.3 * w, 0), (0, 0.4 * w), (0, -0.6 * w), (3 * w, w)]
+    for f, (dx, dy) in enumerate(moves):
+        t[f] = t[f] + np.array([dx, dy, 0.0])
+    for f, deg in ((8, 10.0), (9, -30.0), (10, 90.0), (11, 180.0)):
+        a = np.radians(deg)
+        R[f] = np.array([[np.cos(a), 0, np.sin(a)], [0, 1, 0], [-np.sin(a), 0, np.cos(a)]])
+    z[:, :, ::7] *= np.float32(1.6)  # within a tile
+    z[5, :16, :16] = 0.0  # a tile without depth
+    sel = np.arange(8) if few else np.concatenate([np.arange(n), np.zeros(30, int), np.full(10, 7)])
+    z, rgb, R, t = z[sel], rgb[sel], R[sel], t[sel]
+    kf = scsurf.kf_fuse(torch.from_numpy(z).cuda(), torch.from_numpy(rgb).cuda(), R, t, intr)
+    ref = oracle.kf_fuse(z, rgb, intr, R, t)
+    _check(kf, ref)
+    assert (ref["weight"] > 0).mean() > 0.3
