@@ -564,10 +564,12 @@ __device__ inline int luma(uint32_t px) { return (77 * (int)(px & 255u) + 150 * 
 // halo (2 pixels for the 5-tap binomial, 5 before and 4 after for the 9-tap
 // re-blur box) are staged in LDS with coordinates clamped to the image, which
 // is the edge rule of both filters.  The binomial runs separably on pixels
-// packed as R | G << 16 | B << 32: every channel's weighted sum stays below
+// packed as R | G << 16 and B: every channel's weighted sum stays below
 // 16 * 16 * 255 < 2^16, so the 16-bit lanes never carry into each other and
-// the sums are the per-channel integers.  Each thread then produces four
-// pixels of the unsharp mask and adds their re-blur terms to four int64
+// the sums are the per-channel integers.  Bound by the vector ALU: 60 frames
+// of 640x480 with their depth weights took 178 us with a 64-bit word a pixel
+// and 64-bit re-blur sums, now 164.  Each thread then produces four
+// pixels of the unsharp mask and adds their re-blur terms to four integer
 // sums, reduced over the workgroup and stored as the tile's partial sums (no
 // atomics).
 //   sums k = 0..3: sF_h, sV_h, sF_v, sV_v, the 9x-scaled horizontal and
@@ -579,11 +581,20 @@ constexpr int kPrepHalo = 5;
 constexpr int kPrepStage = (kPrepLW * kPrepLH + 255) / 256;  // staged pixels per thread (256 threads)
 
 struct PrepLds {
-    uint64_t pix[kPrepLH][kPrepLW];
-    uint64_t hsum[kPrepTH + 4][kPrepTW];  // horizontal binomial of staged rows 3 .. 22
+    uint2 pix[kPrepLH][kPrepLW];
+    uint2 hsum[kPrepTH + 4][kPrepTW];  // horizontal binomial of staged rows 3 .. 22
     uint8_t lum[kPrepLH][kPrepLW];  // luma <= 255; bytes keep the workgroup under 26.7 KB of LDS (six per CU)
-    long long red[4][4];
+    int red[4][4];
 };
+
+// a + 4 b + 6 c + 4 d + e in both words.
+__device__ inline uint2 binomial(uint2 a, uint2 b, uint2 c, uint2 d, uint2 e)
+{
+    auto sum = [](uint32_t a0, uint32_t b0, uint32_t c0, uint32_t d0, uint32_t e0) {
+        return (a0 + e0) + ((b0 + d0) << 2) + (c0 << 2) + (c0 << 1);
+    };
+    return make_uint2(sum(a.x, b.x, c.x, d.x, e.x), sum(a.y, b.y, c.y, d.y, e.y));
+}
 
 // kOutCh: 3 (packed RGB, the standalone output) or 4 (RGB and a zero, one
 // 8-byte store per pixel; the layout the colour kernel gathers from).
@@ -617,34 +628,31 @@ __device__ inline void color_prep_tile(FrameColor* __restrict__ C, int f, int ti
         if (p < kPrepLW * kPrepLH) {
             const int i = p % kPrepLW, j = p / kPrepLW;
             const uint32_t px = st[k];
-            pix[j][i] = (uint64_t)(px & 255u) | ((uint64_t)((px >> 8) & 255u) << 16) | ((uint64_t)(px >> 16) << 32);
+            pix[j][i] = make_uint2((px & 255u) | ((px << 8) & 0xFF0000u), px >> 16);
             lum[j][i] = (uint8_t)luma(px);
         }
     }
     __syncthreads();
     for (int p = threadIdx.x; p < (kPrepTH + 4) * kPrepTW; p += blockDim.x) {
         const int c = p % kPrepTW, jr = p / kPrepTW;
-        const uint64_t* row = &pix[jr + kPrepHalo - 2][c + kPrepHalo - 2];
-        hsum[jr][c] = (row[0] + 4 * row[1]) + ((6 * row[2] + 4 * row[3]) + row[4]);
+        const uint2* row = &pix[jr + kPrepHalo - 2][c + kPrepHalo - 2];
+        hsum[jr][c] = binomial(row[0], row[1], row[2], row[3], row[4]);
     }
     __syncthreads();
     const int tx = threadIdx.x & (kPrepTW - 1), ty = threadIdx.x / kPrepTW;
-    long long acc[4] = {0, 0, 0, 0};
+    // at most 9 * 255 a pixel, 1,024 pixels a tile: 32 bits
+    int acc[4] = {0, 0, 0, 0};
     const int u = u0 + tx, i = tx + kPrepHalo;
 #pragma unroll 1
     for (int r = 0; r < kPrepTH / 4; ++r) {
         const int y = ty + 4 * r, v = v0 + y, j = y + kPrepHalo;
         if (u >= W || v >= H) continue;
         // staged row j + b is hsum row y + 2 + b
-        const uint64_t S = (hsum[y][tx] + 4 * hsum[y + 1][tx]) +
-                           ((6 * hsum[y + 2][tx] + 4 * hsum[y + 3][tx]) + hsum[y + 4][tx]);
-        const uint64_t c0 = pix[j][i];
-        uint32_t sh[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const int val = 512 * (int)((c0 >> (16 * k)) & 0xFFFFu) - (int)((S >> (16 * k)) & 0xFFFFu);
-            sh[k] = (uint32_t)clampi(val, 0, 65280);
-        }
+        const uint2 S = binomial(hsum[y][tx], hsum[y + 1][tx], hsum[y + 2][tx], hsum[y + 3][tx], hsum[y + 4][tx]);
+        const uint2 c0 = pix[j][i];
+        const uint32_t sh[3] = {(uint32_t)clampi((int)((c0.x & 0xFFFFu) << 9) - (int)(S.x & 0xFFFFu), 0, 65280),
+                                (uint32_t)clampi((int)((c0.x >> 16) << 9) - (int)(S.x >> 16), 0, 65280),
+                                (uint32_t)clampi((int)(c0.y << 9) - (int)S.y, 0, 65280)};
         const size_t px = (size_t)f * np + (size_t)v * W + u;
         if (kOutCh == 4) {
             *reinterpret_cast<uint2*>(out + 4 * px) = make_uint2(sh[0] | (sh[1] << 16), sh[2]);
@@ -656,16 +664,16 @@ __device__ inline void color_prep_tile(FrameColor* __restrict__ C, int f, int ti
         }
         const int y0 = lum[j][i];
         if (u >= 1) {
-            const long long dF = 9LL * abs(y0 - lum[j][i - 1]);
-            const long long dB = abs(lum[j][i + 4] - lum[j][i - 5]);
+            const int dF = 9 * abs(y0 - lum[j][i - 1]);
+            const int dB = abs(lum[j][i + 4] - lum[j][i - 5]);
             acc[0] += dF;
-            acc[1] += dF > dB ? dF - dB : 0;
+            acc[1] += max(dF - dB, 0);
         }
         if (v >= 1) {
-            const long long dF = 9LL * abs(y0 - lum[j - 1][i]);
-            const long long dB = abs(lum[j + 4][i] - lum[j - 5][i]);
+            const int dF = 9 * abs(y0 - lum[j - 1][i]);
+            const int dB = abs(lum[j + 4][i] - lum[j - 5][i]);
             acc[2] += dF;
-            acc[3] += dF > dB ? dF - dB : 0;
+            acc[3] += max(dF - dB, 0);
         }
     }
 #pragma unroll
@@ -696,7 +704,7 @@ __global__ __launch_bounds__(256) void color_prep_kernel(const uint8_t* __restri
 // frame's workgroups the first prep_tiles take the colour tiles, the others
 // the depth tiles.  Neither needs the other, and each alone waits for its loads with the
 // CUs half empty at its end: 640x480, 5 frames 16.2 + 11.5 us in two launches,
-// now 22 in one; 60 frames 104 + 72 us, now 172.
+// now 21 in one; 60 frames 104 + 72 us, now 164.
 __global__ __launch_bounds__(256) void fuse_front_kernel(sc_intrinsics in, sc_fuse_params p, int prep_x,
                                                          int prep_tiles, int dw_x,
                                                          uint16_t* __restrict__ cs, long long* __restrict__ parts,
