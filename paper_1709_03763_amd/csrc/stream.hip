@@ -558,8 +558,8 @@ void stream_clear(sc_volume* vol)
     size_t n = 0, bytes = 0;
     while (n < st->chunks.size() && bytes + st->chunks[n].second * st->block_bytes <= kKeepBytes)
         bytes += st->chunks[n++].second * st->block_bytes;
-    if (n < st->chunks.size()) {
-        (void)hipEventSynchronize(st->done);  // a kernel may still read them
+    // a kernel may still read the others: kept where that cannot be waited for
+    if (n < st->chunks.size() && hipEventSynchronize(st->done) == hipSuccess) {
         for (size_t c = n; c < st->chunks.size(); ++c) (void)hipHostFree(st->chunks[c].first);
         st->chunks.resize(n);
     }
