@@ -8,6 +8,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "pixel.hpp"
 
 namespace sc {
 
@@ -290,19 +291,19 @@ __device__ inline float pixel_coord_rint(float a, float z, float r, float c, flo
 
 // The projection constants of one operation, read together.
 struct ProjConst {
-    float fx, fy, cx, cy, kin_u, kin_v, wl, hl, wf;
+    float fx, fy, cx, cy, kin_u, kin_v, wl, hl;
+    uint32_t width;
 };
 
 __device__ inline ProjConst proj_const(const OpDesc& op)
 {
-    return {op.fx, op.fy, op.cx, op.cy, op.kin_u, op.kin_v, op.wl, op.hl, op.wf};
+    return {op.fx, op.fy, op.cx, op.cy, op.kin_u, op.kin_v, op.wl, op.hl, (uint32_t)op.width};
 }
 
 // The nearest pixel without branches around it, with pixel_coord_rint: the
 // pixel index (0 when `in` is false: behind the camera or outside the
 // image).  A lane behind the camera projects with z = 1 so that its
-// coordinates stay finite.  The index fv W + fu is an integer below 2^24, so
-// one FP32 fma forms it exactly.
+// coordinates stay finite.
 __device__ inline uint32_t pixel_index_fast(const ProjConst& k, float px, float py, float pz, bool& in)
 {
     const bool front = pz > 0.0f;
@@ -312,7 +313,7 @@ __device__ inline uint32_t pixel_index_fast(const ProjConst& k, float px, float 
     const float fv = pixel_coord_rint(k.fy * py, zs, r, k.cy, k.kin_v, k.hl);
     // bitwise, not short-circuit: no branches
     in = front & (fu >= 0.0f) & (fu <= k.wl) & (fv >= 0.0f) & (fv <= k.hl);
-    const uint32_t p = (uint32_t)fmaf(fv, k.wf, fu);
+    const uint32_t p = pixel_index(fu, fv, k.width);
     return in ? p : 0u;
 }
 
