@@ -48,26 +48,20 @@ __device__ inline void batch_init(const OpDesc* __restrict__ ops, const BatchHdr
     for (int i = threadIdx.x; i < 2 * n_bins; i += blockDim.x) cd.bins[i] = 0u;
     for (int i = threadIdx.x; i < hdr->n_ops * kRecShards; i += blockDim.x) {
         const OpDesc& op = ops[i / kRecShards];
-        if (op.rec_mode == 1) op.rec_count[(i % kRecShards) * kRecCountStride] = 0u;
+        if (op.rec_mode == 1) record_clear(op, i % kRecShards);
     }
 }
 
 // A de-integration whose touched-block record is complete takes its
 // candidates from the record instead of from frustum cells.
-__device__ inline bool uses_record(const OpDesc& op)
-{
-    if (op.rec_mode != 2) return false;
-    // one part a lane, read together (every lane of the wavefront is active)
-    const uint32_t c = op.rec_count[((int)threadIdx.x % kRecShards) * kRecCountStride];
-    return __ballot(c > (uint32_t)op.rec_cap) == 0ull;
-}
+__device__ inline bool uses_record(const OpDesc& op) { return op.rec_mode == 2 && op.rec_count[kRecLost] == 0u; }
 
 // Candidate blocks of de-integrations from their records: every recorded
 // block is claimed in the candidate table and marked with the operation's
 // bit.  Workgroup (x, y) takes operations y, y + gridDim.y, ... and, of each,
-// part x of the record.  A record with a part that overflowed its capacity is
-// not used: the operation's frustum-cell tiles are generated here instead,
-// tile x, x + gridDim.x, ...
+// part x of the record.  A record that overflowed its capacity is not used:
+// the operation's frustum-cell tiles are generated here instead, tile x,
+// x + gridDim.x, ...
 __global__ __launch_bounds__(256) void cand_record_kernel(const OpDesc* __restrict__ ops, const BatchHdr* hdr,
                                                           VolDev v, CandDev cd, int n_bins)
 {
@@ -93,7 +87,7 @@ __global__ __launch_bounds__(256) void cand_record_kernel(const OpDesc* __restri
             }
             continue;
         }
-        const uint32_t n = op.rec_count[blockIdx.x * kRecCountStride];
+        const uint32_t n = min(op.rec_count[blockIdx.x * kRecCountStride], (uint32_t)op.rec_cap);
         for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
             const uint64_t key = op.rec_keys[(size_t)blockIdx.x * op.rec_cap + i];
             int bx, by, bz;
@@ -807,9 +801,8 @@ __device__ inline void record_flush(const OpDesc* __restrict__ ops, PipeBlock& p
 {
     if ((uint32_t)lane < pb.n_rec) {
         const OpDesc& o = ops[pb.rec_op];
-        const uint32_t pos = atomicAdd(o.rec_count + pb.shard * kRecCountStride, 1u);
-        if (pos < (uint32_t)o.rec_cap)
-            o.rec_keys[(size_t)pb.shard * o.rec_cap + pos] = pack_key(pb.bx, pb.by, pb.bz);
+        record_put(o, pb.shard, atomicAdd(o.rec_count + pb.shard * kRecCountStride, 1u),
+                   pack_key(pb.bx, pb.by, pb.bz));
     }
     pb.n_rec = 0u;
 }

@@ -78,13 +78,15 @@ struct OpDesc {
     // the same pose touches the same blocks) when the record did not
     // overflow; rec_mode 0: no record.
     // In kRecShards parts, so that the appends of a pass spread over as many
-    // counters: part p holds up to rec_cap keys from rec_keys + p rec_cap.
+    // counters: part p holds up to rec_cap keys from rec_keys + p rec_cap, and
+    // an append that finds its part full goes on to the others (record_put).
     uint64_t* rec_keys;
-    uint32_t* rec_count;  // appended to part p so far, at p kRecCountStride (may exceed rec_cap: overflowed)
+    uint32_t* rec_count;  // part p: appends tried, at p kRecCountStride (may exceed rec_cap: full); then kRecLost
     int32_t rec_cap;
 };
 constexpr int kRecShards = 16;
 constexpr int kRecCountStride = 32;  // one counter per 128 bytes
+constexpr int kRecLost = 1;          // word of rec_count: a key found every part full, the record is not used
 static_assert(offsetof(OpDesc, za) == 64, "projection constants of OpDesc: za at byte 64");
 
 // Device view of a volume.

@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256) void cand_plain_kernel(OpDesc op, VolDev v, Ca
     }
     // the integration's record starts empty
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kRecShards && op.rec_mode == 1)
-        op.rec_count[threadIdx.x * kRecCountStride] = 0u;
+        record_clear(op, (int)threadIdx.x);
     cand_tile<kTilePlain, kCellPlain>(op, v, cd, cd.counters + parity, blockIdx.x, blockIdx.y, -1, lds, idx);
 }
 
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256) void cand_plain_kernel(OpDesc op, VolDev v, Ca
 // keyframe samples together, then the voxels four slices at a time: all eight
 // at once take 169 registers, or spill).  640x480 keyframe: 1 cm voxels, in an
 // online session, 79 -> 27 us; 5 mm voxels 86 -> 24 us.
-constexpr int kPlainRec = 16;  // recorded blocks a wavefront holds: 65,536 candidates with 1024 workgroups
+constexpr int kPlainRec = 16;  // recorded blocks a wavefront holds; appended by itself when there are more
 
 template <int CM, bool kPacked>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void update_plain_kernel(OpDesc op, VolDev v, CandDev cd, int parity)
@@ -216,6 +216,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void u
     const int wave = (int)bcast(threadIdx.x >> 6);
     const uint32_t n = min(cd.counters[parity], cd.cap);
     const uint32_t n_workers = gridDim.x * 4u;
+    const uint32_t shard = blockIdx.x % kRecShards;
     uint32_t held = 0u;  // recorded blocks not yet appended
     bool bad = false;
     for (uint32_t i = blockIdx.x * 4u + (uint32_t)wave; i < n; i += n_workers) {
@@ -239,8 +240,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void u
         cd.keys[h] = kKeyEmpty;
         if (__ballot(any) == 0ull) continue;
         if (op.rec_mode == 1) {
-            if (held < (uint32_t)kPlainRec) rec[wave][held] = key;  // every lane, the same value
-            ++held;
+            if (held == (uint32_t)kPlainRec) {
+                wave_lds_sync();
+                uint32_t at = 0u;
+                if (lane == 0) at = atomicAdd(op.rec_count + shard * kRecCountStride, held);
+                at = bcast(at);
+                if ((uint32_t)lane < held) record_put(op, shard, at + (uint32_t)lane, rec[wave][lane]);
+                held = 0u;
+            }
+            rec[wave][held++] = key;  // every lane, the same value
         }
         if (slot < 0 && op.sign > 0) slot = vol_insert_wave(v, key, bx, by, bz, lane);
         if (slot < 0) {
@@ -304,22 +312,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void u
     if (op.rec_mode != 1) return;
     if (lane == 0) rec_n[wave] = held;
     __syncthreads();
-    uint32_t sum = 0u, most = 0u, before = 0u;
+    uint32_t sum = 0u, before = 0u;
     for (int q = 0; q < 4; ++q) {
         before += q < wave ? rec_n[q] : 0u;
         sum += rec_n[q];
-        most = max(most, rec_n[q]);
     }
     if (sum == 0u) return;
-    // more than a wavefront holds: the record counts as overflowed and is not used
-    const bool over = most > (uint32_t)kPlainRec;
-    const uint32_t shard = blockIdx.x % kRecShards;
-    if (threadIdx.x == 0)
-        rec_base = atomicAdd(op.rec_count + shard * kRecCountStride, over ? (uint32_t)op.rec_cap + 1u : sum);
+    if (threadIdx.x == 0) rec_base = atomicAdd(op.rec_count + shard * kRecCountStride, sum);
     __syncthreads();
-    const uint32_t pos = rec_base + before + (uint32_t)lane;
-    if (!over && (uint32_t)lane < held && pos < (uint32_t)op.rec_cap)
-        op.rec_keys[(size_t)shard * op.rec_cap + pos] = rec[wave][lane];
+    if ((uint32_t)lane < held) record_put(op, shard, rec_base + before + (uint32_t)lane, rec[wave][lane]);
 }
 
 // Writes imported block records into their pool slots (D widened to FP64;
