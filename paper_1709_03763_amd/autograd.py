@@ -103,14 +103,16 @@ class TsdfIntegrate(torch.autograd.Function):
 
         # one batched call gives the field of the calls one by one, bit for
         # bit: 16 keyframes of 320x240 in 350 us instead of 675.  Its candidate
-        # table holds all keyframes' blocks at once (and a streamed pool those
-        # of a chunk), so where it fails the calls are made one by one.
+        # table holds all keyframes' blocks at once, and a streamed pool those of
+        # a chunk, for which it may send others to the host, out of the export's
+        # and the backward's reach: where it fails or does so the calls are made
+        # one by one.
         start()
         batched = False
         if len(kfs) > 1:
             try:
                 volume.integrate_batch(kfs, intr, Rp, tp)
-                batched = volume.query()[1] == scsurf.SC_OK
+                batched = volume.query()[1] == scsurf.SC_OK and volume.host_blocks() == 0
             except scsurf.ScError:
                 pass
             if not batched:

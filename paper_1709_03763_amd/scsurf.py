@@ -374,12 +374,17 @@ class Volume:
             raise ScError(SC_EDEVICE, "sc_volume_mesh: triangle count changed between calls")
         return xyz[:T], keys[:T]
 
+    def host_blocks(self) -> int:
+        """Number of blocks held by the host store (streaming mode)."""
+        n = ctypes.c_int64()
+        check(lib().sc_stream_export(self._h, None, None, None, None, 0, ctypes.byref(n)), "sc_stream_export")
+        return int(n.value)
+
     def stream_export(self):
         """Blocks held by the host store (streaming mode): dict of NumPy
         arrays in export's layout."""
+        m = self.host_blocks()
         n = ctypes.c_int64()
-        check(lib().sc_stream_export(self._h, None, None, None, None, 0, ctypes.byref(n)), "sc_stream_export")
-        m = int(n.value)
         xyz = np.zeros((m, 3), np.int32)
         D = np.zeros((m, 512), np.float32)
         W = np.zeros((m, 512), np.float32)
