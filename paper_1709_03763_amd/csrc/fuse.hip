@@ -956,7 +956,7 @@ struct FuseWs {
     unsigned long long* acc = nullptr;   // KW, KZ
     long long* parts = nullptr;          // 4 per colour-prep tile and frame
     size_t cap_parts = 0;
-    uint32_t* bins = nullptr;            // source tiles by keyframe tile (bins_words)
+    uint32_t* bins = nullptr;            // source tiles by keyframe tile (bins_words), or null
     size_t cap_bins = 0;
     double* wb = nullptr;
     FuseFrames* d_fr = nullptr;
@@ -968,9 +968,26 @@ static FuseWs g_ws;
 static int prep_tiles_x(int W) { return (W + kPrepTW - 1) / kPrepTW; }
 static int prep_tiles(int W, int H) { return prep_tiles_x(W) * ((H + kPrepTH - 1) / kPrepTH); }
 
-// np pixels per frame, frames frames, parts int64 colour-prep partials, bins
-// words of tile lists.
-static sc_status ws_reserve(size_t np, size_t frames, size_t parts, size_t bins)
+// Words of tile lists of n frames of W x H pixels.
+static size_t bins_words(int n, int W, int H)
+{
+    const size_t tiles = (size_t)((W + 15) / 16) * ((H + 15) / 16);
+    return n > kWarpFew ? tiles * (1 + 3 * (size_t)n) + 1 : 0;
+}
+
+// At least bins_words of every W x H <= px and n W H <= total (W, H >= 3,
+// n <= kMaxFrames): a W x H image has at most (W + 15) (H + 15) / 256 tiles, W
+// + H is at most W H / 3 + 3, so at most 6 W H / 256 + 2 tiles.
+static size_t bins_bound(size_t px, size_t total)
+{
+    return (6 * px + 18 * total) / 256 + 6 * kMaxFrames + 4;
+}
+
+// np pixels per frame, frames frames, parts int64 colour-prep partials.  The
+// tile lists come with the images, for whatever fits those, so that no later
+// call allocates for them (one under capture cannot); without memory for them
+// the warp goes without.
+static sc_status ws_reserve(size_t np, size_t frames, size_t parts)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return SC_EDEVICE;
@@ -1008,6 +1025,14 @@ static sc_status ws_reserve(size_t np, size_t frames, size_t parts, size_t bins)
         if (hipMalloc(&g_ws.acc, sizeof(unsigned long long) * 2 * px) != hipSuccess) return SC_ENOMEM;
         g_ws.cap_px = px;
         g_ws.cap_frames = fr;
+        (void)hipFree(g_ws.bins);
+        g_ws.bins = nullptr;
+        g_ws.cap_bins = bins_bound(px, px * fr);
+        if (hipMalloc(&g_ws.bins, sizeof(uint32_t) * g_ws.cap_bins) != hipSuccess) {
+            (void)hipGetLastError();
+            g_ws.bins = nullptr;
+            g_ws.cap_bins = 0;
+        }
     }
     if (parts > g_ws.cap_parts) {
         if (hipDeviceSynchronize() != hipSuccess) return SC_EDEVICE;
@@ -1016,14 +1041,6 @@ static sc_status ws_reserve(size_t np, size_t frames, size_t parts, size_t bins)
         g_ws.cap_parts = 0;
         if (hipMalloc(&g_ws.parts, sizeof(long long) * parts) != hipSuccess) return SC_ENOMEM;
         g_ws.cap_parts = parts;
-    }
-    if (bins > g_ws.cap_bins) {
-        if (hipDeviceSynchronize() != hipSuccess) return SC_EDEVICE;
-        (void)hipFree(g_ws.bins);
-        g_ws.bins = nullptr;
-        g_ws.cap_bins = 0;
-        if (hipMalloc(&g_ws.bins, sizeof(uint32_t) * bins) != hipSuccess) return SC_ENOMEM;
-        g_ws.cap_bins = bins;
     }
     return SC_OK;
 }
@@ -1146,12 +1163,6 @@ struct FuseBufs {
     FuseFrames* fr;
     uint32_t* bins;  // bins_words, or null
 };
-
-static size_t bins_words(int n, int W, int H)
-{
-    const size_t tiles = (size_t)((W + 15) / 16) * ((H + 15) / 16);
-    return n > kWarpFew ? tiles * (1 + 3 * (size_t)n) + 1 : 0;
-}
 
 static WarpBins warp_bins(uint32_t* words, int n, const sc_intrinsics& in)
 {
@@ -1326,7 +1337,7 @@ sc_status sc_color_prep(const uint8_t* rgb, int32_t n_frames, int32_t width, int
         return SC_EINVAL;
     std::lock_guard<std::mutex> lk(g_ws.mu);
     const sc_status st =
-        ws_reserve((size_t)width * height, (size_t)n_frames, 4 * (size_t)prep_tiles(width, height) * n_frames, 0);
+        ws_reserve((size_t)width * height, (size_t)n_frames, 4 * (size_t)prep_tiles(width, height) * n_frames);
     if (st != SC_OK) return st;
     const int tiles = prep_tiles(width, height);
     color_prep_kernel<<<dim3((unsigned)tiles, (unsigned)n_frames), 256, 0, (hipStream_t)stream>>>(
@@ -1348,10 +1359,10 @@ sc_status kf_fuse_frames(const float* const* depth, const uint8_t* const* rgb, c
     const sc_intrinsics in = *intr;
     const int64_t np = (int64_t)in.width * in.height;
     std::lock_guard<std::mutex> lk(g_ws.mu);
-    sc_status st = ws_reserve((size_t)np, (size_t)n_frames, 4 * (size_t)prep_tiles(in.width, in.height) * n_frames,
-                              bins_words(n_frames, in.width, in.height));
+    sc_status st = ws_reserve((size_t)np, (size_t)n_frames, 4 * (size_t)prep_tiles(in.width, in.height) * n_frames);
     if (st != SC_OK) return st;
-    const FuseBufs b{g_ws.wz, g_ws.cs, g_ws.acc, g_ws.parts, g_ws.wb, g_ws.d_fr, g_ws.bins};
+    uint32_t* bins = bins_words(n_frames, in.width, in.height) <= g_ws.cap_bins ? g_ws.bins : nullptr;
+    const FuseBufs b{g_ws.wz, g_ws.cs, g_ws.acc, g_ws.parts, g_ws.wb, g_ws.d_fr, bins};
     launch_fuse(b, depth, rgb, poses, n_frames, ref, in, *params, kf_depth, kf_weight, kf_rgba, s);
     return hipGetLastError() == hipSuccess ? SC_OK : SC_EDEVICE;
 }
