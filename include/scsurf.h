@@ -389,8 +389,9 @@ sc_status sc_volume_stats(sc_volume* vol, void* stream, int64_t* stats);
  * (SC_EINVAL) while the host store holds blocks.  hash_alloc,
  * sc_volume_import and tsdf_integrate_backward return SC_EINVAL while it
  * does; export, mesh and stats see the device blocks only.  The host store
- * (pinned memory) is emptied by sc_volume_reset, which keeps up to 256 MiB of
- * it for reuse, and freed with the volume. */
+ * (pinned memory) is emptied by sc_volume_reset; the next operation that
+ * streams keeps up to 256 MiB of it for reuse and frees the rest, and it is
+ * freed with the volume. */
 sc_status sc_stream_enable(sc_volume* vol, int32_t enable);
 
 /* Streams out (to the host store) every device block whose centre

@@ -48,6 +48,7 @@ struct StreamStore {
     std::vector<std::pair<unsigned char*, size_t>> chunks;  // pinned, blocks
     size_t cur = 0, pos = 0;                             // first record never used: in chunk cur at pos
     std::vector<unsigned char*> free_recs;
+    bool surplus = false;  // a reset left chunks beyond kKeepBytes: freed at the next wait
     StreamItem* in = nullptr;   // pinned lists
     StreamItem* out = nullptr;
     size_t in_cap = 0, out_cap = 0;
@@ -310,13 +311,26 @@ static bool streaming(const sc_volume* vol) { return vol->stream && vol->stream-
 
 int64_t stream_host_blocks(const sc_volume* vol) { return vol->stream ? (int64_t)vol->stream->where.size() : 0; }
 
+// The emptied store keeps chunks up to this size; the others are given back.
+constexpr size_t kKeepBytes = (size_t)256 << 20;
+
 // Waits for the report enqueued on `s`, and for the last use of the lists and
-// records if that was on another stream.
+// records if that was on another stream; then nothing on the device uses the
+// chunks that a reset left over.
 static sc_status wait_report(sc_volume* vol, hipStream_t s)
 {
+    StreamStore* st = vol->stream;
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess ||
-        hipEventSynchronize(vol->stream->done) != hipSuccess)
+        hipEventSynchronize(st->done) != hipSuccess)
         return SC_EDEVICE;
+    if (st->surplus) {
+        st->surplus = false;
+        size_t n = 0, bytes = 0;
+        while (n < st->chunks.size() && bytes + st->chunks[n].second * st->block_bytes <= kKeepBytes)
+            bytes += st->chunks[n++].second * st->block_bytes;
+        for (size_t c = n; c < st->chunks.size(); ++c) (void)hipHostFree(st->chunks[c].first);
+        st->chunks.resize(n);
+    }
     return SC_OK;
 }
 
@@ -545,9 +559,9 @@ static sc_status stream_in_plain_impl(sc_volume* vol, int parity, hipStream_t s)
         moved);
 }
 
-// The emptied store keeps chunks up to this size; the others are given back.
-constexpr size_t kKeepBytes = (size_t)256 << 20;
-
+// Host side of a reset, which only enqueues: it waits for nothing and frees
+// nothing (a kernel may still read the records).  No record is in use until
+// the next wait.
 void stream_clear(sc_volume* vol)
 {
     StreamStore* st = vol->stream;
@@ -555,14 +569,7 @@ void stream_clear(sc_volume* vol)
     st->where.clear();
     st->free_recs.clear();
     st->cur = st->pos = 0;
-    size_t n = 0, bytes = 0;
-    while (n < st->chunks.size() && bytes + st->chunks[n].second * st->block_bytes <= kKeepBytes)
-        bytes += st->chunks[n++].second * st->block_bytes;
-    // a kernel may still read the others: kept where that cannot be waited for
-    if (n < st->chunks.size() && hipEventSynchronize(st->done) == hipSuccess) {
-        for (size_t c = n; c < st->chunks.size(); ++c) (void)hipHostFree(st->chunks[c].first);
-        st->chunks.resize(n);
-    }
+    st->surplus = true;
 }
 
 void stream_destroy(sc_volume* vol)
