@@ -389,10 +389,16 @@ sc_status sc_volume_stats(sc_volume* vol, void* stream, int64_t* stats);
  * (SC_EINVAL) while the host store holds blocks.  hash_alloc,
  * sc_volume_import and tsdf_integrate_backward return SC_EINVAL while it
  * does; export, mesh and stats see the device blocks only.  The host store
- * (pinned memory) is emptied by sc_volume_reset; the next operation that
- * streams keeps up to 256 MiB of it for reuse and frees the rest, and it is
- * freed with the volume. */
+ * lies in pinned memory, which the kernels use directly; where no more can be
+ * pinned, in pageable memory, through a staging buffer.  It is emptied by
+ * sc_volume_reset; the next operation that streams keeps up to 256 MiB of it
+ * for reuse and frees the rest, and it is freed with the volume. */
 sc_status sc_stream_enable(sc_volume* vol, int32_t enable);
+
+/* Bounds the memory that the host store pins from here on (default: what can
+ * be pinned); what it needs beyond is pageable.  SC_EINVAL before the first
+ * sc_stream_enable. */
+sc_status sc_stream_pinned_limit(sc_volume* vol, int64_t bytes);
 
 /* Streams out (to the host store) every device block whose centre
  * s (8 b + 3.5) lies farther than `radius` metres from center (host

@@ -11,6 +11,7 @@
 // touch and the field equals the one a fully resident volume would hold,
 // bit for bit, whatever sphere the caller streams to.  The sphere decides
 // only how much stays on the device between calls.
+#include <stdlib.h>
 #include <string.h>
 
 #include <algorithm>
@@ -38,16 +39,32 @@ struct StreamReport {
     int32_t err;
 };
 
+// A host record.
+struct StreamRec {
+    unsigned char* p;
+    bool pinned;
+};
+struct StreamChunk {
+    unsigned char* p;
+    size_t blocks;
+    bool pinned;
+};
+constexpr size_t kStageBlocks = 256;  // records of pageable memory moved at once
+
 // Host side of the streaming mode.  The records lie in chunks of pinned
 // memory, which the kernels write and read themselves: no staging copy on
-// either side, and the host waits once an operation, for the report.
+// either side, and the host waits once an operation, for the report.  Where no
+// more memory can be pinned the chunks are pageable, and their records pass
+// through a pinned staging buffer, with a wait for every kStageBlocks of them.
 struct StreamStore {
     bool enabled = false;
     size_t block_bytes = 0;                              // one block's record in the pool
-    std::unordered_map<uint64_t, unsigned char*> where;  // block key -> host record
-    std::vector<std::pair<unsigned char*, size_t>> chunks;  // pinned, blocks
+    std::unordered_map<uint64_t, StreamRec> where;       // block key -> host record
+    std::vector<StreamChunk> chunks;
+    size_t pinned = 0, pinned_limit = SIZE_MAX;          // bytes of the pinned chunks, and at most
     size_t cur = 0, pos = 0;                             // first record never used: in chunk cur at pos
-    std::vector<unsigned char*> free_recs;
+    std::vector<StreamRec> free_recs;
+    unsigned char* stage = nullptr;                      // pinned, kStageBlocks records
     bool surplus = false;  // a reset left chunks beyond kKeepBytes: freed at the next wait
     StreamItem* in = nullptr;   // pinned lists
     StreamItem* out = nullptr;
@@ -278,34 +295,95 @@ static bool grow_keys(StreamStore* st, size_t n)
 static bool reserve_recs(StreamStore* st, size_t n)
 {
     size_t have = st->free_recs.size();
-    for (size_t c = st->cur; c < st->chunks.size(); ++c) have += st->chunks[c].second - (c == st->cur ? st->pos : 0);
+    for (size_t c = st->cur; c < st->chunks.size(); ++c) have += st->chunks[c].blocks - (c == st->cur ? st->pos : 0);
     while (have < n) {
-        const size_t blocks = st->chunks.empty() ? 1024 : std::min<size_t>(2 * st->chunks.back().second, 8192);
-        unsigned char* p = nullptr;
-        if (hipHostMalloc((void**)&p, blocks * st->block_bytes, hipHostMallocCoherent) != hipSuccess) {
-            (void)hipGetLastError();
-            return false;
+        const size_t blocks = st->chunks.empty() ? 1024 : std::min<size_t>(2 * st->chunks.back().blocks, 8192);
+        const size_t bytes = blocks * st->block_bytes;
+        StreamChunk c{nullptr, blocks, false};
+        if (bytes <= st->pinned_limit && st->pinned <= st->pinned_limit - bytes) {
+            c.pinned = hipHostMalloc((void**)&c.p, bytes, hipHostMallocCoherent) == hipSuccess;
+            if (!c.pinned) (void)hipGetLastError();
         }
-        st->chunks.emplace_back(p, blocks);
+        if (!c.pinned) c.p = static_cast<unsigned char*>(malloc(bytes));
+        if (!c.p) return false;
+        if (c.pinned) st->pinned += bytes;
+        st->chunks.push_back(c);
         have += blocks;
     }
     return true;
 }
 
+// Frees the chunks from the n-th on.
+static void drop_chunks(StreamStore* st, size_t n)
+{
+    for (size_t c = n; c < st->chunks.size(); ++c) {
+        if (st->chunks[c].pinned) {
+            (void)hipHostFree(st->chunks[c].p);
+            st->pinned -= st->chunks[c].blocks * st->block_bytes;
+        } else {
+            free(st->chunks[c].p);
+        }
+    }
+    st->chunks.resize(std::min(n, st->chunks.size()));
+}
+
 // A free record; there is one (reserve_recs).
-static unsigned char* take_rec(StreamStore* st)
+static StreamRec take_rec(StreamStore* st)
 {
     if (!st->free_recs.empty()) {
-        unsigned char* p = st->free_recs.back();
+        const StreamRec r = st->free_recs.back();
         st->free_recs.pop_back();
-        return p;
+        return r;
     }
-    while (st->pos == st->chunks[st->cur].second) {
+    while (st->pos == st->chunks[st->cur].blocks) {
         ++st->cur;
         st->pos = 0;
     }
-    return st->chunks[st->cur].first + st->block_bytes * st->pos++;
+    const StreamChunk& c = st->chunks[st->cur];
+    return StreamRec{c.p + st->block_bytes * st->pos++, c.pinned};
 }
+
+// The list of an operation's items, their records, and which of them go
+// through the staging buffer: the i-th such one at its place i modulo
+// kStageBlocks.
+struct StreamMoves {
+    std::vector<StreamRec> recs;
+    std::vector<size_t> staged;  // items
+
+    unsigned char* add(const StreamStore* st, StreamRec r)
+    {
+        recs.push_back(r);
+        if (r.pinned) return r.p;
+        staged.push_back(recs.size() - 1);
+        return st->stage + st->block_bytes * ((staged.size() - 1) % kStageBlocks);
+    }
+
+    // Runs move(a, b) over ranges [a, b) of the items that the staging buffer
+    // holds, and before or after it their copies between staging and records.
+    template <class Move>
+    sc_status run(const StreamStore* st, bool out, hipStream_t s, Move move) const
+    {
+        size_t a = 0, p = 0;
+        while (a < recs.size()) {
+            const size_t q = std::min(staged.size(), p + kStageBlocks);
+            const size_t b = q < staged.size() ? staged[q] : recs.size();
+            auto copy = [&] {
+                for (size_t i = p; i < q; ++i) {
+                    unsigned char* const rec = recs[staged[i]].p;
+                    unsigned char* const stage = st->stage + st->block_bytes * (i - p);
+                    memcpy(out ? rec : stage, out ? stage : rec, st->block_bytes);
+                }
+            };
+            if (!out) copy();
+            move(a, b);
+            if (q > p && (out || b < recs.size()) && hipStreamSynchronize(s) != hipSuccess) return SC_EDEVICE;
+            if (out) copy();
+            a = b;
+            p = q;
+        }
+        return SC_OK;
+    }
+};
 
 static bool streaming(const sc_volume* vol) { return vol->stream && vol->stream->enabled; }
 
@@ -326,10 +404,9 @@ static sc_status wait_report(sc_volume* vol, hipStream_t s)
     if (st->surplus) {
         st->surplus = false;
         size_t n = 0, bytes = 0;
-        while (n < st->chunks.size() && bytes + st->chunks[n].second * st->block_bytes <= kKeepBytes)
-            bytes += st->chunks[n++].second * st->block_bytes;
-        for (size_t c = n; c < st->chunks.size(); ++c) (void)hipHostFree(st->chunks[c].first);
-        st->chunks.resize(n);
+        while (n < st->chunks.size() && bytes + st->chunks[n].blocks * st->block_bytes <= kKeepBytes)
+            bytes += st->chunks[n++].blocks * st->block_bytes;
+        drop_chunks(st, n);
     }
     return SC_OK;
 }
@@ -369,11 +446,14 @@ static sc_status stream_in_keys(sc_volume* vol, const uint64_t* want, size_t n, 
     moved = 0;
     if (st->where.empty()) return SC_OK;
     if (!grow_items(st->in, st->in_cap, std::min(n, st->where.size()))) return SC_ENOMEM;
-    size_t m = 0;
+    StreamMoves moves;
     for (size_t i = 0; i < n; ++i) {
         auto it = st->where.find(want[i]);
-        if (it != st->where.end()) st->in[m++] = StreamItem{it->first, it->second, -1, -1};
+        if (it == st->where.end()) continue;
+        const size_t j = moves.recs.size();
+        st->in[j] = StreamItem{it->first, moves.add(st, it->second), -1, -1};
     }
+    const size_t m = moves.recs.size();
     if (m == 0) return SC_OK;
     if (nb + (int64_t)m > vol->p.max_blocks) {
         // the work cannot run with every block it may touch: the field is
@@ -381,11 +461,14 @@ static sc_status stream_in_keys(sc_volume* vol, const uint64_t* want, size_t n, 
         set_error_kernel<<<1, 1, 0, s>>>(vol->dev.err, SC_EPOOLFULL);
         return SC_EPOOLFULL;
     }
-    stream_in_kernel<<<(unsigned)m, 256, 0, s>>>(vol->dev, st->in, (int64_t)m, nb);
+    const sc_status e = moves.run(st, false, s, [&](size_t a, size_t b) {
+        stream_in_kernel<<<(unsigned)(b - a), 256, 0, s>>>(vol->dev, st->in + a, (int64_t)(b - a), nb + (int64_t)a);
+    });
+    if (e != SC_OK) return e;
     if (hipGetLastError() != hipSuccess || hipEventRecord(st->done, s) != hipSuccess) return SC_EDEVICE;
     // later uses of the records are enqueued behind the kernel
     for (size_t i = 0; i < m; ++i) {
-        st->free_recs.push_back(st->in[i].host);
+        st->free_recs.push_back(moves.recs[i]);
         st->where.erase(st->in[i].key);
     }
     st->blocks_in += (int64_t)m;
@@ -405,7 +488,8 @@ static sc_status evict(sc_volume* vol, const uint64_t* keys, const std::vector<c
     if (e == 0) return SC_OK;
     const int64_t live = nb - (int64_t)e;
     if (!grow_items(st->out, st->out_cap, e) || !reserve_recs(st, e)) return SC_ENOMEM;
-    size_t k = 0;
+    StreamMoves moves;
+    moves.recs.reserve(e);
     int64_t mover = live;
     for (int64_t i = 0; i < nb; ++i) {
         if (!out[i]) continue;
@@ -414,13 +498,18 @@ static sc_status evict(sc_volume* vol, const uint64_t* keys, const std::vector<c
             while (out[mover]) ++mover;
             from = mover++;
         }
-        st->out[k++] = StreamItem{keys[i], take_rec(st), (int32_t)i, (int32_t)from};
+        const size_t k = moves.recs.size();
+        st->out[k] = StreamItem{keys[i], moves.add(st, take_rec(st)), (int32_t)i, (int32_t)from};
     }
-    stream_out_kernel<<<(unsigned)std::max<size_t>(e, (size_t)vol->n_cu * 2), 256, 0, s>>>(vol->dev, st->out,
-                                                                                           (int64_t)e);
+    // (the hash table is emptied by every range)
+    const sc_status r = moves.run(st, true, s, [&](size_t a, size_t b) {
+        stream_out_kernel<<<(unsigned)std::max<size_t>(b - a, (size_t)vol->n_cu * 2), 256, 0, s>>>(
+            vol->dev, st->out + a, (int64_t)(b - a));
+    });
+    if (r != SC_OK) return r;
     hash_rebuild_kernel<<<vol->n_cu * 4, 256, 0, s>>>(vol->dev, live);
     if (hipGetLastError() != hipSuccess || hipEventRecord(st->done, s) != hipSuccess) return SC_EDEVICE;
-    for (size_t i = 0; i < e; ++i) st->where[st->out[i].key] = st->out[i].host;
+    for (size_t i = 0; i < e; ++i) st->where[st->out[i].key] = moves.recs[i];
     st->blocks_out += (int64_t)e;
     return SC_OK;
 }
@@ -576,7 +665,8 @@ void stream_destroy(sc_volume* vol)
 {
     StreamStore* st = vol->stream;
     if (!st) return;
-    for (const auto& c : st->chunks) (void)hipHostFree(c.first);
+    drop_chunks(st, 0);
+    if (st->stage) (void)hipHostFree(st->stage);
     if (st->in) (void)hipHostFree(st->in);
     if (st->out) (void)hipHostFree(st->out);
     if (st->report) (void)hipHostFree(st->report);
@@ -604,6 +694,7 @@ sc_status sc_stream_enable(sc_volume* vol, int32_t enable)
         st->block_bytes = sizeof(float) * (size_t)vol->dev.stride;
         if (hipMalloc(&st->d_req, sizeof(uint32_t)) != hipSuccess ||
             hipHostMalloc((void**)&st->report, sizeof(StreamReport), hipHostMallocCoherent) != hipSuccess ||
+            hipHostMalloc((void**)&st->stage, kStageBlocks * st->block_bytes, hipHostMallocCoherent) != hipSuccess ||
             hipEventCreateWithFlags(&st->done, hipEventDisableTiming) != hipSuccess) {
             (void)hipGetLastError();
             stream_destroy(vol);
@@ -618,6 +709,13 @@ sc_status sc_stream_enable(sc_volume* vol, int32_t enable)
     }
     if (!enable && !vol->stream->where.empty()) return SC_EINVAL;  // blocks still on the host
     vol->stream->enabled = enable != 0;
+    return SC_OK;
+}
+
+sc_status sc_stream_pinned_limit(sc_volume* vol, int64_t bytes)
+{
+    if (!vol || !vol->stream || bytes < 0) return SC_EINVAL;
+    vol->stream->pinned_limit = (size_t)bytes;
     return SC_OK;
 }
 
@@ -678,7 +776,7 @@ sc_status sc_stream_export(sc_volume* vol, int32_t* block_xyz, float* D, float* 
     int64_t b = 0;
     for (const auto& kv : st->where) {
         if (b >= cap) break;
-        const float* rec = reinterpret_cast<const float*>(kv.second);
+        const float* rec = reinterpret_cast<const float*>(kv.second.p);
         int x, y, z;
         unpack_key(kv.first, x, y, z);
         if (block_xyz) {

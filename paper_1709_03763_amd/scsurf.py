@@ -72,7 +72,7 @@ EXPORTS = ["sc_version", "sc_volume_create", "sc_volume_destroy", "sc_volume_res
            "sc_set_schedule", "sc_get_schedule", "sc_autotune", "sc_autotune_clear", "sc_batch_timing", "sc_batch_timing_read",
            "sc_volume_stats", "tsdf_integrate_backward", "sc_keyframe_pack", "sc_keyframe_pack_bytes", "sc_overlap",
            "sc_volume_mesh", "sc_mesh_vertices", "sc_nn_distance", "sc_mesh_table",
-           "sc_volume_import", "sc_stream_enable", "sc_stream_out", "sc_stream_in_all", "sc_stream_stats",
+           "sc_volume_import", "sc_stream_enable", "sc_stream_pinned_limit", "sc_stream_out", "sc_stream_in_all", "sc_stream_stats",
            "sc_stream_export"]
 
 _lib = None
@@ -107,6 +107,7 @@ def lib():
     L.sc_stream_enable.argtypes = [P, i32]
     L.sc_stream_out.argtypes = [P, P, ctypes.c_double, P]
     L.sc_stream_in_all.argtypes = [P, P]
+    L.sc_stream_pinned_limit.argtypes = [P, i64]
     L.sc_stream_stats.argtypes = [P, P, P]
     L.sc_stream_export.argtypes = [P, P, P, P, P, i64, ctypes.POINTER(i64)]
     L.sc_relative_motion.argtypes = [ctypes.POINTER(sc_pose), ctypes.POINTER(sc_pose), ctypes.POINTER(ctypes.c_double),
@@ -515,6 +516,11 @@ class Volume:
         """Streaming mode (Sec. 3): operations stream in the host-held blocks
         among their candidates before running."""
         check(lib().sc_stream_enable(self._h, int(bool(enable))), "sc_stream_enable")
+
+    def stream_pinned_limit(self, nbytes: int):
+        """Bounds the memory that the host store pins from here on; the rest
+        of it is pageable."""
+        check(lib().sc_stream_pinned_limit(self._h, int(nbytes)), "sc_stream_pinned_limit")
 
     def stream_out(self, center, radius: float, stream=None):
         """Moves the device blocks outside the sphere (center, radius) to the
