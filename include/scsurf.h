@@ -473,7 +473,11 @@ sc_status tsdf_integrate_backward(sc_volume* vol, const sc_keyframe* kfs, int32_
  * (blocks in pool order, cubes in voxel order within a block); the first
  * min(count, cap) are written and *n_tri (host) receives the count, so a
  * call with cap = 0 sizes the buffers.  Allocates temporaries (per-block
- * counts and offsets); synchronises. */
+ * counts and offsets); synchronises.
+ * The temporaries of this call, sc_mesh_vertices, sc_nn_distance and
+ * sc_volume_import are kept for the next one, up to 1 GiB in all, while the
+ * process has a volume: they are freed when any volume is destroyed, and when
+ * an allocation of this library finds no memory. */
 sc_status sc_volume_mesh(sc_volume* vol, void* stream, float* tri_xyz, int32_t* tri_keys, int64_t cap,
                          int64_t* n_tri);
 
@@ -490,7 +494,7 @@ sc_status sc_mesh_table(uint8_t* loops, uint8_t* ntri);
  * triangles); vert_xyz (device, cap x 3 FP32) receives the first
  * min(count, cap) distinct vertices in no fixed order, *n_vert (host) the
  * count.  SC_ERANGE if a voxel coordinate is outside [-2^19, 2^19).
- * Allocates a temporary hash set; synchronises. */
+ * Allocates a temporary hash set (see sc_volume_mesh); synchronises. */
 sc_status sc_mesh_vertices(const float* tri_xyz, const int32_t* tri_keys, int64_t n_tri, float* vert_xyz, int64_t cap,
                            int64_t* n_vert, void* stream);
 
@@ -505,7 +509,7 @@ sc_status sc_mesh_vertices(const float* tri_xyz, const int32_t* tri_keys, int64_
  * FP64) receives the sum of the distances when not NULL.  Exact search over a
  * uniform grid of cells slightly larger than the radius, valid while
  * |coordinate| / radius < 10^5.  SC_EINVAL for a radius that is not positive
- * and finite.  Allocates temporaries; synchronises. */
+ * and finite.  Allocates temporaries (see sc_volume_mesh); synchronises. */
 sc_status sc_nn_distance(const float* ref, int64_t n_ref, const float* query, int64_t n_query, float radius,
                          float* dist, double* sum, void* stream);
 

@@ -1006,8 +1006,8 @@ static sc_status ws_reserve(size_t np, size_t frames, size_t parts)
         g_ws.device = dev;
     }
     if (!g_ws.d_fr) {
-        if (hipMalloc(&g_ws.d_fr, sizeof(FuseFrames)) != hipSuccess) return SC_ENOMEM;
-        if (hipMalloc(&g_ws.wb, sizeof(double) * kMaxFrames) != hipSuccess) return SC_ENOMEM;
+        if (!device_alloc(&g_ws.d_fr, sizeof(FuseFrames))) return SC_ENOMEM;
+        if (!device_alloc(&g_ws.wb, sizeof(double) * kMaxFrames)) return SC_ENOMEM;
     }
     if (np * frames > g_ws.cap_px * g_ws.cap_frames || np > g_ws.cap_px) {
         if (hipDeviceSynchronize() != hipSuccess) return SC_EDEVICE;
@@ -1020,15 +1020,15 @@ static sc_status ws_reserve(size_t np, size_t frames, size_t parts)
         g_ws.cs = nullptr;
         g_ws.acc = nullptr;
         g_ws.cap_px = g_ws.cap_frames = 0;
-        if (hipMalloc(&g_ws.wz, sizeof(float) * px * fr) != hipSuccess) return SC_ENOMEM;
-        if (hipMalloc(&g_ws.cs, sizeof(uint16_t) * 4 * px * fr) != hipSuccess) return SC_ENOMEM;
-        if (hipMalloc(&g_ws.acc, sizeof(unsigned long long) * 2 * px) != hipSuccess) return SC_ENOMEM;
+        if (!device_alloc(&g_ws.wz, sizeof(float) * px * fr)) return SC_ENOMEM;
+        if (!device_alloc(&g_ws.cs, sizeof(uint16_t) * 4 * px * fr)) return SC_ENOMEM;
+        if (!device_alloc(&g_ws.acc, sizeof(unsigned long long) * 2 * px)) return SC_ENOMEM;
         g_ws.cap_px = px;
         g_ws.cap_frames = fr;
         (void)hipFree(g_ws.bins);
         g_ws.bins = nullptr;
         g_ws.cap_bins = bins_bound(px, px * fr);
-        if (hipMalloc(&g_ws.bins, sizeof(uint32_t) * g_ws.cap_bins) != hipSuccess) {
+        if (!device_alloc(&g_ws.bins, sizeof(uint32_t) * g_ws.cap_bins)) {
             (void)hipGetLastError();
             g_ws.bins = nullptr;
             g_ws.cap_bins = 0;
@@ -1039,7 +1039,7 @@ static sc_status ws_reserve(size_t np, size_t frames, size_t parts)
         (void)hipFree(g_ws.parts);
         g_ws.parts = nullptr;
         g_ws.cap_parts = 0;
-        if (hipMalloc(&g_ws.parts, sizeof(long long) * parts) != hipSuccess) return SC_ENOMEM;
+        if (!device_alloc(&g_ws.parts, sizeof(long long) * parts)) return SC_ENOMEM;
         g_ws.cap_parts = parts;
     }
     return SC_OK;

@@ -15,6 +15,17 @@ struct Scratch {
 Scratch scratch_take(size_t bytes);
 void scratch_give(Scratch& s, bool idle);
 void scratch_trim();
+// A volume begins (+1) or ends (-1): without one nothing is kept.
+void scratch_volumes(int change);
+
+// hipMalloc; where there is no memory, once more without the kept scratch.
+// Leaves no error behind.
+bool device_alloc_bytes(void** p, size_t bytes);
+template <class T>
+bool device_alloc(T** p, size_t bytes)
+{
+    return device_alloc_bytes(reinterpret_cast<void**>(p), bytes);
+}
 
 // Parts of one buffer, 256-byte aligned.
 struct Carve {

@@ -282,7 +282,7 @@ static bool grow_keys(StreamStore* st, size_t n)
     st->d_all = nullptr;
     st->keys_cap = 0;
     if (hipHostMalloc((void**)&st->h_keys, cap * sizeof(uint64_t), hipHostMallocCoherent) != hipSuccess ||
-        hipMalloc(&st->d_all, cap * sizeof(uint64_t)) != hipSuccess) {
+        !device_alloc(&st->d_all, cap * sizeof(uint64_t))) {
         (void)hipGetLastError();
         return false;
     }
@@ -692,7 +692,7 @@ sc_status sc_stream_enable(sc_volume* vol, int32_t enable)
         if (!vol->stream) return SC_ENOMEM;
         StreamStore* st = vol->stream;
         st->block_bytes = sizeof(float) * (size_t)vol->dev.stride;
-        if (hipMalloc(&st->d_req, sizeof(uint32_t)) != hipSuccess ||
+        if (!device_alloc(&st->d_req, sizeof(uint32_t)) ||
             hipHostMalloc((void**)&st->report, sizeof(StreamReport), hipHostMallocCoherent) != hipSuccess ||
             hipHostMalloc((void**)&st->stage, kStageBlocks * st->block_bytes, hipHostMallocCoherent) != hipSuccess ||
             hipEventCreateWithFlags(&st->done, hipEventDisableTiming) != hipSuccess) {

@@ -557,8 +557,8 @@ static bool rec_ready(sc_volume* vol)
     if (!r || r->failed) return false;
     if (r->d_keys) return true;
     const int cap = (int)std::min<int64_t>(kRecCap, vol->p.max_blocks);
-    if (hipMalloc(&r->d_keys, sizeof(uint64_t) * (size_t)kRecSlots * kRecShards * cap) != hipSuccess ||
-        hipMalloc(&r->d_count, sizeof(uint32_t) * (size_t)kRecSlots * kRecShards * kRecCountStride) != hipSuccess) {
+    if (!device_alloc(&r->d_keys, sizeof(uint64_t) * (size_t)kRecSlots * kRecShards * cap) ||
+        !device_alloc(&r->d_count, sizeof(uint32_t) * (size_t)kRecSlots * kRecShards * kRecCountStride)) {
         (void)hipGetLastError();
         hipFree(r->d_keys);
         r->d_keys = nullptr;
@@ -740,6 +740,7 @@ sc_status sc_volume_create(const sc_volume_params* p, sc_volume** out)
     sc_volume* vol = new (std::nothrow) sc_volume();
     if (!vol) return SC_ENOMEM;
     memset(vol, 0, sizeof(*vol));
+    scratch_volumes(+1);
     vol->p = *p;
     vol->device = dev;
     vol->n_cu = prop.multiProcessorCount;
@@ -781,30 +782,30 @@ sc_status sc_volume_create(const sc_volume_params* p, sc_volume** out)
     c.words = (p->max_batch_ops + 63) / 64;
     c.seg_cap = (uint32_t)(cb / 16);  // twice an even share; what does not fit goes to the last list
     bool ok = true;
-    ok &= hipMalloc(&d.keys, sizeof(uint64_t) * p->n_buckets) == hipSuccess;
-    ok &= hipMalloc(&d.vals, sizeof(int32_t) * p->n_buckets) == hipSuccess;
-    ok &= hipMalloc(&d.slot_keys, sizeof(uint64_t) * p->max_blocks) == hipSuccess;
-    ok &= hipMalloc(&d.pool, sizeof(float) * (size_t)d.stride * p->max_blocks) == hipSuccess;
-    ok &= hipMalloc(&d.n_blocks, 64) == hipSuccess;
-    ok &= hipMalloc(&d.err, 64) == hipSuccess;
-    ok &= hipMalloc(&c.keys, sizeof(uint64_t) * cb) == hipSuccess;
-    ok &= hipMalloc(&c.mask, sizeof(uint64_t) * cb * c.words) == hipSuccess;
-    ok &= hipMalloc(&c.list, sizeof(uint32_t) * c.cap) == hipSuccess;
-    ok &= hipMalloc(&c.sorted, sizeof(uint32_t) * cb) == hipSuccess;  // every bucket may be a candidate
-    ok &= hipMalloc(&c.skey, sizeof(uint64_t) * cb) == hipSuccess;
-    ok &= hipMalloc(&c.sslot, sizeof(int32_t) * cb) == hipSuccess;
-    ok &= hipMalloc(&c.counters, 64 * sizeof(uint32_t)) == hipSuccess;
-    ok &= hipMalloc(&c.bins, sizeof(uint32_t) * 2 * (kMaxBatchOps + 2)) == hipSuccess;
-    ok &= hipMalloc(&c.seg, sizeof(uint32_t) * ((size_t)kSegs * c.seg_cap + cb)) == hipSuccess;
-    ok &= hipMalloc(&c.seg_n, sizeof(uint32_t) * (kSegs + 1) * kRecCountStride) == hipSuccess;
-    ok &= hipMalloc(&c.cursors, sizeof(uint32_t) * 2 * kCursorSet) == hipSuccess;
-    ok &= hipMalloc(&c.big, sizeof(uint32_t) * (kBigCap + 1)) == hipSuccess;
-    ok &= hipMalloc(&c.stats, sizeof(unsigned long long) * 4 * kStatSlots * kStatStride) == hipSuccess;
-    ok &= hipMalloc(&vol->d_ops, sizeof(OpDesc) * p->max_batch_ops) == hipSuccess;
-    ok &= hipMalloc(&vol->adj_acc, sizeof(double) * 3 * kAdjChunk) == hipSuccess;
+    ok &= device_alloc(&d.keys, sizeof(uint64_t) * p->n_buckets);
+    ok &= device_alloc(&d.vals, sizeof(int32_t) * p->n_buckets);
+    ok &= device_alloc(&d.slot_keys, sizeof(uint64_t) * p->max_blocks);
+    ok &= device_alloc(&d.pool, sizeof(float) * (size_t)d.stride * p->max_blocks);
+    ok &= device_alloc(&d.n_blocks, 64);
+    ok &= device_alloc(&d.err, 64);
+    ok &= device_alloc(&c.keys, sizeof(uint64_t) * cb);
+    ok &= device_alloc(&c.mask, sizeof(uint64_t) * cb * c.words);
+    ok &= device_alloc(&c.list, sizeof(uint32_t) * c.cap);
+    ok &= device_alloc(&c.sorted, sizeof(uint32_t) * cb);  // every bucket may be a candidate
+    ok &= device_alloc(&c.skey, sizeof(uint64_t) * cb);
+    ok &= device_alloc(&c.sslot, sizeof(int32_t) * cb);
+    ok &= device_alloc(&c.counters, 64 * sizeof(uint32_t));
+    ok &= device_alloc(&c.bins, sizeof(uint32_t) * 2 * (kMaxBatchOps + 2));
+    ok &= device_alloc(&c.seg, sizeof(uint32_t) * ((size_t)kSegs * c.seg_cap + cb));
+    ok &= device_alloc(&c.seg_n, sizeof(uint32_t) * (kSegs + 1) * kRecCountStride);
+    ok &= device_alloc(&c.cursors, sizeof(uint32_t) * 2 * kCursorSet);
+    ok &= device_alloc(&c.big, sizeof(uint32_t) * (kBigCap + 1));
+    ok &= device_alloc(&c.stats, sizeof(unsigned long long) * 4 * kStatSlots * kStatStride);
+    ok &= device_alloc(&vol->d_ops, sizeof(OpDesc) * p->max_batch_ops);
+    ok &= device_alloc(&vol->adj_acc, sizeof(double) * 3 * kAdjChunk);
     ok &= hipHostMalloc((void**)&vol->h_ops, 2 * sizeof(OpDesc) * p->max_batch_ops, hipHostMallocDefault) ==
           hipSuccess;
-    ok &= hipMalloc(&vol->d_hdr, sizeof(BatchHdr)) == hipSuccess;
+    ok &= device_alloc(&vol->d_hdr, sizeof(BatchHdr));
     ok &= hipHostMalloc((void**)&vol->h_hdr, 2 * sizeof(BatchHdr), hipHostMallocDefault) == hipSuccess;
     ok &= hipStreamCreateWithFlags(&vol->cap_stream, hipStreamNonBlocking) == hipSuccess;
     ok &= hipEventCreateWithFlags(&vol->staged[0], hipEventDisableTiming) == hipSuccess;
@@ -864,7 +865,7 @@ void sc_volume_destroy(sc_volume* vol)
         if (e) hipEventDestroy(e);
     rec_destroy(vol);
     stream_destroy(vol);
-    scratch_trim();
+    scratch_volumes(-1);
     delete vol;
 }
 
