@@ -475,11 +475,15 @@ sc_status tsdf_integrate_backward(sc_volume* vol, const sc_keyframe* kfs, int32_
  * call with cap = 0 sizes the buffers.  Allocates temporaries (per-block
  * counts and offsets); synchronises.
  * The temporaries of this call, sc_mesh_vertices, sc_nn_distance and
- * sc_volume_import are kept for the next one, up to 1 GiB in all, while the
- * process has a volume: they are freed when any volume is destroyed, and when
- * an allocation of this library finds no memory. */
+ * sc_volume_import are kept for the next one, up to 1 GiB in all (128 MiB
+ * while the process has no volume).  They are freed when a volume is
+ * destroyed, when an allocation of this library finds no memory, and by
+ * sc_release_scratch. */
 sc_status sc_volume_mesh(sc_volume* vol, void* stream, float* tri_xyz, int32_t* tri_keys, int64_t cap,
                          int64_t* n_tri);
+
+/* Frees the temporaries kept between calls (waits for the device). */
+void sc_release_scratch(void);
 
 /* The case table sc_volume_mesh uses, as built on the host (no device
  * work): loops (host, 256 x 16 bytes) holds, per case (bit k set = corner k

@@ -15,7 +15,7 @@ struct Scratch {
 Scratch scratch_take(size_t bytes);
 void scratch_give(Scratch& s, bool idle);
 void scratch_trim();
-// A volume begins (+1) or ends (-1): without one nothing is kept.
+// A volume begins (+1) or ends (-1).
 void scratch_volumes(int change);
 
 // hipMalloc; where there is no memory, once more without the kept scratch.

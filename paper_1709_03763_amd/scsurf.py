@@ -71,7 +71,7 @@ EXPORTS = ["sc_version", "sc_volume_create", "sc_volume_destroy", "sc_volume_res
            "reintegrate_plain",
            "sc_set_schedule", "sc_get_schedule", "sc_autotune", "sc_autotune_clear", "sc_batch_timing", "sc_batch_timing_read",
            "sc_volume_stats", "tsdf_integrate_backward", "sc_keyframe_pack", "sc_keyframe_pack_bytes", "sc_overlap",
-           "sc_volume_mesh", "sc_mesh_vertices", "sc_nn_distance", "sc_mesh_table",
+           "sc_volume_mesh", "sc_release_scratch", "sc_mesh_vertices", "sc_nn_distance", "sc_mesh_table",
            "sc_volume_import", "sc_stream_enable", "sc_stream_pinned_limit", "sc_stream_out", "sc_stream_in_all", "sc_stream_stats",
            "sc_stream_export"]
 
@@ -108,6 +108,7 @@ def lib():
     L.sc_stream_out.argtypes = [P, P, ctypes.c_double, P]
     L.sc_stream_in_all.argtypes = [P, P]
     L.sc_stream_pinned_limit.argtypes = [P, i64]
+    L.sc_release_scratch.restype = None
     L.sc_stream_stats.argtypes = [P, P, P]
     L.sc_stream_export.argtypes = [P, P, P, P, P, i64, ctypes.POINTER(i64)]
     L.sc_relative_motion.argtypes = [ctypes.POINTER(sc_pose), ctypes.POINTER(sc_pose), ctypes.POINTER(ctypes.c_double),
@@ -690,6 +691,12 @@ def _fuse(entry: str, depth: torch.Tensor, rgb: torch.Tensor, R, t, intr, params
 def kf_fuse(depth: torch.Tensor, rgb: torch.Tensor, R, t, intr, params=None, ref=0, stream=None, out=None) -> Keyframe:
     """Fuses frames (n,H,W) / (n,H,W,3) at poses (R, t) into one keyframe."""
     return _fuse("kf_fuse", depth, rgb, R, t, intr, params, ref, stream, out)
+
+
+def release_scratch():
+    """Frees the device memory that mesh, vertex, distance and import calls
+    keep for the next one."""
+    lib().sc_release_scratch()
 
 
 def frames_fusible(depth, rgb) -> bool:

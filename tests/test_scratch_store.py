@@ -1,6 +1,6 @@
 """Host check of the kept device scratch (csrc/scratch.cpp, compiled here
 against a stand-in for the allocator with a limit): what is kept is bounded, is
-given back when no volume is left, and never stands in the way of an
+given back when a volume ends and on demand, and never stands in the way of an
 allocation of the library."""
 import ctypes
 import os
@@ -64,9 +64,13 @@ def store(tmp_path):
     return L
 
 
-def test_nothing_is_kept_without_a_volume(store):
-    assert store.take(0, 100 * MIB)
-    store.give(0, 1)
+def test_little_is_kept_without_a_volume(store):
+    for size in (90, 300):
+        assert store.take(0, size * MIB)
+        store.give(0, 1)
+        assert store.used() <= 128 * MIB
+    assert store.used() >= 90 * MIB
+    store.sc_release_scratch()
     assert store.used() == 0
     store.volumes(1)
     store.volumes(1)
