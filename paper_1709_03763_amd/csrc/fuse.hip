@@ -446,11 +446,26 @@ __global__ __launch_bounds__(256) void warp_bin_kernel(int n, sc_intrinsics in, 
 // samples all go to memory.
 // Bound: the vector ALU and the loads' latency, four source tiles at a time.
 // 60 frames of 640x480: 0.9 % of the samples outside the windows, 110 us with
-// warp_bin_kernel's 13 (242 us by a displacement a frame).  With few frames the
-// second launch costs more than it saves (whole fusions of 6 frames of a
-// turning camera 70 us against 65, of 10 frames 109 against 120), so groups of
-// more than kWarpFew take this way.
-constexpr int kWpOver = 64, kWarpFew = 8;
+// warp_bin_kernel's 13 (242 us by a displacement a frame).
+constexpr int kWpOver = 64;
+
+static int warp_tiles(int W, int H) { return ((W + 15) / 16) * ((H + 15) / 16); }
+
+// Whether n frames of W x H pixels are warped by their source tiles.  It costs
+// a launch and one pass over the frames' tiles, and leaves a workgroup a
+// keyframe tile, so few tiles in all or too few keyframe tiles for the CUs go
+// by a displacement a frame.  Whole fusions of a room scan and of a turning
+// camera, by displacements / by tiles: 640x480 9 frames 117 / 127 and 109 / 115
+// us, 12 frames 132 / 142 and 127 / 127, 13 frames 142 / 149 and 138 / 134, 32
+// frames 327 / 267 and 278 / 237; 1280x960 8 frames 266 / 258 and 241 / 220, 9
+// frames 338 / 321 and 309 / 279 (with 8 at most the colours take another way);
+// 320x240 (300 tiles) 16 frames 82 / 95 and 86 / 95, 64 frames 201 / 238 and
+// 184 / 213.
+static bool warp_by_tiles(int n, int W, int H)
+{
+    const int tiles = warp_tiles(W, H);
+    return n > 8 && tiles >= 600 && (int64_t)n * tiles > 12 * 1200;
+}
 
 __global__ __launch_bounds__(256) void warp_bins_kernel(const float* __restrict__ wz, int n, sc_intrinsics in,
                                                         const FuseFrames* __restrict__ fr, unsigned long long* KW,
@@ -971,8 +986,7 @@ static int prep_tiles(int W, int H) { return prep_tiles_x(W) * ((H + kPrepTH - 1
 // Words of tile lists of n frames of W x H pixels.
 static size_t bins_words(int n, int W, int H)
 {
-    const size_t tiles = (size_t)((W + 15) / 16) * ((H + 15) / 16);
-    return n > kWarpFew ? tiles * (1 + 3 * (size_t)n) + 1 : 0;
+    return warp_by_tiles(n, W, H) ? (size_t)warp_tiles(W, H) * (1 + 3 * (size_t)n) + 1 : 0;
 }
 
 // At least bins_words of every W x H <= px and n W H <= total (W, H >= 3,
@@ -1168,7 +1182,7 @@ static WarpBins warp_bins(uint32_t* words, int n, const sc_intrinsics& in)
 {
     WarpBins b;
     b.tiles_x = (in.width + 15) / 16;
-    b.tiles = b.tiles_x * ((in.height + 15) / 16);
+    b.tiles = warp_tiles(in.width, in.height);
     b.cap = 2 * n;
     b.count = words;
     b.items = words + b.tiles + 1;
@@ -1187,7 +1201,8 @@ static void launch_fuse(const FuseBufs& b, const float* const* depth, const uint
     FuseInit init;
     init.acc = b.acc;
     init.fr = b.fr;
-    const WarpBins bins = n_frames > kWarpFew && b.bins ? warp_bins(b.bins, n_frames, in) : WarpBins{};
+    const WarpBins bins = warp_by_tiles(n_frames, in.width, in.height) && b.bins ? warp_bins(b.bins, n_frames, in)
+                                                                                : WarpBins{};
     init.bins = bins;
     init.Z0 = depth[0];
     init.C0 = rgb[0];
