@@ -761,14 +761,11 @@ __device__ inline void nn_range(const NnGrid& g, int cx, int cy, int cz, uint32_
 // (one atomic a wavefront on the sum had serialised).
 constexpr int kNnLanes = 2;
 
+// The minimum of a query's lanes, two neighbours.
 __device__ inline float nn_group_min(float x)
 {
-    // lanes exchanged by 1 and 2 within four, then the halves of eight
-    if (kNnLanes > 1) x = fminf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false)));
-    if (kNnLanes > 2) x = fminf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false)));
-    if (kNnLanes > 4)
-        x = fminf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, false)));
-    return x;
+    static_assert(kNnLanes == 2, "one exchange");
+    return fminf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false)));
 }
 
 __global__ __launch_bounds__(256) void nn_query_kernel(const float* __restrict__ q, int64_t n, NnGrid g, bool empty,
