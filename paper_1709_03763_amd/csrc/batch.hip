@@ -1557,11 +1557,14 @@ sc_status run_candidates(sc_volume* vol, const OpDesc* ops, int n_ops, const sc_
             from_cells = from_cells && ops[o].cells != nullptr;
         }
     // 32-pixel tiles for unpacked keyframes whose 64-pixel tiles span more than
-    // four blocks at 2 m: such a tile's blocks crowd its LDS set.  Sixteen
-    // keyframes at 320x240 (1 cm voxels, six blocks): candidate stage 291 us
-    // on 64-pixel tiles, 136 on 32; at 640x480 (three blocks) 152 and 134, but
-    // eight keyframes 78 and 133.  Packed keyframes' bit maps do not crowd:
-    // 85 and 140 us for sixteen at 640x480, 93 and 95 at 320x240
+    // four blocks at 2 m: such a tile's blocks crowd its LDS set, however many
+    // operations there are.  Everything but the voxel pass of 1, 2, 4, 8 and 16
+    // integrations, on 64-pixel / on 32-pixel tiles: 320x240 with 1 cm voxels
+    // (six blocks) 125 185 190 204 302 / 95 102 108 127 158 us, with 5 mm
+    // (twelve) 1146 .. 1197 / 533 .. 665, 640x480 with 5 mm (six) 1060 .. 1135 /
+    // 182 .. 482; with 1 cm (three) 104 110 141 158 195 / 107 111 123 176 211.
+    // Packed keyframes' bit maps do not crowd: candidate stage 85 / 140 us for
+    // sixteen at 640x480, 93 / 95 at 320x240
     const bool small = !from_cells && (float)kTileBatch * 2.0f > 4.0f * 8.0f * vol->p.voxel_size * in->fx;
     const int tile = small ? kTilePlain : kTileBatch;
     hdr->tiles_x = (in->width + tile - 1) / tile;

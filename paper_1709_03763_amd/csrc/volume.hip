@@ -393,7 +393,7 @@ __global__ __launch_bounds__(256) void export_kernel(VolDev v, int64_t cap, int3
 // A wavefront takes 64 columns of one row of cells, a lane a column of four
 // pixels (its loads issue together), and four lanes share a cell.  Bound: the
 // launch and one round of loads; records and cells in two kernels, the cells
-// reading every pixel again, took 3.6 + 5.4 us at 640x480, now 4.3.
+// reading every pixel again, took 5.1 + 5.5 us at 640x480, now 6.0 (traced).
 __global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ depth, const float* __restrict__ weight,
                                                    const uint32_t* __restrict__ color, uint4* out, float2* cells,
                                                    int width, int height, int cells_w, int64_t n_items)

@@ -111,8 +111,10 @@ class OnlineSession:
         R, t = np.array(self._R), np.array(self._t)
         if self.stream is None and scsurf.frames_fusible(self._depth, self._rgb):
             # where they lie: stacking copied 5 frames of 640x480 in 18 us of
-            # the keyframe's 165.  On the current stream only, whose order the
-            # frames' memory follows when they are let go of below.
+            # the keyframe's 165.  On the current stream only: the frames are
+            # let go of below, and memory allocated on this stream is reused in
+            # its order.  Frames of another stream's memory are the caller's to
+            # keep until this one is done, as they were with a stack of them.
             kf = scsurf.kf_fuse_frames(self._depth, self._rgb, R, t, self.intr)
         else:
             z = torch.stack(self._depth)
