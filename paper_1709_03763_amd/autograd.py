@@ -111,7 +111,7 @@ class TsdfIntegrate(torch.autograd.Function):
         batched = False
         if len(kfs) > 1:
             try:
-                volume.integrate_batch(kfs, intr, Rp, tp)
+                volume.integrate_batch(kfs, intr, Rp[:len(kfs)], tp[:len(kfs)])
                 batched = volume.query()[1] == scsurf.SC_OK and volume.host_blocks() == 0
             except scsurf.ScError:
                 pass
