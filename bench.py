@@ -36,7 +36,7 @@ STORAGE_VOXEL_BYTES = 16  # the voxel as stored here: FP64 D + FP32 W + RGBA8 co
 KF_PIXEL_BYTES = 12  # keyframe depth + weight + RGBA8 colour
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "voxel_pass_traffic_batched_reintegration.json")
 KERNEL_SOURCES = ["paper_1709_03763_amd/csrc/batch.hip", "paper_1709_03763_amd/csrc/kernels.hpp",
-                  "paper_1709_03763_amd/csrc/common.hpp"]
+                  "paper_1709_03763_amd/csrc/common.hpp", "paper_1709_03763_amd/csrc/pixel.hpp"]
 
 
 def log(msg):

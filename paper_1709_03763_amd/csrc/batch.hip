@@ -54,7 +54,7 @@ __device__ inline void batch_init(const OpDesc* __restrict__ ops, const BatchHdr
 
 // A de-integration whose touched-block record is complete takes its
 // candidates from the record instead of from frustum cells.
-__device__ inline bool uses_record(const OpDesc& op) { return op.rec_mode == 2 && op.rec_count[kRecLost] == 0u; }
+__device__ inline bool uses_record(const OpDesc& op) { return op.rec_mode == 2 && !(op.rec_count[kRecFull] & kRecLost); }
 
 // Candidate blocks of de-integrations from their records: every recorded
 // block is claimed in the candidate table and marked with the operation's
@@ -76,6 +76,8 @@ __global__ __launch_bounds__(256) void cand_record_kernel(const OpDesc* __restri
     for (int o = blockIdx.y; o < n_ops; o += gridDim.y) {
         const OpDesc& op = ops[o];
         if (op.rec_mode != 2) continue;
+        // with the word that uses_record reads, in one round of loads
+        const uint32_t n = min(op.rec_count[blockIdx.x * kRecCountStride], (uint32_t)op.rec_cap);
         if (!uses_record(op)) {
             const int tiles_x = (op.width + kTileBatch - 1) / kTileBatch;
             const int tiles = tiles_x * ((op.height + kTileBatch - 1) / kTileBatch);
@@ -87,7 +89,6 @@ __global__ __launch_bounds__(256) void cand_record_kernel(const OpDesc* __restri
             }
             continue;
         }
-        const uint32_t n = min(op.rec_count[blockIdx.x * kRecCountStride], (uint32_t)op.rec_cap);
         for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
             const uint64_t key = op.rec_keys[(size_t)blockIdx.x * op.rec_cap + i];
             int bx, by, bz;
@@ -1161,10 +1162,7 @@ __device__ inline bool ring_step(const OpDesc* __restrict__ ops, const VolDev& v
         // the integration touched the block: lane n_rec remembers the
         // operation, and the block's record appends are issued together
         // when the block is done (no atomic waits while gathers are in
-        // flight); a 65th operation flushes the list first
-        if (pb.n_rec == 64u) {
-            record_flush(ops, pb, lane);
-        }
+        // flight), or when 64 are waiting
         pb.rec_op = (lane == (int)pb.n_rec) ? op_c : pb.rec_op;
         pb.n_rec += 1u;
     }
@@ -1259,12 +1257,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void b
             Ring ring;
             ring.head = ring.tail = 0u;
             int part_c = 0;
-            for (;;) {
-                if (!ring_step<CM, kPacked>(ops, v, walk, pb, f0, f1, gc, op_c, part_c, lane, L, ring)) break;
-                if (!ring_step<CM, kPacked>(ops, v, walk, pb, f1, f0, gc, op_c, part_c, lane, L, ring)) break;
-            }
+            bool more;
+            do {
+                more = ring_step<CM, kPacked>(ops, v, walk, pb, f0, f1, gc, op_c, part_c, lane, L, ring) &&
+                       ring_step<CM, kPacked>(ops, v, walk, pb, f1, f0, gc, op_c, part_c, lane, L, ring);
+                // a round ends at most one operation; one copy of the appends,
+                // outside the steps (one in each step: voxel pass of 400
+                // operations 2.00 ms, so 1.90)
+                if (pb.n_rec == 64u || (!more && pb.n_rec)) record_flush(ops, pb, lane);
+            } while (more);
         }
-        if (pb.n_rec) record_flush(ops, pb, lane);
         n_pairs += pb.pairs;
         n_upd += pb.n_upd;
         const int all = (__ballot(pb.re_touch) ? 1 : 0) | (__ballot(pb.e_na) ? 2 : 0) | (__ballot(pb.e_w) ? 4 : 0);

@@ -81,12 +81,13 @@ struct OpDesc {
     // counters: part p holds up to rec_cap keys from rec_keys + p rec_cap, and
     // an append that finds its part full goes on to the others (record_put).
     uint64_t* rec_keys;
-    uint32_t* rec_count;  // part p: appends tried, at p kRecCountStride (may exceed rec_cap: full); then kRecLost
+    uint32_t* rec_count;  // part p: appends tried, at p kRecCountStride (may exceed rec_cap); kRecFull
     int32_t rec_cap;
 };
 constexpr int kRecShards = 16;
 constexpr int kRecCountStride = 32;  // one counter per 128 bytes
-constexpr int kRecLost = 1;          // word of rec_count: a key found every part full, the record is not used
+constexpr int kRecFull = 1;          // word of rec_count: bit p, part p is full
+constexpr uint32_t kRecLost = 1u << 31;  // its bit: a key found every part full, the record is not used
 static_assert(offsetof(OpDesc, za) == 64, "projection constants of OpDesc: za at byte 64");
 
 // Device view of a volume.

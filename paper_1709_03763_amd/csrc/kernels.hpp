@@ -655,31 +655,35 @@ __device__ inline bool update_f32(double& D, float& W, double C[3], double d, fl
 __device__ inline void record_clear(const OpDesc& o, int part)
 {
     o.rec_count[part * kRecCountStride] = 0u;
-    if (part == 0) o.rec_count[kRecLost] = 0u;
+    if (part == 0) o.rec_count[kRecFull] = 0u;
 }
 
 // Stores a key at place `pos` of a part, given by an addition to its counter.
-// Past the part's end it goes to the next part with room, so that a record
-// takes kRecShards rec_cap keys (16,384) however uneven the parts' shares are:
-// a lost record costs its de-integration up to 0.8 ms (25,600 blocks of 5 mm),
-// its tiles being generated by 16 workgroups.  The counters of full parts are
-// read before they are added to, and nothing more is tried once the record is
-// lost.
+// Past the part's end it goes to the next part not marked full, so that a
+// record takes kRecShards rec_cap keys (16,384) however uneven the parts'
+// shares are: a lost record costs its de-integration up to 0.8 ms (25,600
+// blocks of 5 mm), its tiles being generated by 16 workgroups.  Who stores at a
+// part's last place marks it, and who finds a part full that is not marked yet;
+// one load then tells a key where there is room, or that there is none.
 __device__ inline void record_put(const OpDesc& o, uint32_t part, uint32_t pos, uint64_t key)
 {
     const uint32_t cap = (uint32_t)o.rec_cap;
-    auto read = [](const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    uint32_t* const full = o.rec_count + kRecFull;
 #pragma unroll 1
-    for (int k = 1; pos >= cap; ++k) {
-        if (k == kRecShards || read(o.rec_count + kRecLost) != 0u) {
-            __hip_atomic_store(o.rec_count + kRecLost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (pos >= cap) {
+        const uint32_t m = __hip_atomic_load(full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!((m >> part) & 1u)) atomicOr(full, 1u << part);
+        const uint32_t open = ~(m | (1u << part)) & ((1u << kRecShards) - 1u);
+        if (open == 0u) {
+            if (!(m & kRecLost)) atomicOr(full, kRecLost);
             return;
         }
-        part = (part + 1u) % kRecShards;
-        uint32_t* const c = o.rec_count + part * kRecCountStride;
-        if (read(c) < cap) pos = atomicAdd(c, 1u);
+        const uint32_t above = open & ~((2u << part) - 1u);
+        part = (uint32_t)__ffs((int)(above ? above : open)) - 1u;
+        pos = atomicAdd(o.rec_count + part * kRecCountStride, 1u);
     }
     o.rec_keys[(size_t)part * cap + pos] = key;
+    if (pos == cap - 1u) atomicOr(full, 1u << part);
 }
 
 // ---------------------------------------------------------------------------
