@@ -35,21 +35,15 @@
 
 namespace sc {
 
-// Clears the batch's counters, cursors and histogram, and starts an empty
-// record for every integration that records its touched blocks; run by one
-// workgroup of the first candidate kernel (nothing else that kernel does
-// reads them).
-__device__ inline void batch_init(const OpDesc* __restrict__ ops, const BatchHdr* hdr, const CandDev& cd, int n_bins)
+// Clears the batch's counters, cursors and histogram; run by one workgroup of
+// the first candidate kernel (nothing else that kernel does reads them).
+__device__ inline void batch_init(const CandDev& cd, int n_bins)
 {
     for (int i = threadIdx.x; i < 8; i += blockDim.x) cd.counters[4 + i] = 0u;
     for (int i = threadIdx.x; i < 2 * kCursors; i += blockDim.x) cd.cursors[i * kCursorStride] = 0u;
     if (threadIdx.x < 2) cd.cursors[threadIdx.x * kCursorSet + kCursorDone] = 0u;
     if (threadIdx.x == 0) cd.big[0] = 0u;
     for (int i = threadIdx.x; i < 2 * n_bins; i += blockDim.x) cd.bins[i] = 0u;
-    for (int i = threadIdx.x; i < hdr->n_ops * kRecShards; i += blockDim.x) {
-        const OpDesc& op = ops[i / kRecShards];
-        if (op.rec_mode == 1) record_clear(op, i % kRecShards);
-    }
 }
 
 // A de-integration whose touched-block record is complete takes its
@@ -68,13 +62,16 @@ __global__ __launch_bounds__(256) void cand_record_kernel(const OpDesc* __restri
     __shared__ uint64_t lds[CandCfg<kTileBatch, kCellBatch>::lds_set];
     __shared__ uint16_t idx[CandCfg<kTileBatch, kCellBatch>::lds_set];
     __shared__ uint32_t fresh[kFresh], n_fresh, base;
-    if (blockIdx.x == 0 && blockIdx.y == 0) batch_init(ops, hdr, cd, n_bins);
+    if (blockIdx.x == 0 && blockIdx.y == 0) batch_init(cd, n_bins);
     const int n_ops = hdr->n_ops;
     const FreshList fl{fresh, &n_fresh, (int)((blockIdx.y * gridDim.x + blockIdx.x) % kSegs)};
     if (threadIdx.x == 0) n_fresh = 0u;
     __syncthreads();
     for (int o = blockIdx.y; o < n_ops; o += gridDim.y) {
         const OpDesc& op = ops[o];
+        // the integrations' records start empty (all cleared by one workgroup,
+        // that one was the last to end: 400 operations 60 us, so 48)
+        if (op.rec_mode == 1 && threadIdx.x == 0) record_clear(op, (int)blockIdx.x);
         if (op.rec_mode != 2) continue;
         // with the word that uses_record reads, in one round of loads
         const uint32_t n = min(op.rec_count[blockIdx.x * kRecCountStride], (uint32_t)op.rec_cap);
